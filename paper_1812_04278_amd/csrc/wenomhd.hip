@@ -605,7 +605,7 @@ wm_status launch_floors(wm_patch* p, S* hydro, const S* bcell) {
   hipLaunchKernelGGL(floor_kernel<S>, dim3(nb), dim3(RED_THREADS), 0, p->stream, p->g.N, p->cfg.gamma,
                      p->cfg.rho_floor, p->cfg.p_floor, hydro, bcell, p->floor_part());
   WM_LAUNCH_CHECK("floor kernel");
-  hipLaunchKernelGGL(floor_final_kernel, dim3(1), dim3(1), 0, p->stream, nb, p->floor_part(), p->floor_total(),
+  hipLaunchKernelGGL(floor_final_kernel, dim3(1), dim3(RED_THREADS), 0, p->stream, nb, p->floor_part(), p->floor_total(),
                      p->floor_reset ? 1 : 0);
   WM_LAUNCH_CHECK("floor count kernel");
   p->floor_reset = false;
@@ -910,7 +910,7 @@ wm_status wm_diagnostics(wm_patch* p, wm_diag* out) {
     hipLaunchKernelGGL(diag_partial_kernel<double>, dim3(nb), dim3(RED_THREADS), 0, p->stream, p->g, p->cfg.gamma,
                        1.0 / p->cfg.h, p->hyd<double>(), p->bf<double>(), p->bc<double>(), p->diag_part());
   WM_LAUNCH_CHECK("diag kernel");
-  hipLaunchKernelGGL(diag_final_kernel, dim3(1), dim3(64), 0, p->stream, nb, p->diag_part(), p->diag_out());
+  hipLaunchKernelGGL(diag_final_kernel, dim3(1), dim3(RED_THREADS), 0, p->stream, nb, p->diag_part(), p->diag_out());
   WM_LAUNCH_CHECK("diag final kernel");
   double h[13];
   if ((s = hip_check(hipMemcpyAsync(h, p->diag_out(), sizeof(h), hipMemcpyDeviceToHost, p->stream), "diag copy")) !=
