@@ -310,7 +310,7 @@ wm_status wm_profile(wm_patch* p, int enable);
 
 /* Synchronises the stream and reports the session: out[2*c] = number of
  * launches and out[2*c+1] = summed milliseconds of kernel class c, with
- * c = 0 sweeps, 1 update (divergence + CT + RK), 2 zone-B interpolation,
+ * c = 0 sweeps (a launch of all three axes counts as three), 1 update (divergence + CT + RK), 2 zone-B interpolation,
  * 3 time-step reduction, 4 other (adjoint kernels).  n_out must be >= 10. */
 wm_status wm_profile_report(wm_patch* p, double* out, int n_out);
 

@@ -10,8 +10,8 @@
  *   [3] central flux / face state / differences formed, [4] after the
  *   difference stores and their barriers, [5] eigensystem and WENO done,
  *   [6] flux stores issued, [7] the hardware id of the wave's compute unit.
- * Layout: stamps[(block * 4 + wave) * 8 + q], block the linear id
- * (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x of the launch.
+ * Layout: stamps[(block * 4 + wave) * 8 + q], block the number of the block
+ * among those of its axis (one launch covers the three axes).
  */
 #ifndef WENOMHD_CLOCK_H
 #define WENOMHD_CLOCK_H

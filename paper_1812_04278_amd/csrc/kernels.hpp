@@ -1,9 +1,10 @@
 // HIP kernels of the WENO5-CT step for gfx950 (wave64, 256-thread blocks).
 //
-//   sweep_kernel<AXIS>   face fluxes along one axis: zone prologue staged in
-//                        LDS, one face per lane, eigensystem + projections in
-//                        registers.  Writes the five hydro flux components
-//                        (global frame) and the two CT transport fluxes.
+//   sweep_kernel         face fluxes along the three axes, one launch: zone
+//                        prologue staged in LDS, one face per lane,
+//                        eigensystem + projections in registers.  Writes the
+//                        five hydro flux components (global frame) and the
+//                        two CT transport fluxes of each axis.
 //   update_kernel<STAGE> flux divergence, corner fluxes, face-B right-hand
 //                        side and the SSP-RK3 increment, one zone per lane.
 //   bcell_kernel         zone B = fourth-order interpolation of the face field.
@@ -76,17 +77,21 @@ __device__ __forceinline__ void face_stencil(int c, int n, int wall, int idx[4],
 // ---------------------------------------------------------------------------
 // directional sweep
 // ---------------------------------------------------------------------------
-// Tile of TA faces along the sweep axis by TB faces across it (256 lanes, one
-// face each), for work type TW.  The x sweep uses 128 x 2 (266 zones for 256
-// faces; a wave reads whole 128-byte lines of a row), 0.5% faster than 64 x 4.
-// The y and z sweeps have x across: in FP64 32 x 8 (296 zones; rows of 64
-// bytes), which fits three blocks per CU in LDS, against 16 x 16 (336 zones,
-// 128-byte rows) in the FP32 work type (32 x 8 measured 1% slower there); 64 x 4
-// (276 zones, 32-byte rows) measured 4% slower in FP64.
-template <int AXIS, typename TW> struct SweepTile {
-  static constexpr int TA = sizeof(TW) == 8 ? 32 : 16, TB = sizeof(TW) == 8 ? 8 : 16;
+// A block computes a tile of ta faces along the sweep axis in tb columns, one
+// face per lane, ta * tb <= 256, both chosen at run time (choose_tile in
+// wenomhd.hip).  The columns of an axis are numbered through both directions
+// across it (x: y + ny z; y: x + nx z; z: x + nx y), so a tile's columns may lie in
+// two planes and no lanes are left at the end of a row.  Tiles fixed at 32 x 8
+// (y, z) and 128 x 2 (x) left 22% of the lanes idle at 75 zones, half of them at
+// 36 and 88% of the x sweep's at 16: a 97 x 75 x 61 step took 584 us against 474
+// now, 48 x 40 x 36 (WENO-Z, four steps) 759 against 502.  At 256^3, where both
+// fill the lanes, the run-time column count costs nothing that shows (13.56-13.78
+// ms per step against 13.59-13.91 with the y and z tiles fixed, two runs each).
+template <typename TW> struct SweepTile {
+  // zones a tile may hold, (ta + 5) * tb: what three blocks per CU leave of the
+  // 160 KB of LDS, allocated in units of 1,280 bytes
+  static constexpr int ZONES = sizeof(TW) == 8 ? 304 : 372;
 };
-template <typename TW> struct SweepTile<0, TW> { static constexpr int TA = 128, TB = 2; };
 constexpr int SW_THREADS = 256;
 constexpr int SW_HL = 2, SW_HR = 3;          // stencil zones i-2 .. i+3
 constexpr int SW_NQ = 14;                    // q (7) and F (7) per zone
@@ -148,19 +153,33 @@ __device__ __forceinline__ SpeedKey wave_max_key(SpeedKey k) {
   return ((SpeedKey)hm << 32) | lm;
 }
 
+// Run-time tile of one axis: ntile tiles along it, and 2^20 over a divisor,
+// rounded up, for the quotients of lane and zone numbers below 2^9 by it
+// (n * divisor < 2^20, so the rounding never reaches the next integer).
+constexpr int SW_DIV_SHIFT = 20;
+struct SweepAxis {
+  int ta, tb, ntile;
+  unsigned div_ta, div_na, div_tb;   // of ta, ta + 5 and tb
+  int ncol;                          // columns across the axis
+  unsigned blk0;                     // first block of the axis
+};
+
 template <typename S>
 struct SweepArgs {
   Grid g;
   Phys ph;
   const S* hydro;        // [5][N] rho, mx, my, mz, E
   const S* bcell;        // [3][N] zone B
-  S* fhydro;             // [5][N] interface flux, global frame (rho, mx, my, mz, E)
-  S* T;                  // [2][N] transport fluxes T^n_t1, T^n_t2
-  double* dbg;           // optional [9][N]: 7 sweep-frame flux components + 2 T
-  S* wallF;              // walled sweep axis: [5][nB * nC] fluxes through the lower wall face
+  S* faces;              // [21][N]: interface fluxes F^x, F^y, F^z (5 each, global frame: rho, mx, my, mz, E),
+                         // then the transport fluxes T^n_t1, T^n_t2 of x, y, z
+  double* dbg;           // optional [9][N] (one axis launched): 7 sweep-frame flux components + 2 T
+  S* wallF[3];           // walled axes: [5][columns] fluxes through the lower wall face
   SpeedKey* smax_blk;    // optional: per wave (4 per block), the maximum of |v_n| + c_fast over its zones (cfl_key)
+  SweepAxis ax[3];
+  unsigned nblk;         // blocks of all axes
+  double inv_nx;
 #ifdef WM_SWEEP_CLOCK
-  unsigned long long* clk;   // clock build: [block][wave][8] phase stamps, or null
+  unsigned long long* clk[3];   // clock build: per axis [block][wave][8] phase stamps, or null
 #endif
 };
 
@@ -188,14 +207,9 @@ __device__ __forceinline__ int sweep_zone(int z, int n, int wall, double& flip) 
 // LDS per block, two arrays: zone q and F in FP64 (the differences are formed
 // in FP64, then stored over them), and the zone primitives and speeds in the
 // work type TW.
-template <int AXIS, typename TW> constexpr int sweep_zones() {
-  return (SweepTile<AXIS, TW>::TA + SW_HL + SW_HR) * SweepTile<AXIS, TW>::TB;
-}
-template <int AXIS, typename TW> constexpr size_t sweep_q_doubles() {
-  return (size_t)SW_NQ * sweep_zones<AXIS, TW>();
-}
-template <int AXIS, typename TW> constexpr size_t sweep_p_doubles() {
-  return ((size_t)SW_NPF * sweep_zones<AXIS, TW>() * sizeof(TW) + 7) / 8;
+template <typename TW> constexpr size_t sweep_q_doubles() { return (size_t)SW_NQ * SweepTile<TW>::ZONES; }
+template <typename TW> constexpr size_t sweep_p_doubles() {
+  return ((size_t)SW_NPF * SweepTile<TW>::ZONES * sizeof(TW) + 7) / 8;
 }
 
 // Phases: (1) zone prologue of the tile and its halo into LDS; (2) per face:
@@ -210,32 +224,52 @@ template <int AXIS, typename TW> constexpr size_t sweep_p_doubles() {
 // of the eq. (cfl) signal speed over its zones to a.smax_blk (the first stage
 // of a step), a separate instantiation so that the other sweeps carry none of it.
 
-template <int AXIS, bool WENO_Z, typename TW, typename S, bool DTMAX = false>
-__global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
-  constexpr int TA = SweepTile<AXIS, TW>::TA, TB = SweepTile<AXIS, TW>::TB;
-  constexpr int NA = TA + SW_HL + SW_HR;     // zones along the axis
-  constexpr int NI = TA + 4;                 // interfaces i-3/2 .. i+TA+3/2
-  constexpr int NC = NA * TB;
-  constexpr int NIF = NI * TB;
-  static_assert(TA * TB == SW_THREADS, "one face per lane");
-  static_assert(TA >= 4, "extra interfaces are built by lanes fa < 4");
-  __shared__ double sQ[sweep_q_doubles<AXIS, TW>()];
-  __shared__ double sP[sweep_p_doubles<AXIS, TW>()];
+template <int AXIS, bool WENO_Z, typename TW, typename S, bool DTMAX>
+__device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, double* sQ, double* sP) {
+  constexpr int NC = SweepTile<TW>::ZONES;   // LDS pitch of one zone value
+  // and of one difference: in the FP32 work type a multiple of 64, so that one
+  // instruction reads two of them (ds_read2st64); in FP64 that does not fit the LDS
+  constexpr int ND = sizeof(TW) == 8 ? NC : 384;
+  static_assert(ND >= NC && SW_NQ * ND * sizeof(TW) <= SW_NQ * NC * sizeof(double), "differences alias the zone values");
   double* Q = sQ;                            // [14][NC] zone q and F, later the differences
-  TW* Pz = reinterpret_cast<TW*>(sP);        // [11][NC] zone primitives and speeds
-  TW* Dl = reinterpret_cast<TW*>(sQ);        // [14][NIF] interface differences (aliases Q)
+  TW* Pz = reinterpret_cast<TW*>(sP);        // [8][NC] zone primitives and speeds
+  TW* Dl = reinterpret_cast<TW*>(sQ);        // [14][ND] interface differences (aliases Q)
 
   const Grid& g = a.g;
+  const SweepAxis& ax = a.ax[AXIS];
+  const int TA = ax.ta, TB = ax.tb;
+  const int NA = TA + SW_HL + SW_HR;         // zones along the axis
+  const int NI = TA + 4;                     // interfaces i-3/2 .. i+TA+3/2
+  const int ncell = NA * TB;
   const int nA = AXIS == 0 ? g.nx : (AXIS == 1 ? g.ny : g.nz);
-  const int nB = AXIS == 0 ? g.ny : g.nx;
   constexpr int CN = AXIS, CT1 = (AXIS + 1) % 3, CT2 = (AXIS + 2) % 3;
-  auto cidx = [](int aa, int bb) { return AXIS == 0 ? bb * NA + aa : aa * TB + bb; };
-  auto iidx = [](int ia, int bb) { return AXIS == 0 ? bb * NI + ia : ia * TB + bb; };
+  auto cidx = [&](int aa, int bb) { return AXIS == 0 ? bb * NA + aa : aa * TB + bb; };
+  auto iidx = [&](int ia, int bb) { return AXIS == 0 ? bb * NI + ia : ia * TB + bb; };
+  // quotient of a lane or zone number by ta, ta + 5 or tb
+  auto quot = [](int n, unsigned div) { return (int)(((unsigned)n * div) >> SW_DIV_SHIFT); };
+  auto split_cell = [&](int cell, int& aa, int& bb) {
+    if (AXIS == 0) { bb = quot(cell, ax.div_na); aa = cell - bb * NA; }
+    else           { aa = quot(cell, ax.div_tb); bb = cell - aa * TB; }
+  };
+  auto split_face = [&](int t, int& fa, int& fb) {
+    if (AXIS == 0) { fb = quot(t, ax.div_ta); fa = t - fb * TA; }
+    else           { fa = quot(t, ax.div_tb); fb = t - fa * TB; }
+  };
   // faces 0 .. nA-1 (i+1/2), and with walls also the lower wall face -1/2
   const int wl = g.wall[AXIS];
-  const int a0 = blockIdx.x * TA - wl;
-  const int b0 = blockIdx.y * TB;
-  const int c = blockIdx.z;
+  const unsigned grp = blk / (unsigned)ax.ntile;
+  const int a0 = (int)(blk - grp * (unsigned)ax.ntile) * TA - wl;
+  const int b0 = (int)grp * TB;
+  // element index of zone ia of column q, 32 bits (N < 2^31): base + ia * stride.
+  // The quotient q / nx, q < 2^26 and nx <= 2^13, is exact from the rounded
+  // reciprocal ((q + 1/2) / nx is at least 2^-14 from an integer).
+  const unsigned stride = AXIS == 0 ? 1u : (AXIS == 1 ? (unsigned)g.nx : (unsigned)g.nx * (unsigned)g.ny);
+  auto column = [&](int q) -> unsigned {
+    if (AXIS == 0) return (unsigned)q * (unsigned)g.nx;
+    if (AXIS == 2) return (unsigned)q;
+    const unsigned z = (unsigned)(((double)q + 0.5) * a.inv_nx);
+    return (unsigned)q + z * ((unsigned)g.nx * (unsigned)(g.ny - 1));
+  };
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid) / 64;   // uniform: held in a scalar register
   // every array of the state and the fluxes within 4 GiB: buffer accesses with 32-bit offsets
@@ -248,7 +282,7 @@ __global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
 #endif
 
   // ---- (1) zone prologue, zones i-2 .. i+TA+2 along the axis (periodic wrap
-  // or wall mirror).  The tile has more zones than lanes (NR = 2 per lane at
+  // or wall mirror).  The tile may have more zones than lanes (NR = 2 per lane at
   // most): every lane issues the loads of all its zones before evaluating any,
   // so the block waits for one round trip to memory, not two.  Lanes past the
   // last zone load it again and discard it.
@@ -256,25 +290,19 @@ __global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
   double raw[NR][8];
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    const int cell = min(tid + r * SW_THREADS, NC - 1);
     int aa, bb;
-    if (AXIS == 0) { aa = cell % NA; bb = cell / NA; }
-    else           { bb = cell % TB; aa = cell / TB; }
+    split_cell(min(tid + r * SW_THREADS, ncell - 1), aa, bb);
     double flip;
     const int ia = sweep_zone(a0 - SW_HL + aa, nA, wl, flip);
-    const int ib = min(b0 + bb, nB - 1);
-    int i, j, k;
-    if (AXIS == 0)      { i = ia; j = ib; k = c; }
-    else if (AXIS == 1) { i = ib; j = ia; k = c; }
-    else                { i = ib; j = c;  k = ia; }
+    const unsigned gz = column(min(b0 + bb, ax.ncol - 1)) + (unsigned)ia * stride;
     if (off32) {
-      const unsigned off = g.at32(i, j, k) * (unsigned)sizeof(S);
+      const unsigned off = gz * (unsigned)sizeof(S);
 #pragma unroll
       for (int v = 0; v < 5; ++v) raw[r][v] = double(buf_load(buf_rsrc(a.hydro + v * g.N, abytes), off, S()));
 #pragma unroll
       for (int v = 0; v < 3; ++v) raw[r][5 + v] = double(buf_load(buf_rsrc(a.bcell + v * g.N, abytes), off, S()));
     } else {
-      const size_t gi = g.at(i, j, k);
+      const size_t gi = gz;
 #pragma unroll
       for (int v = 0; v < 5; ++v) raw[r][v] = double(a.hydro[v * g.N + gi]);
 #pragma unroll
@@ -287,7 +315,7 @@ __global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
     const int cell = tid + r * SW_THREADS;
-    if (cell >= NC) continue;
+    if (cell >= ncell) continue;
     const double* m = raw[r] + 1;
     const double* B = raw[r] + 5;
     double z[Z_NVAR];
@@ -307,8 +335,7 @@ __global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
   if constexpr (DTMAX) {   // the wave's maximum, one value per wave
     static_assert(SW_THREADS == 256, "four waves per block");
     const SpeedKey wk = wave_max_key(key);
-    if (__lane_id() == 0)
-      a.smax_blk[((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 4 + wave] = wk;
+    if (__lane_id() == 0) a.smax_blk[(ax.blk0 + blk) * 4 + wave] = wk;
   }
 #ifdef WM_SWEEP_CLOCK
   stamp[1] = clock64();
@@ -318,10 +345,11 @@ __global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
   stamp[2] = clock64();
 #endif
 
-  // ---- (2) per face: central flux, face state, LF speeds, own interface differences
+  // ---- (2) per face: central flux, face state, LF speeds, own interface
+  // differences.  Lanes past the tile's faces repeat face 0 (equal values) and
+  // store nothing.
   int fa, fb;
-  if (AXIS == 0) { fa = tid % TA; fb = tid / TA; }
-  else           { fb = tid % TB; fa = tid / TB; }
+  split_face(tid < TA * TB ? tid : 0, fa, fb);
   const int cL = cidx(fa + 2, fb), cR = cidx(fa + 3, fb);
   double Fc[7];
 #pragma unroll
@@ -333,11 +361,10 @@ __global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
   auto PR = [&](int v) { return double(Pz[v * NC + cR]); };
   auto QL = [&](int v) { return Q[v * NC + cL]; };
   auto QR = [&](int v) { return Q[v * NC + cR]; };
-  // face state: mean of the primitive states of zones i and i+1 (rho, B_t from q)
-  const double fp[8] = {0.5 * (QL(Z_RHO) + QR(Z_RHO)), 0.5 * (PL(FP_VN) + PR(FP_VN)),
-                        0.5 * (PL(FP_VT1) + PR(FP_VT1)), 0.5 * (PL(FP_VT2) + PR(FP_VT2)),
-                        0.5 * (PL(FP_BN) + PR(FP_BN)), 0.5 * (QL(Z_BT1) + QR(Z_BT1)),
-                        0.5 * (QL(Z_BT2) + QR(Z_BT2)), 0.5 * (PL(FP_P) + PR(FP_P))};
+  // face state: mean of the primitive states of zones i and i+1; rho and B_t, from
+  // q, here, the others in phase 3
+  const double f_rho = 0.5 * (QL(Z_RHO) + QR(Z_RHO)), f_bt1 = 0.5 * (QL(Z_BT1) + QR(Z_BT1)),
+               f_bt2 = 0.5 * (QL(Z_BT2) + QR(Z_BT2));
   double d0[SW_NQ], d1[SW_NQ];
   {
     const int c0 = cidx(fa, fb), c1 = cidx(fa + 1, fb);
@@ -356,14 +383,14 @@ __global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
   // differences stored as (Delta F, Delta q): j = 0..6 flux, 7..13 state
 #pragma unroll
   for (int v = 0; v < 7; ++v) {
-    Dl[v * NIF + iidx(fa, fb)] = TW(d0[7 + v]);
-    Dl[(7 + v) * NIF + iidx(fa, fb)] = TW(d0[v]);
+    Dl[v * ND + iidx(fa, fb)] = TW(d0[7 + v]);
+    Dl[(7 + v) * ND + iidx(fa, fb)] = TW(d0[v]);
   }
   if (fa < 4) {
 #pragma unroll
     for (int v = 0; v < 7; ++v) {
-      Dl[v * NIF + iidx(TA + fa, fb)] = TW(d1[7 + v]);
-      Dl[(7 + v) * NIF + iidx(TA + fa, fb)] = TW(d1[v]);
+      Dl[v * ND + iidx(TA + fa, fb)] = TW(d1[7 + v]);
+      Dl[(7 + v) * ND + iidx(TA + fa, fb)] = TW(d1[v]);
     }
   }
   __syncthreads();
@@ -372,7 +399,7 @@ __global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
 #endif
 
   // ---- (3) characteristic WENO flux of this face
-  auto dl = [&](int j, int k) -> TW { return Dl[j * NIF + iidx(fa + k, fb)]; };
+  auto dl = [&](int j, int k) -> TW { return Dl[j * ND + iidx(fa + k, fb)]; };
   // Lax-Friedrichs speed of field m (0-based), read when its pair needs it:
   // max(|v_L + sg c_L|, |v_R + sg c_R|), c = c_f (m = 0, 6), c_A (1, 5), c_s (2, 4), 0 (3)
   auto alf = [&](int m) -> TW {
@@ -383,7 +410,8 @@ __global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
     return TW(fmax(fabs(vL + sg * PL(sp)), fabs(vR + sg * PR(sp))));
   };
   FaceEig e;
-  face_eig(fp[0], fp[1], fp[2], fp[3], fp[4], fp[5], fp[6], fp[7], a.ph, e);
+  auto mean = [&](int v) { return 0.5 * (PL(v) + PR(v)); };
+  face_eig(f_rho, mean(FP_VN), mean(FP_VT1), mean(FP_VT2), mean(FP_BN), f_bt1, f_bt2, mean(FP_P), a.ph, e);
   // F = F_c + corr: the characteristic part is added onto the central term
   double Ff[7];
 #pragma unroll
@@ -405,46 +433,43 @@ __global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
   // FP64: the face's coordinates again, from the wave index and the lane id,
   // for the stores: holding them through phase 3 cost a spilled register (the
   // FP32 work type has registers to spare and measured 0.7% slower with this)
-  if constexpr (sizeof(TW) == 8) {
-    const int t = wave * 64 + (int)__lane_id();
-    if (AXIS == 0) { fa = t % TA; fb = t / TA; }
-    else           { fb = t % TB; fa = t / TB; }
-  }
-  if (a0 + fa < 0 && b0 + fb < nB) {          // the lower wall face (-1/2): hydro fluxes only
+  const int t = sizeof(TW) == 8 ? wave * 64 + (int)__lane_id() : tid;
+  if constexpr (sizeof(TW) == 8) split_face(t, fa, fb);
+  const bool inside = t < TA * TB && b0 + fb < ax.ncol;
+  if (a0 + fa < 0 && inside) {                // the lower wall face (-1/2): hydro fluxes only
     double fm[3];
     fm[CN] = Ff[1]; fm[CT1] = Ff[2]; fm[CT2] = Ff[3];
-    const size_t wi = (size_t)(b0 + fb) + (size_t)nB * c;
-    const size_t P = (size_t)nB * (AXIS == 2 ? g.ny : g.nz);
-    a.wallF[wi] = S(Ff[0]);
-    a.wallF[P + wi] = S(fm[0]);
-    a.wallF[2 * P + wi] = S(fm[1]);
-    a.wallF[3 * P + wi] = S(fm[2]);
-    a.wallF[4 * P + wi] = S(Ff[6]);
-  } else if (a0 + fa < nA && b0 + fb < nB) {
-  int i, j, k;
-  if (AXIS == 0)      { i = a0 + fa; j = b0 + fb; k = c; }
-  else if (AXIS == 1) { i = b0 + fb; j = a0 + fa; k = c; }
-  else                { i = b0 + fb; j = c;       k = a0 + fa; }
-  const size_t gi = g.at(i, j, k);
+    const size_t wi = (size_t)(b0 + fb), P = ax.ncol;
+    S* wf = a.wallF[AXIS];
+    wf[wi] = S(Ff[0]);
+    wf[P + wi] = S(fm[0]);
+    wf[2 * P + wi] = S(fm[1]);
+    wf[3 * P + wi] = S(fm[2]);
+    wf[4 * P + wi] = S(Ff[6]);
+  } else if (a0 + fa < nA && inside) {
+  const unsigned gz = column(b0 + fb) + (unsigned)(a0 + fa) * stride;
+  const size_t gi = gz;
   double fm[3];
   fm[CN] = Ff[1]; fm[CT1] = Ff[2]; fm[CT2] = Ff[3];
+  S* fh = a.faces + 5 * AXIS * g.N;
+  S* fT = a.faces + (15 + 2 * AXIS) * g.N;
   if (off32) {
-    const unsigned off = g.at32(i, j, k) * (unsigned)sizeof(S);
-    buf_store(buf_rsrc(a.fhydro, abytes), off, S(Ff[0]));
-    buf_store(buf_rsrc(a.fhydro + g.N, abytes), off, S(fm[0]));
-    buf_store(buf_rsrc(a.fhydro + 2 * g.N, abytes), off, S(fm[1]));
-    buf_store(buf_rsrc(a.fhydro + 3 * g.N, abytes), off, S(fm[2]));
-    buf_store(buf_rsrc(a.fhydro + 4 * g.N, abytes), off, S(Ff[6]));
-    buf_store(buf_rsrc(a.T, abytes), off, S(T1));
-    buf_store(buf_rsrc(a.T + g.N, abytes), off, S(T2));
+    const unsigned off = gz * (unsigned)sizeof(S);
+    buf_store(buf_rsrc(fh, abytes), off, S(Ff[0]));
+    buf_store(buf_rsrc(fh + g.N, abytes), off, S(fm[0]));
+    buf_store(buf_rsrc(fh + 2 * g.N, abytes), off, S(fm[1]));
+    buf_store(buf_rsrc(fh + 3 * g.N, abytes), off, S(fm[2]));
+    buf_store(buf_rsrc(fh + 4 * g.N, abytes), off, S(Ff[6]));
+    buf_store(buf_rsrc(fT, abytes), off, S(T1));
+    buf_store(buf_rsrc(fT + g.N, abytes), off, S(T2));
   } else {
-    a.fhydro[gi] = S(Ff[0]);
-    a.fhydro[g.N + gi] = S(fm[0]);
-    a.fhydro[2 * g.N + gi] = S(fm[1]);
-    a.fhydro[3 * g.N + gi] = S(fm[2]);
-    a.fhydro[4 * g.N + gi] = S(Ff[6]);
-    a.T[gi] = S(T1);
-    a.T[g.N + gi] = S(T2);
+    fh[gi] = S(Ff[0]);
+    fh[g.N + gi] = S(fm[0]);
+    fh[2 * g.N + gi] = S(fm[1]);
+    fh[3 * g.N + gi] = S(fm[2]);
+    fh[4 * g.N + gi] = S(Ff[6]);
+    fT[gi] = S(T1);
+    fT[g.N + gi] = S(T2);
   }
   if (a.dbg) {
 #pragma unroll
@@ -456,13 +481,27 @@ __global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
 #ifdef WM_SWEEP_CLOCK
   stamp[6] = clock64();
   stamp[7] = __smid();
-  if (a.clk && (tid & 63) == 0) {
-    const size_t blk = ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-    unsigned long long* o = a.clk + (blk * (SW_THREADS / 64) + tid / 64) * 8;
+  if (a.clk[AXIS] && (tid & 63) == 0) {
+    unsigned long long* o = a.clk[AXIS] + ((size_t)blk * (SW_THREADS / 64) + tid / 64) * 8;
 #pragma unroll
     for (int q = 0; q < 8; ++q) o[q] = stamp[q];
   }
 #endif
+}
+
+// The three axes in one launch, the blocks of x, y and z in turn: a small box
+// fills the chip better and the tails of the axes overlap.  At 16^3 and 32^3 an
+// axis alone has too few blocks for 256 CUs and took 8-9 and 9-14 us, three times
+// per stage: a step 111 -> 61 us (16^3) and 133 -> 86 us (32^3).
+template <bool WENO_Z, typename TW, typename S, bool DTMAX>
+__global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
+  __shared__ double sQ[sweep_q_doubles<TW>()];
+  __shared__ double sP[sweep_p_doubles<TW>()];
+  const unsigned blk = blockIdx.y * gridDim.x + blockIdx.x;
+  if (blk >= a.nblk) return;
+  if (blk < a.ax[1].blk0) sweep_tile<0, WENO_Z, TW, S, DTMAX>(a, blk, sQ, sP);
+  else if (blk < a.ax[2].blk0) sweep_tile<1, WENO_Z, TW, S, DTMAX>(a, blk - a.ax[1].blk0, sQ, sP);
+  else sweep_tile<2, WENO_Z, TW, S, DTMAX>(a, blk - a.ax[2].blk0, sQ, sP);
 }
 
 // ---------------------------------------------------------------------------

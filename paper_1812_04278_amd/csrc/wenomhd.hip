@@ -213,6 +213,12 @@ size_t adjoint_bytes(const wm_config* c) {
   return align_up(adjoint_arrays(c) * N * sizeof(double) + 256);
 }
 
+// A sweep launch: the axes' tiles and their blocks.
+struct SweepPlan {
+  SweepAxis ax[3];
+  unsigned nblk;
+};
+
 }  // namespace
 
 struct wm_patch {
@@ -230,11 +236,13 @@ struct wm_patch {
   bool floor_reset = true;   // the floor count restarts at the next floor pass
   int stage_done = -1;       // last completed stage of the current step (-1: none)
   bool dt_valid = false;
+  SweepPlan sweep_all;       // the launch of all three sweeps
   TilePlan adj_plan[3];      // adjoint sweep launch classes per axis (grid sizes >= 3)
   // event timing (wm_profile)
   bool prof = false;
   std::vector<hipEvent_t> ev;       // pool, 2 per record
   std::vector<int> ev_class;        // kernel class per record
+  std::vector<int> ev_count;        // launches it counts as (the three sweeps run in one)
   size_t n_rec = 0;
 
   template <typename S> S* us() const { return reinterpret_cast<S*>(scratch + lay.us); }
@@ -265,7 +273,7 @@ constexpr size_t kMaxRec = 8192;
 enum KClass { K_SWEEP = 0, K_UPDATE = 1, K_BCELL = 2, K_DT = 3, K_OTHER = 4, K_NCLASS = 5 };
 
 // Records a start event before a launch of class c; returns the record index or -1.
-long prof_begin(wm_patch* p, int c) {
+long prof_begin(wm_patch* p, int c, int count = 1) {
   if (!p->prof || p->n_rec >= kMaxRec) return -1;
   const size_t r = p->n_rec;
   while (p->ev.size() < 2 * (r + 1)) {
@@ -273,8 +281,12 @@ long prof_begin(wm_patch* p, int c) {
     if (hipEventCreate(&e) != hipSuccess) return -1;
     p->ev.push_back(e);
   }
-  if (p->ev_class.size() < r + 1) p->ev_class.resize(r + 1);
+  if (p->ev_class.size() < r + 1) {
+    p->ev_class.resize(r + 1);
+    p->ev_count.resize(r + 1);
+  }
   p->ev_class[r] = c;
+  p->ev_count[r] = count;
   if (hipEventRecord(p->ev[2 * r], p->stream) != hipSuccess) return -1;
   return (long)r;
 }
@@ -292,54 +304,94 @@ wm_status with_storage(const wm_patch* p, Fn&& fn) {
   return p->f32 ? fn(float{}) : fn(double{});
 }
 
-// Launch grid of the sweep along AXIS: the tile depends on the work type
-// (FP32 for the FP32 state and the mixed form); with walls the sweep also
-// computes the lower wall face (-1/2)
-template <int AXIS>
-dim3 sweep_grid(const wm_patch* p) {
-  const int nA = AXIS == 0 ? p->g.nx : (AXIS == 1 ? p->g.ny : p->g.nz);
-  const int nB = AXIS == 0 ? p->g.ny : p->g.nx;
-  const int nC = AXIS == 2 ? p->g.ny : p->g.nz;
-  auto grid_for = [&](auto tw) {
-    using TW = decltype(tw);
-    constexpr int TA = SweepTile<AXIS, TW>::TA, TB = SweepTile<AXIS, TW>::TB;
-    return dim3((nA + p->g.wall[AXIS] + TA - 1) / TA, (nB + TB - 1) / TB, nC);
-  };
-  const bool f32_work = p->f32 || p->cfg.precision == WM_MIXED;
-  return f32_work ? grid_for(float{}) : grid_for(double{});
+bool f32_work(const wm_patch* p) { return p->f32 || p->cfg.precision == WM_MIXED; }
+
+// Tile of one sweep axis of n faces in ncol columns that leaves the fewest
+// lanes idle: for each number of tiles along the axis, the shortest tile and as
+// many columns as 256 lanes and the LDS (max_zones) take.  Across the y and z
+// axes (xacross) rows shorter than 64 bytes are weighed down: 64 x 4 tiles ran
+// 4% slower than 32 x 8 in FP64, though both use every lane.
+SweepAxis choose_tile(int n, int ncol, int max_zones, bool xacross, size_t es) {
+  SweepAxis best{};
+  double best_cost = 0.0;
+  for (int nt = 1; nt <= n; ++nt) {
+    const int ta = std::max(4, (n + nt - 1) / nt);
+    if (nt > 1 && ta < 12) break;
+    if (ta > SW_THREADS || ta + 5 > max_zones) continue;
+    const int tb = std::min(std::min(SW_THREADS / ta, max_zones / (ta + 5)), ncol);
+    const double blocks = (double)((n + ta - 1) / ta) * ((ncol + tb - 1) / tb);
+    const size_t row = tb * es;
+    const double cost = blocks * (!xacross || row >= 64 ? 1.0 : (row >= 32 ? 1.04 : 1.12));
+    if (best.ta == 0 || cost < best_cost) {
+      best.ta = ta;
+      best.tb = tb;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
-size_t sweep_blocks(const dim3& g) { return (size_t)g.x * g.y * g.z; }
+// The launch of the axes in `mask` (bit d: axis d).
+SweepPlan sweep_plan(const wm_patch* p, int mask) {
+  const Grid& g = p->g;
+  const int n3[3] = {g.nx, g.ny, g.nz};
+  const int zones = f32_work(p) ? SweepTile<float>::ZONES : SweepTile<double>::ZONES;
+  const size_t es = p->f32 ? sizeof(float) : sizeof(double);
+  SweepPlan pl{};
+  unsigned blk = 0;
+  for (int d = 0; d < 3; ++d) {
+    const int n = n3[d] + g.wall[d], ncol = (int)(g.N / n3[d]);
+    SweepAxis& x = pl.ax[d];
+    x = choose_tile(n, ncol, zones, d != 0, es);
+    const unsigned one = 1u << SW_DIV_SHIFT;
+    x.div_ta = (one + x.ta - 1) / x.ta;
+    x.div_na = (one + x.ta + 4) / (x.ta + 5);
+    x.div_tb = (one + x.tb - 1) / x.tb;
+    x.ncol = ncol;
+    x.ntile = (n + x.ta - 1) / x.ta;
+    x.blk0 = blk;
+    if (mask >> d & 1) blk += (unsigned)x.ntile * (unsigned)((ncol + x.tb - 1) / x.tb);
+  }
+  pl.nblk = blk;
+  return pl;
+}
 
-template <int AXIS, typename S>
-wm_status launch_sweep(wm_patch* p, const S* hydro, const S* bcell, S* fh, S* T, double* dbg,
-                       SpeedKey* smax_blk = nullptr) {
+// Launches the sweeps of the axes in `mask` (7: all) of a state.  smax: optional,
+// the per-wave signal-speed maxima (4 per block), for the fused time step.
+template <typename S>
+wm_status sweeps(wm_patch* p, const S* hydro, const S* bcell, SpeedKey* smax = nullptr, int mask = 7,
+                 double* dbg = nullptr) {
+  const SweepPlan pl = mask == 7 ? p->sweep_all : sweep_plan(p, mask);
   SweepArgs<S> a;
   a.g = p->g;
   a.ph = p->ph;
   a.hydro = hydro;
   a.bcell = bcell;
-  a.fhydro = fh;
-  a.T = T;
+  a.faces = p->faces<S>();
   a.dbg = dbg;
-  a.wallF = p->g.wall[AXIS] ? p->wallF<S>(AXIS) : nullptr;
-  a.smax_blk = smax_blk;
+  a.smax_blk = smax;
+  a.nblk = pl.nblk;
+  a.inv_nx = 1.0 / p->g.nx;
+  for (int d = 0; d < 3; ++d) {
+    a.wallF[d] = p->g.wall[d] ? p->wallF<S>(d) : nullptr;
+    a.ax[d] = pl.ax[d];
 #ifdef WM_SWEEP_CLOCK
-  a.clk = nullptr;
+    const size_t nb = (d == 2 ? pl.nblk : pl.ax[d + 1].blk0) - pl.ax[d].blk0;
+    a.clk[d] = nb * (SW_THREADS / 64) * 8 <= g_sweep_clk_n[d] ? g_sweep_clk[d] : nullptr;
 #endif
-  const dim3 grid = sweep_grid<AXIS>(p);
-#ifdef WM_SWEEP_CLOCK
-  if ((size_t)grid.x * grid.y * grid.z * (SW_THREADS / 64) * 8 <= g_sweep_clk_n[AXIS]) a.clk = g_sweep_clk[AXIS];
-#endif
-  const long r = prof_begin(p, K_SWEEP);
+  }
+  // a grid dimension counts work-items in 32 bits: blocks past 2^20 go to y
+  const unsigned gx = std::min(pl.nblk, 1u << 20);
+  const dim3 grid(gx, (pl.nblk + gx - 1) / gx);
+  const long r = prof_begin(p, K_SWEEP, mask == 7 ? 3 : 1);
   // kernel choice: work type (FP32 for the FP32 state and the mixed form),
-  // weights, and whether the block writes its signal-speed maximum
+  // weights, and whether the waves write their signal-speed maxima
   auto go = [&](auto tw, auto wz, auto dtmax) {
-    hipLaunchKernelGGL((sweep_kernel<AXIS, decltype(wz)::value, decltype(tw), S, decltype(dtmax)::value>), grid,
+    hipLaunchKernelGGL((sweep_kernel<decltype(wz)::value, decltype(tw), S, decltype(dtmax)::value>), grid,
                        dim3(SW_THREADS), 0, p->stream, a);
   };
   auto pick_dt = [&](auto tw, auto wz) {
-    if (smax_blk) go(tw, wz, std::true_type{});
+    if (smax) go(tw, wz, std::true_type{});
     else go(tw, wz, std::false_type{});
   };
   auto pick_wz = [&](auto tw) {
@@ -354,21 +406,6 @@ wm_status launch_sweep(wm_patch* p, const S* hydro, const S* bcell, S* fh, S* T,
   }
   WM_LAUNCH_CHECK("sweep kernel");
   prof_end(p, r);
-  return WM_OK;
-}
-
-// smax: optional, the per-wave signal-speed maxima of the three sweeps in turn
-// (4 per block of each axis' grid), for the fused time step
-template <typename S>
-wm_status sweeps(wm_patch* p, const S* hydro, const S* bcell, SpeedKey* smax = nullptr) {
-  const size_t N = p->g.N;
-  S* f = p->faces<S>();
-  SpeedKey* s1 = smax ? smax + 4 * sweep_blocks(sweep_grid<0>(p)) : nullptr;
-  SpeedKey* s2 = smax ? s1 + 4 * sweep_blocks(sweep_grid<1>(p)) : nullptr;
-  wm_status s;
-  if ((s = launch_sweep<0, S>(p, hydro, bcell, f, f + 15 * N, nullptr, smax)) != WM_OK) return s;
-  if ((s = launch_sweep<1, S>(p, hydro, bcell, f + 5 * N, f + 17 * N, nullptr, s1)) != WM_OK) return s;
-  if ((s = launch_sweep<2, S>(p, hydro, bcell, f + 10 * N, f + 19 * N, nullptr, s2)) != WM_OK) return s;
   return WM_OK;
 }
 
@@ -596,6 +633,7 @@ void setup_patch(wm_patch* p, const wm_config* cfg, void* hip_stream, void* scra
   p->scratch = reinterpret_cast<char*>(scratch_buf);
   p->lay = L;
   p->f32 = cfg->precision == WM_MIXED_F32STATE;
+  p->sweep_all = sweep_plan(p, 7);
 }
 
 // Opt-in floors on a stage result (hydro with its zone field) and the count.
@@ -781,17 +819,15 @@ namespace {
 // wave values, or 0 when they do not fit there, in which case the step runs the
 // stand-alone time-step pass first (very thin grids, e.g. 1 x 1 x n).
 size_t fused_dt_blocks(const wm_patch* p) {
-  const size_t nb =
-      4 * (sweep_blocks(sweep_grid<0>(p)) + sweep_blocks(sweep_grid<1>(p)) + sweep_blocks(sweep_grid<2>(p)));
+  const size_t nb = 4 * (size_t)p->sweep_all.nblk;
   const size_t acc_bytes = 8 * p->g.N * (p->f32 ? sizeof(float) : sizeof(double));
   // (at most 2^31 values: the kernels index them in 32 bits)
   return nb * sizeof(SpeedKey) <= acc_bytes && nb <= (size_t(1) << 31) ? nb : 0;
 }
 
 wm_status launch_fused_dt(wm_patch* p) {
-  const unsigned n0 = (unsigned)(4 * sweep_blocks(sweep_grid<0>(p))),
-                 n1 = (unsigned)(4 * sweep_blocks(sweep_grid<1>(p))),
-                 n2 = (unsigned)(4 * sweep_blocks(sweep_grid<2>(p)));
+  const SweepPlan& pl = p->sweep_all;
+  const unsigned n0 = 4 * pl.ax[1].blk0, n1 = 4 * pl.ax[2].blk0 - n0, n2 = 4 * pl.nblk - n0 - n1;
   const unsigned nmax = std::max(n0, std::max(n1, n2));
   const int nb = (int)std::min<unsigned>((nmax + RED_THREADS - 1) / RED_THREADS, (unsigned)RED_BLOCKS);
   const long r = prof_begin(p, K_DT);
@@ -940,17 +976,11 @@ wm_status wm_debug_sweep(wm_patch* p, int axis, void* out) {
   wm_status s = check_bound(p);
   if (s != WM_OK) return s;
   if (!out) return fail(WM_ERR_ARG, "null output");
-  const size_t N = p->g.N;
   double* o = reinterpret_cast<double*>(out);
   if (axis < 0 || axis > 2) return fail(WM_ERR_ARG, "axis must be 0, 1 or 2");
   return with_storage(p, [&](auto tag) {
     using S = decltype(tag);
-    S* f = p->faces<S>();
-    switch (axis) {
-      case 0: return launch_sweep<0, S>(p, p->hyd<S>(), p->bc<S>(), f, f + 15 * N, o);
-      case 1: return launch_sweep<1, S>(p, p->hyd<S>(), p->bc<S>(), f + 5 * N, f + 17 * N, o);
-      default: return launch_sweep<2, S>(p, p->hyd<S>(), p->bc<S>(), f + 10 * N, f + 19 * N, o);
-    }
+    return sweeps<S>(p, p->hyd<S>(), p->bc<S>(), nullptr, 1 << axis, o);
   });
 }
 
@@ -1160,7 +1190,7 @@ wm_status wm_profile_report(wm_patch* p, double* out, int n_out) {
   for (size_t r = 0; r < p->n_rec; ++r) {
     float ms = 0.f;
     if ((s = hip_check(hipEventElapsedTime(&ms, p->ev[2 * r], p->ev[2 * r + 1]), "event time")) != WM_OK) return s;
-    out[2 * p->ev_class[r]] += 1.0;
+    out[2 * p->ev_class[r]] += p->ev_count[r];
     out[2 * p->ev_class[r] + 1] += ms;
   }
   return WM_OK;
