@@ -32,6 +32,10 @@ struct Grid {
   }
 };
 
+// q / n for q < 2^31 and n <= 2^13 from inv = 1.0 / n, exactly: (q + 1/2) / n is at
+// least 2^-14 from an integer, the rounding of the product at most 2^-21.
+__device__ __forceinline__ unsigned quot_by(unsigned q, double inv) { return (unsigned)(((double)q + 0.5) * inv); }
+
 // Raw buffer access to one array of at most 4 GiB: the array's base lives in a
 // scalar descriptor and the hardware adds the lane's 32-bit byte offset, so an
 // access costs no 64-bit address arithmetic.  Word 3 of the descriptor is the
@@ -260,14 +264,12 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
   const unsigned grp = blk / (unsigned)ax.ntile;
   const int a0 = (int)(blk - grp * (unsigned)ax.ntile) * TA - wl;
   const int b0 = (int)grp * TB;
-  // element index of zone ia of column q, 32 bits (N < 2^31): base + ia * stride.
-  // The quotient q / nx, q < 2^26 and nx <= 2^13, is exact from the rounded
-  // reciprocal ((q + 1/2) / nx is at least 2^-14 from an integer).
+  // element index of zone ia of column q, 32 bits (N < 2^31): base + ia * stride
   const unsigned stride = AXIS == 0 ? 1u : (AXIS == 1 ? (unsigned)g.nx : (unsigned)g.nx * (unsigned)g.ny);
   auto column = [&](int q) -> unsigned {
     if (AXIS == 0) return (unsigned)q * (unsigned)g.nx;
     if (AXIS == 2) return (unsigned)q;
-    const unsigned z = (unsigned)(((double)q + 0.5) * a.inv_nx);
+    const unsigned z = quot_by((unsigned)q, a.inv_nx);
     return (unsigned)q + z * ((unsigned)g.nx * (unsigned)(g.ny - 1));
   };
   const int tid = threadIdx.x;
@@ -520,7 +522,68 @@ struct UpdateArgs {
   double* rhs_out;       // optional [8][N]: the right-hand side itself (no state update)
   const double* dt;      // device scalar
   const S* wallF[3];     // per walled axis: [5][nB * nC] fluxes through the lower wall face
+  double inv_row, inv_ny;   // 1 / threads per row (nx, or nx / 2 with two zones each), 1 / ny
+  // stage 0, keys not null: dt = cfl_h / sum_d max of the nkeys[d] signal speeds
+  // of axis d (the axes in turn), formed by every block; block 0 also stores it
+  const SpeedKey* keys;
+  unsigned nkeys[3];
+  double cfl_h;
+  double *dt_out, *smax_out;
 };
+
+// Zone of a thread numbered through the box: no lanes idle at the end of a row
+// (blocks of 256-zone rows left half of them at nx = 128, and blocks of 64 zones a
+// quarter at 97: a 97 x 75 x 61 step 480 -> 453 us, the update of a 128^3 RK4 step
+// 155-179 -> 150-176).  Where nx is a multiple of 256 the row kernels stay: the
+// FP32-state update needs 93 registers instead of 87 with numbered threads, and a
+// 512^3 step took 83.1 ms against 81.5.
+__device__ __forceinline__ void thread_zone(unsigned t, double inv_row, unsigned row, double inv_ny, unsigned ny,
+                                            int& col, int& j, int& k) {
+  const unsigned r = quot_by(t, inv_row);
+  col = (int)(t - r * row);
+  k = (int)quot_by(r, inv_ny);
+  j = (int)(r - (unsigned)k * ny);
+}
+
+// dt of eq. (cfl) from the three maxima, as dt_final_kernel
+__device__ __forceinline__ double speed_of(SpeedKey k) {
+  return (k >> 63) ? __builtin_nan("") : __builtin_bit_cast(double, k);
+}
+
+// The time step of a step's first stage, by every block of its update for
+// itself: in a small box (at most DT_IN_UPDATE keys) reading them again is
+// cheaper than the two launches that reduce them first (16^3 step 62.5 -> 58 us,
+// 228 keys; even at 32^3, 1,536 keys).
+constexpr unsigned DT_IN_UPDATE = 1536;
+template <typename S>
+__device__ __forceinline__ double stage0_dt(const UpdateArgs<S>& a) {
+  __shared__ SpeedKey red[3][4];
+  const SpeedKey* base = a.keys;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    SpeedKey mx = 0;
+    for (unsigned q = threadIdx.x; q < a.nkeys[d]; q += 256) mx = kmax(mx, base[q]);
+    mx = wave_max_key(mx);
+    if ((threadIdx.x & 63) == 0) red[d][threadIdx.x >> 6] = mx;
+    base += a.nkeys[d];
+  }
+  __syncthreads();
+  double m[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+    m[d] = speed_of(kmax(kmax(red[d][0], red[d][1]), kmax(red[d][2], red[d][3])));
+  const double dt = a.cfl_h / ((m[0] + m[1]) + m[2]);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *a.dt_out = dt;
+    a.smax_out[0] = m[0]; a.smax_out[1] = m[1]; a.smax_out[2] = m[2];
+  }
+  // uniform: held in scalar registers (two vector registers more would cost the
+  // FP64 two-zone update a wave per SIMD)
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, dt);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32));
+  return __builtin_bit_cast(double, (unsigned long long)hi << 32 | lo);
+}
 
 // The update's streams that are used once (U^n and the accumulator read, the
 // stage state and the accumulator written) as nontemporal accesses: they pass
@@ -565,10 +628,14 @@ template <int RK, int STAGE, typename S>
 __global__ __launch_bounds__(256) void update_kernel(UpdateArgs<S> a) {
   static_assert((RK == 3 && STAGE >= 0 && STAGE < 3) || (RK == 4 && STAGE >= 0 && STAGE < 4), "stage of the scheme");
   const Grid& g = a.g;
-  const int i = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int j = blockIdx.y * 4 + (threadIdx.x >> 6);
-  const int k = blockIdx.z;
-  if (i >= g.nx || j >= g.ny) return;
+  double dt = 0.0;
+  if constexpr (STAGE == 0) {
+    if (a.keys) dt = stage0_dt(a);
+  }
+  const unsigned t = blockIdx.x * 256u + threadIdx.x;
+  if (t >= g.N) return;
+  int i, j, k;
+  thread_zone(t, a.inv_row, g.nx, a.inv_ny, g.ny, i, j, k);
   const int im = i == 0 ? g.nx - 1 : i - 1, ip = i + 1 == g.nx ? 0 : i + 1;
   const int jm = j == 0 ? g.ny - 1 : j - 1, jp = j + 1 == g.ny ? 0 : j + 1;
   const int km = k == 0 ? g.nz - 1 : k - 1, kp = k + 1 == g.nz ? 0 : k + 1;
@@ -636,7 +703,7 @@ __global__ __launch_bounds__(256) void update_kernel(UpdateArgs<S> a) {
     for (int v = 0; v < 8; ++v) a.rhs_out[v * N + c0] = kv[v];
     return;
   }
-  const double dt = *a.dt;
+  if (STAGE != 0 || !a.keys) dt = *a.dt;
 #pragma unroll
   for (int v = 0; v < 8; ++v) {
     const double un = double(nt_load(v < 5 ? a.Un + v * N + c0 : a.bn + (v - 5) * N + c0));
@@ -680,24 +747,37 @@ template <> struct Pair2<double> { using T = double2; };
 // in flight per instruction (with 4-byte values, one zone per thread keeps
 // half the bytes of the FP64 kernel, and the update is bound by the latency
 // of its many streams).  Needs nx even and arrays at even element offsets.
-// Blocks of PAIR_ROW_ZONES x PAIR_ROWS zones: long rows (a wave covers 128
-// contiguous zones of a row) keep the x-neighbour reads at the row ends few;
-// 256 x 2 measured 1.252 ms per FP64 update at 256^3 against 1.260 (128 x 4)
-// and 1.329 (64 x 8), and 0.632 ms against 0.643 and 0.700 for the FP32 state.
+// A wave covers 128 contiguous zones, which keeps the x-neighbour reads at its
+// ends few: at 256^3, 256 x 2-zone blocks measured 1.252 ms per FP64 update
+// against 1.260 (128 x 4) and 1.329 (64 x 8), and 0.632 ms against 0.643 and 0.700
+// for the FP32 state.
 // Each zone's arithmetic is update_kernel's, term by term in the same order
 // (the compiler may still fuse a different product into an FMA).
+// ROWS (nx a multiple of 256): blocks of two 256-zone rows of a plane.
 constexpr int PAIR_ROW_ZONES = 256;
 constexpr int PAIR_ROWS = 2 * 256 / PAIR_ROW_ZONES;   // 256 threads, two zones each
-template <int RK, int STAGE, typename S>
+template <int RK, int STAGE, typename S, bool ROWS>
 __global__ __launch_bounds__(256) void update_pair_kernel(UpdateArgs<S> a) {
   using V2 = typename Pair2<S>::T;
   static_assert((RK == 3 && STAGE >= 0 && STAGE < 3) || (RK == 4 && STAGE >= 0 && STAGE < 4), "stage of the scheme");
   const Grid& g = a.g;
-  const int i0 = blockIdx.x * PAIR_ROW_ZONES + 2 * (threadIdx.x % (PAIR_ROW_ZONES / 2));
-  const int j = blockIdx.y * PAIR_ROWS + threadIdx.x / (PAIR_ROW_ZONES / 2);
-  const int k = blockIdx.z;
-  if (i0 >= g.nx || j >= g.ny) return;
+  double dt = 0.0;
+  if constexpr (STAGE == 0 && !ROWS) {   // (a box of 256-zone rows has more keys)
+    if (a.keys) dt = stage0_dt(a);
+  }
   const int nx = g.nx;
+  int i0, j, k;
+  if constexpr (ROWS) {
+    i0 = blockIdx.x * PAIR_ROW_ZONES + 2 * (threadIdx.x % (PAIR_ROW_ZONES / 2));
+    j = blockIdx.y * PAIR_ROWS + threadIdx.x / (PAIR_ROW_ZONES / 2);
+    k = blockIdx.z;
+    if (j >= g.ny) return;
+  } else {
+    const unsigned t = blockIdx.x * 256u + threadIdx.x;
+    if (t >= g.N / 2) return;
+    thread_zone(t, a.inv_row, (unsigned)nx / 2, a.inv_ny, g.ny, i0, j, k);
+    i0 *= 2;
+  }
   const int jm = j == 0 ? g.ny - 1 : j - 1, jp = j + 1 == g.ny ? 0 : j + 1;
   const int km = k == 0 ? g.nz - 1 : k - 1, kp = k + 1 == g.nz ? 0 : k + 1;
   const int imm = i0 == 0 ? nx - 2 : i0 - 2;          // pair holding zone i0 - 1 (as .y)
@@ -810,7 +890,7 @@ __global__ __launch_bounds__(256) void update_pair_kernel(UpdateArgs<S> a) {
     }
     return;
   }
-  const double dt = *a.dt;
+  if (STAGE != 0 || !a.keys) dt = *a.dt;
 #pragma unroll
   for (int v = 0; v < 8; ++v) {
     const S* unp = v < 5 ? a.Un + v * N : a.bn + (v - 5) * N;
@@ -862,16 +942,25 @@ __global__ __launch_bounds__(256) void update_pair_kernel(UpdateArgs<S> a) {
 }
 
 // zone B = (-b_{i-2} + 9 b_{i-1} + 9 b_i - b_{i+1}) / 16 along each component's own axis
-// Blocks of BCELL_ROW_ZONES x BCELL_ROWS zones (256 threads): 64 x 4 measured
-// 0.191 ms per 256^3 FP64 pass against 0.192 (128 x 2) and 0.200 (256 x 1).
+// Blocks of 64 x 4 zones where nx is a multiple of 64 (256 threads; at 256^3 FP64
+// 0.191 ms per pass against 0.192 with 128 x 2 and 0.200 with 256 x 1), otherwise
+// threads numbered through the box, whose rows leave no lanes idle.
 constexpr int BCELL_ROW_ZONES = 64;
 constexpr int BCELL_ROWS = 256 / BCELL_ROW_ZONES;
+inline __host__ __device__ bool bcell_rows(int nx) { return nx % BCELL_ROW_ZONES == 0; }
 template <typename S>
-__global__ __launch_bounds__(256) void bcell_kernel(Grid g, const S* b, S* B) {
-  const int i = blockIdx.x * BCELL_ROW_ZONES + threadIdx.x % BCELL_ROW_ZONES;
-  const int j = blockIdx.y * BCELL_ROWS + threadIdx.x / BCELL_ROW_ZONES;
-  const int k = blockIdx.z;
-  if (i >= g.nx || j >= g.ny) return;
+__global__ __launch_bounds__(256) void bcell_kernel(Grid g, double inv_nx, double inv_ny, const S* b, S* B) {
+  int i, j, k;
+  if (bcell_rows(g.nx)) {
+    i = blockIdx.x * BCELL_ROW_ZONES + threadIdx.x % BCELL_ROW_ZONES;
+    j = blockIdx.y * BCELL_ROWS + threadIdx.x / BCELL_ROW_ZONES;
+    k = blockIdx.z;
+    if (j >= g.ny) return;
+  } else {
+    const unsigned t = blockIdx.x * 256u + threadIdx.x;
+    if (t >= g.N) return;
+    thread_zone(t, inv_nx, g.nx, inv_ny, g.ny, i, j, k);
+  }
   const size_t N = g.N, c0 = g.at(i, j, k);
   const S* bx = b;
   const S* by = b + N;
@@ -1030,10 +1119,7 @@ __global__ __launch_bounds__(RED_THREADS) void dt_final_kernel(int nblocks, doub
   if (threadIdx.x == 0) {
     double m[3];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const SpeedKey k = red[d][0];
-      m[d] = (k >> 63) ? __builtin_nan("") : __builtin_bit_cast(double, k);
-    }
+    for (int d = 0; d < 3; ++d) m[d] = speed_of(red[d][0]);
     const double s = (m[0] + m[1]) + m[2];
     *dt = cfl_h / s;
     smax[0] = m[0]; smax[1] = m[1]; smax[2] = m[2];

@@ -296,6 +296,8 @@ void prof_end(wm_patch* p, long r) {
   if (hipEventRecord(p->ev[2 * r + 1], p->stream) == hipSuccess) p->n_rec = (size_t)r + 1;
 }
 
+dim3 lin_grid(size_t n) { return dim3((unsigned)((n + 255) / 256)); }
+
 dim3 zone_grid(const Grid& g) { return dim3((g.nx + 63) / 64, (g.ny + 3) / 4, g.nz); }
 
 // Runs fn(S{}) with S the patch's storage type.
@@ -409,24 +411,34 @@ wm_status sweeps(wm_patch* p, const S* hydro, const S* bcell, SpeedKey* smax = n
   return WM_OK;
 }
 
+// Per axis, the number of per-wave signal speeds its sweep writes
+void sweep_keys(const wm_patch* p, unsigned n[3]) {
+  const SweepPlan& pl = p->sweep_all;
+  n[0] = 4 * pl.ax[1].blk0;
+  n[1] = 4 * pl.ax[2].blk0 - n[0];
+  n[2] = 4 * pl.nblk - n[0] - n[1];
+}
+
 int n_stages(const wm_patch* p) { return p->cfg.integrator == WM_RK4 ? 4 : 3; }
 
 // Launches the update of one stage: with nx even and every array aligned to
 // two elements, the two-zone kernel (vector loads), else one zone per thread.
-constexpr bool kUpdatePairs = true;
 template <int RK, int STAGE, typename S>
-void launch_update_kernel(wm_patch* p, const UpdateArgs<S>& a) {
-  if (kUpdatePairs) {
-    auto al = [](const void* q) { return q == nullptr || (reinterpret_cast<uintptr_t>(q) % (2 * sizeof(S))) == 0; };
-    const bool pair = p->g.nx % 2 == 0 && al(a.faces) && al(a.Un) && al(a.bn) && al(a.acc) && al(a.hyd_out) &&
-                      al(a.b_out);
-    if (pair) {
-      const dim3 grid((p->g.nx + PAIR_ROW_ZONES - 1) / PAIR_ROW_ZONES, (p->g.ny + PAIR_ROWS - 1) / PAIR_ROWS, p->g.nz);
-      hipLaunchKernelGGL((update_pair_kernel<RK, STAGE, S>), grid, dim3(256), 0, p->stream, a);
-      return;
-    }
+void launch_update_kernel(wm_patch* p, UpdateArgs<S> a) {
+  const Grid& g = p->g;
+  auto al = [](const void* q) { return q == nullptr || (reinterpret_cast<uintptr_t>(q) % (2 * sizeof(S))) == 0; };
+  const bool pair = g.nx % 2 == 0 && al(a.faces) && al(a.Un) && al(a.bn) && al(a.acc) && al(a.hyd_out) && al(a.b_out);
+  a.inv_ny = 1.0 / g.ny;
+  if (pair && g.nx % PAIR_ROW_ZONES == 0 && !a.keys) {
+    const dim3 grid(g.nx / PAIR_ROW_ZONES, (g.ny + PAIR_ROWS - 1) / PAIR_ROWS, g.nz);
+    hipLaunchKernelGGL((update_pair_kernel<RK, STAGE, S, true>), grid, dim3(256), 0, p->stream, a);
+  } else if (pair) {
+    a.inv_row = 2.0 / g.nx;
+    hipLaunchKernelGGL((update_pair_kernel<RK, STAGE, S, false>), lin_grid(g.N / 2), dim3(256), 0, p->stream, a);
+  } else {
+    a.inv_row = 1.0 / g.nx;
+    hipLaunchKernelGGL((update_kernel<RK, STAGE, S>), lin_grid(g.N), dim3(256), 0, p->stream, a);
   }
-  hipLaunchKernelGGL((update_kernel<RK, STAGE, S>), zone_grid(p->g), dim3(256), 0, p->stream, a);
 }
 
 template <typename S>
@@ -447,8 +459,10 @@ void launch_update_stage(wm_patch* p, const UpdateArgs<S>& a, bool rk4, int stag
   }
 }
 
+// keys: optional (stage 0), the per-wave signal speeds of the stage's sweeps, for
+// an update that forms the time step itself
 template <typename S>
-wm_status launch_update(wm_patch* p, int stage, double* rhs_out) {
+wm_status launch_update(wm_patch* p, int stage, double* rhs_out, const SpeedKey* keys = nullptr) {
   const size_t N = p->g.N;
   UpdateArgs<S> a;
   a.g = p->g;
@@ -460,6 +474,13 @@ wm_status launch_update(wm_patch* p, int stage, double* rhs_out) {
   a.rhs_out = rhs_out;
   a.dt = p->dt_dev();
   for (int d = 0; d < 3; ++d) a.wallF[d] = p->g.wall[d] ? p->wallF<S>(d) : nullptr;
+  a.keys = keys;
+  if (keys) {
+    sweep_keys(p, a.nkeys);
+    a.cfl_h = p->cfg.cfl * p->cfg.h;
+    a.dt_out = p->dt_dev();
+    a.smax_out = p->smax_dev();
+  }
   if (stage == n_stages(p) - 1) {
     a.hyd_out = p->hyd<S>();
     a.b_out = p->bf<S>();
@@ -477,8 +498,10 @@ wm_status launch_update(wm_patch* p, int stage, double* rhs_out) {
 template <typename S>
 wm_status launch_bcell(wm_patch* p, const S* b, S* B) {
   const long r = prof_begin(p, K_BCELL);
-  const dim3 grid((p->g.nx + BCELL_ROW_ZONES - 1) / BCELL_ROW_ZONES, (p->g.ny + BCELL_ROWS - 1) / BCELL_ROWS, p->g.nz);
-  hipLaunchKernelGGL(bcell_kernel<S>, grid, dim3(256), 0, p->stream, p->g, b, B);
+  const dim3 grid = bcell_rows(p->g.nx)
+                        ? dim3(p->g.nx / BCELL_ROW_ZONES, (p->g.ny + BCELL_ROWS - 1) / BCELL_ROWS, p->g.nz)
+                        : lin_grid(p->g.N);
+  hipLaunchKernelGGL(bcell_kernel<S>, grid, dim3(256), 0, p->stream, p->g, 1.0 / p->g.nx, 1.0 / p->g.ny, b, B);
   WM_LAUNCH_CHECK("bcell kernel");
   prof_end(p, r);
   return WM_OK;
@@ -494,8 +517,6 @@ wm_status check_bound(wm_patch* p) {
   if (!p->hydro || !p->bface || !p->bcell) return fail(WM_ERR_STATE, "state not bound (wm_bind_state)");
   return WM_OK;
 }
-
-dim3 lin_grid(size_t n) { return dim3((unsigned)((n + 255) / 256)); }
 
 template <int AXIS>
 wm_status launch_adj_sweep(wm_patch* p, const double* hydro, const double* bcell, const double* lam_k,
@@ -582,6 +603,7 @@ wm_status forward_stages(wm_patch* p, const S* Uh, const S* Ub, S* Bz, const dou
     a.acc = acc;
     a.rhs_out = nullptr;
     a.dt = dtp;
+    a.keys = nullptr;
     for (int d = 0; d < 3; ++d) a.wallF[d] = nullptr;   // the adjoint is for periodic boxes
     S* out = outs[st];
     a.hyd_out = out;
@@ -813,26 +835,30 @@ wm_status wm_compute_dt(wm_patch* p, double* dt_host) {
 namespace {
 
 // The fused time step: the sweeps of a step's first stage write per-wave
-// maxima of the eq. (cfl) signal speed (4 per block) into the accumulator
-// region (free until that stage's update writes it), and speed_blocks_kernel +
-// dt_final_kernel turn them into dt before the update.  Returns the number of
-// wave values, or 0 when they do not fit there, in which case the step runs the
-// stand-alone time-step pass first (very thin grids, e.g. 1 x 1 x n).
-size_t fused_dt_blocks(const wm_patch* p) {
-  const size_t nb = 4 * (size_t)p->sweep_all.nblk;
+// maxima of the eq. (cfl) signal speed (4 per block).  Up to DT_IN_UPDATE of them go
+// to the reduction scratch and the stage's update turns them into dt itself; more
+// go to the accumulator region (free until that update writes it), and
+// speed_blocks_kernel + dt_final_kernel turn them into dt before the update.  Where
+// they do not fit there either (very thin grids), the step runs the stand-alone
+// time-step pass first.
+enum class StepDt { given, in_update, blocks };
+StepDt fused_dt(const wm_patch* p) {
+  const size_t n = 4 * (size_t)p->sweep_all.nblk;
+  static_assert(DT_IN_UPDATE <= 23 * RED_BLOCKS, "the keys lie in the speed and diagnostics partials");
+  if (n <= DT_IN_UPDATE) return StepDt::in_update;
   const size_t acc_bytes = 8 * p->g.N * (p->f32 ? sizeof(float) : sizeof(double));
   // (at most 2^31 values: the kernels index them in 32 bits)
-  return nb * sizeof(SpeedKey) <= acc_bytes && nb <= (size_t(1) << 31) ? nb : 0;
+  return n * sizeof(SpeedKey) <= acc_bytes && n <= (size_t(1) << 31) ? StepDt::blocks : StepDt::given;
 }
 
 wm_status launch_fused_dt(wm_patch* p) {
-  const SweepPlan& pl = p->sweep_all;
-  const unsigned n0 = 4 * pl.ax[1].blk0, n1 = 4 * pl.ax[2].blk0 - n0, n2 = 4 * pl.nblk - n0 - n1;
-  const unsigned nmax = std::max(n0, std::max(n1, n2));
+  unsigned n[3];
+  sweep_keys(p, n);
+  const unsigned nmax = std::max(n[0], std::max(n[1], n[2]));
   const int nb = (int)std::min<unsigned>((nmax + RED_THREADS - 1) / RED_THREADS, (unsigned)RED_BLOCKS);
   const long r = prof_begin(p, K_DT);
   hipLaunchKernelGGL(speed_blocks_kernel, dim3(nb), dim3(RED_THREADS), 0, p->stream,
-                     reinterpret_cast<const SpeedKey*>(p->acc<char>()), n0, n1, n2, p->speed_part());
+                     reinterpret_cast<const SpeedKey*>(p->acc<char>()), n[0], n[1], n[2], p->speed_part());
   WM_LAUNCH_CHECK("speed blocks kernel");
   hipLaunchKernelGGL(dt_final_kernel, dim3(1), dim3(RED_THREADS), 0, p->stream, nb, p->cfg.cfl * p->cfg.h,
                      p->speed_part(), p->dt_dev(), p->smax_dev());
@@ -842,9 +868,9 @@ wm_status launch_fused_dt(wm_patch* p) {
   return WM_OK;
 }
 
-// One stage (after the caller's checks); fuse_dt (stage 0 only): dt from the
-// stage's own sweeps
-wm_status run_stage(wm_patch* p, int stage, bool fuse_dt) {
+// One stage (after the caller's checks); how (stage 0 only): dt given, or from
+// the stage's own sweeps
+wm_status run_stage(wm_patch* p, int stage, StepDt how) {
   const int ns = n_stages(p);
   const size_t N = p->g.N;
   wm_status s = with_storage(p, [&](auto tag) -> wm_status {
@@ -852,10 +878,12 @@ wm_status run_stage(wm_patch* p, int stage, bool fuse_dt) {
     const S* hyd_in = stage == 0 ? p->hyd<S>() : p->us<S>();
     const S* bcell_in = stage == 0 ? p->bc<S>() : p->us<S>() + 8 * N;
     wm_status st;
-    SpeedKey* smax = fuse_dt ? reinterpret_cast<SpeedKey*>(p->acc<char>()) : nullptr;
+    SpeedKey* keys = how == StepDt::in_update ? p->speed_part() : nullptr;
+    SpeedKey* smax = how == StepDt::blocks ? reinterpret_cast<SpeedKey*>(p->acc<char>()) : keys;
     if ((st = sweeps<S>(p, hyd_in, bcell_in, smax)) != WM_OK) return st;
-    if (fuse_dt && (st = launch_fused_dt(p)) != WM_OK) return st;
-    if ((st = launch_update<S>(p, stage, nullptr)) != WM_OK) return st;
+    if (how == StepDt::blocks && (st = launch_fused_dt(p)) != WM_OK) return st;
+    if ((st = launch_update<S>(p, stage, nullptr, keys)) != WM_OK) return st;
+    if (keys) p->dt_valid = true;
     S* hyd_out = stage == ns - 1 ? p->hyd<S>() : p->us<S>();
     S* b_out = stage == ns - 1 ? p->bf<S>() : p->us<S>() + 5 * N;
     S* bc_out = stage == ns - 1 ? p->bc<S>() : p->us<S>() + 8 * N;
@@ -888,17 +916,17 @@ wm_status wm_rk_stage(wm_patch* p, int stage, const double* dt_host) {
   } else if (!p->dt_valid) {
     return fail(WM_ERR_STATE, "no dt: call wm_compute_dt or pass dt");
   }
-  return run_stage(p, stage, false);
+  return run_stage(p, stage, StepDt::given);
 }
 
 wm_status wm_step(wm_patch* p, double* dt_used) {
   wm_status s = check_bound(p);
   if (s != WM_OK) return s;
   p->stage_done = -1;
-  const bool fuse = fused_dt_blocks(p) > 0;
-  if (!fuse && (s = wm_compute_dt(p, nullptr)) != WM_OK) return s;
+  const StepDt how = fused_dt(p);
+  if (how == StepDt::given && (s = wm_compute_dt(p, nullptr)) != WM_OK) return s;
   for (int st = 0; st < n_stages(p); ++st)
-    if ((s = run_stage(p, st, fuse && st == 0)) != WM_OK) return s;
+    if ((s = run_stage(p, st, st == 0 ? how : StepDt::given)) != WM_OK) return s;
   if (dt_used) {
     if ((s = hip_check(hipMemcpyAsync(dt_used, p->dt_dev(), sizeof(double), hipMemcpyDeviceToHost, p->stream),
                        "dt copy")) != WM_OK)
