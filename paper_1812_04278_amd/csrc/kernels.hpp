@@ -164,6 +164,7 @@ constexpr int SW_DIV_SHIFT = 20;
 struct SweepAxis {
   int ta, tb, ntile;
   unsigned div_ta, div_na, div_tb;   // of ta, ta + 5 and tb
+  double inv_ntile;                  // 1 / ntile
   int ncol;                          // columns across the axis
   unsigned blk0;                     // first block of the axis
 };
@@ -247,33 +248,45 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
   const int ncell = NA * TB;
   const int nA = AXIS == 0 ? g.nx : (AXIS == 1 ? g.ny : g.nz);
   constexpr int CN = AXIS, CT1 = (AXIS + 1) % 3, CT2 = (AXIS + 2) % 3;
-  auto cidx = [&](int aa, int bb) { return AXIS == 0 ? bb * NA + aa : aa * TB + bb; };
-  auto iidx = [&](int ia, int bb) { return AXIS == 0 ? bb * NI + ia : ia * TB + bb; };
+  // Products of factors below 2^24 take the full-rate 24-bit multiply (the 32-bit
+  // one has a quarter of the rate, and the tile's numbering needs some twenty).
+  auto mul = [](int x, int y) { return (int)__umul24((unsigned)x, (unsigned)y); };
+  auto cidx = [&](int aa, int bb) { return AXIS == 0 ? mul(bb, NA) + aa : mul(aa, TB) + bb; };
+  auto iidx = [&](int ia, int bb) { return AXIS == 0 ? mul(bb, NI) + ia : mul(ia, TB) + bb; };
   // quotient of a lane or zone number by ta, ta + 5 or tb
-  auto quot = [](int n, unsigned div) { return (int)(((unsigned)n * div) >> SW_DIV_SHIFT); };
+  auto quot = [](int n, unsigned div) { return (int)(__umul24((unsigned)n, div) >> SW_DIV_SHIFT); };
   auto split_cell = [&](int cell, int& aa, int& bb) {
-    if (AXIS == 0) { bb = quot(cell, ax.div_na); aa = cell - bb * NA; }
-    else           { aa = quot(cell, ax.div_tb); bb = cell - aa * TB; }
+    if (AXIS == 0) { bb = quot(cell, ax.div_na); aa = cell - mul(bb, NA); }
+    else           { aa = quot(cell, ax.div_tb); bb = cell - mul(aa, TB); }
   };
   auto split_face = [&](int t, int& fa, int& fb) {
-    if (AXIS == 0) { fb = quot(t, ax.div_ta); fa = t - fb * TA; }
-    else           { fa = quot(t, ax.div_tb); fb = t - fa * TB; }
+    if (AXIS == 0) { fb = quot(t, ax.div_ta); fa = t - mul(fb, TA); }
+    else           { fa = quot(t, ax.div_tb); fb = t - mul(fa, TB); }
   };
   // faces 0 .. nA-1 (i+1/2), and with walls also the lower wall face -1/2
   const int wl = g.wall[AXIS];
-  const unsigned grp = blk / (unsigned)ax.ntile;
+  const unsigned grp = (unsigned)__builtin_amdgcn_readfirstlane((int)quot_by(blk, ax.inv_ntile));
   const int a0 = (int)(blk - grp * (unsigned)ax.ntile) * TA - wl;
   const int b0 = (int)grp * TB;
   // element index of zone ia of column q, 32 bits (N < 2^31): base + ia * stride
-  const unsigned stride = AXIS == 0 ? 1u : (AXIS == 1 ? (unsigned)g.nx : (unsigned)g.nx * (unsigned)g.ny);
-  auto column = [&](int q) -> unsigned {
-    if (AXIS == 0) return (unsigned)q * (unsigned)g.nx;
-    if (AXIS == 2) return (unsigned)q;
+  // (planes of 2^24 zones and more take the 32-bit multiply)
+  const unsigned plane = (unsigned)g.nx * (unsigned)g.ny;
+  const bool small = plane < (1u << 24) && (unsigned)ax.ncol < (1u << 24);
+  auto mul_zone = [&](unsigned x, unsigned y) -> unsigned { return small ? __umul24(x, y) : x * y; };
+  auto zone_at = [&](int q, int ia) -> unsigned {
+    if (AXIS == 0) return mul_zone((unsigned)q, (unsigned)g.nx) + (unsigned)ia;
+    if (AXIS == 2) return (unsigned)q + mul_zone((unsigned)ia, plane);
     const unsigned z = quot_by((unsigned)q, a.inv_nx);
-    return (unsigned)q + z * ((unsigned)g.nx * (unsigned)(g.ny - 1));
+    return (unsigned)q + mul_zone(z, plane - (unsigned)g.nx) + (unsigned)mul(ia, g.nx);
   };
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid) / 64;   // uniform: held in a scalar register
+  // the thread's number, formed anew for each phase from the wave's (uniform, held
+  // in a scalar register) and the lane's: holding it costs a spilled register
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x) / 64;
+  auto thread = [&]() -> int {
+    int lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    return wave * 64 + lane;
+  };
   // every array of the state and the fluxes within 4 GiB: buffer accesses with 32-bit offsets
   const size_t abytes = g.N * sizeof(S);
   const bool off32 = !g.wide && abytes < (size_t(1) << 32);
@@ -289,6 +302,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
   // so the block waits for one round trip to memory, not two.  Lanes past the
   // last zone load it again and discard it.
   constexpr int NR = (NC + SW_THREADS - 1) / SW_THREADS;
+  const int tid = thread();
   double raw[NR][8];
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
@@ -296,7 +310,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
     split_cell(min(tid + r * SW_THREADS, ncell - 1), aa, bb);
     double flip;
     const int ia = sweep_zone(a0 - SW_HL + aa, nA, wl, flip);
-    const unsigned gz = column(min(b0 + bb, ax.ncol - 1)) + (unsigned)ia * stride;
+    const unsigned gz = zone_at(min(b0 + bb, ax.ncol - 1), ia);
     if (off32) {
       const unsigned off = gz * (unsigned)sizeof(S);
 #pragma unroll
@@ -347,36 +361,50 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
   stamp[2] = clock64();
 #endif
 
-  // ---- (2) per face: central flux, face state, LF speeds, own interface
-  // differences.  Lanes past the tile's faces repeat face 0 (equal values) and
-  // store nothing.
+  // ---- (2) per face: the difference of its own interface (zones L and R), from
+  // the same reads its face state and the mean flux of the central term
+  //   F_c = (F_L + F_R)/2 + (Delta F_{i-1/2} - Delta F_{i+3/2})/12;
+  // in FP64 phase 3, which reads those differences anyway, adds the second part
+  // (the FP32 work type holds rounded ones, so here).  The four interfaces of a
+  // column beyond its faces' own go to the lanes fa < 4.  LDS reads bound this
+  // kernel beside the VALU: at 256^3 FP64 a SIMD issues VALU work 80% of the time
+  // (1,510 quad cycles of three waves' 5,650 each), and the reads of ~340 doubles
+  // per face, before this form, took ~70% of the LDS bandwidth; 55 fewer of them
+  // and the shorter arithmetic below brought a 256^3 step from 13.9 to 13.1 ms,
+  // WENO-Z RK4 at 128^3 from 2.43 to 2.30 and the mixed form from 12.1 to 11.6.  Lanes past the tile's faces repeat face 0
+  // (equal values) and store nothing.
   int fa, fb;
-  split_face(tid < TA * TB ? tid : 0, fa, fb);
+  {
+    const int t = thread();
+    split_face(t < TA * TB ? t : 0, fa, fb);
+  }
   const int cL = cidx(fa + 2, fb), cR = cidx(fa + 3, fb);
-  double Fc[7];
+  auto PL = [&](int v) { return double(Pz[v * NC + cL]); };
+  auto PR = [&](int v) { return double(Pz[v * NC + cR]); };
+  double Fc[7], d0[SW_NQ], d1[SW_NQ];
 #pragma unroll
   for (int j = 0; j < 7; ++j) {
     const double* F = Q + (SW_NQ / 2 + j) * NC;
-    Fc[j] = (-F[cidx(fa + 1, fb)] + 7.0 * F[cL] + 7.0 * F[cR] - F[cidx(fa + 4, fb)]) * (1.0 / 12.0);
+    const double FL = F[cL], FR = F[cR];
+    d0[7 + j] = FR - FL;
+    if constexpr (sizeof(TW) == 8) Fc[j] = 0.5 * (FL + FR);
+    else Fc[j] = (7.0 * (FL + FR) - (F[cidx(fa + 1, fb)] + F[cidx(fa + 4, fb)])) * (1.0 / 12.0);
   }
-  auto PL = [&](int v) { return double(Pz[v * NC + cL]); };
-  auto PR = [&](int v) { return double(Pz[v * NC + cR]); };
-  auto QL = [&](int v) { return Q[v * NC + cL]; };
-  auto QR = [&](int v) { return Q[v * NC + cR]; };
   // face state: mean of the primitive states of zones i and i+1; rho and B_t, from
   // q, here, the others in phase 3
-  const double f_rho = 0.5 * (QL(Z_RHO) + QR(Z_RHO)), f_bt1 = 0.5 * (QL(Z_BT1) + QR(Z_BT1)),
-               f_bt2 = 0.5 * (QL(Z_BT2) + QR(Z_BT2));
-  double d0[SW_NQ], d1[SW_NQ];
-  {
-    const int c0 = cidx(fa, fb), c1 = cidx(fa + 1, fb);
+  double f_q[7];
 #pragma unroll
-    for (int v = 0; v < SW_NQ; ++v) d0[v] = Q[v * NC + c1] - Q[v * NC + c0];
-    if (fa < 4) {
-      const int c2 = cidx(TA + fa, fb), c3 = cidx(TA + fa + 1, fb);
+  for (int v = 0; v < 7; ++v) {
+    const double qL = Q[v * NC + cL], qR = Q[v * NC + cR];
+    d0[v] = qR - qL;
+    f_q[v] = 0.5 * (qL + qR);
+  }
+  const double f_rho = f_q[Z_RHO], f_bt1 = f_q[Z_BT1], f_bt2 = f_q[Z_BT2];
+  const int ie = fa < 2 ? fa : TA + fa;
+  if (fa < 4) {
+    const int c2 = cidx(ie, fb), c3 = cidx(ie + 1, fb);
 #pragma unroll
-      for (int v = 0; v < SW_NQ; ++v) d1[v] = Q[v * NC + c3] - Q[v * NC + c2];
-    }
+    for (int v = 0; v < SW_NQ; ++v) d1[v] = Q[v * NC + c3] - Q[v * NC + c2];
   }
 #ifdef WM_SWEEP_CLOCK
   stamp[3] = clock64();
@@ -385,14 +413,14 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
   // differences stored as (Delta F, Delta q): j = 0..6 flux, 7..13 state
 #pragma unroll
   for (int v = 0; v < 7; ++v) {
-    Dl[v * ND + iidx(fa, fb)] = TW(d0[7 + v]);
-    Dl[(7 + v) * ND + iidx(fa, fb)] = TW(d0[v]);
+    Dl[v * ND + iidx(fa + 2, fb)] = TW(d0[7 + v]);
+    Dl[(7 + v) * ND + iidx(fa + 2, fb)] = TW(d0[v]);
   }
   if (fa < 4) {
 #pragma unroll
     for (int v = 0; v < 7; ++v) {
-      Dl[v * ND + iidx(TA + fa, fb)] = TW(d1[7 + v]);
-      Dl[(7 + v) * ND + iidx(TA + fa, fb)] = TW(d1[v]);
+      Dl[v * ND + iidx(ie, fb)] = TW(d1[7 + v]);
+      Dl[(7 + v) * ND + iidx(ie, fb)] = TW(d1[v]);
     }
   }
   __syncthreads();
@@ -401,7 +429,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
 #endif
 
   // ---- (3) characteristic WENO flux of this face
-  auto dl = [&](int j, int k) -> TW { return Dl[j * ND + iidx(fa + k, fb)]; };
+  const TW* dl0 = Dl + iidx(fa, fb);
+  const int dstep = AXIS == 0 ? 1 : TB;      // from one interface of a column to the next
+  auto row = [&](int k) -> const TW* { return dl0 + k * dstep; };
   // Lax-Friedrichs speed of field m (0-based), read when its pair needs it:
   // max(|v_L + sg c_L|, |v_R + sg c_R|), c = c_f (m = 0, 6), c_A (1, 5), c_s (2, 4), 0 (3)
   auto alf = [&](int m) -> TW {
@@ -418,7 +448,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
   double Ff[7];
 #pragma unroll
   for (int j = 0; j < 7; ++j) Ff[j] = Fc[j];
-  face_corr<WENO_Z, TW>(e, alf, dl, a.ph, Ff);
+  face_corr<WENO_Z, ND, TW>(e, alf, row, a.ph, Ff);
   // CT transport-flux correction: face mean of B_n v_t (eq. fct1-fct6)
   const double tc1 = 0.5 * (PL(FP_BN) * PL(FP_VT1) + PR(FP_BN) * PR(FP_VT1));
   const double tc2 = 0.5 * (PL(FP_BN) * PL(FP_VT2) + PR(FP_BN) * PR(FP_VT2));
@@ -432,11 +462,9 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
   // guarded block defeats register allocation (hundreds of spills)
 #pragma unroll
   for (int j = 0; j < 7; ++j) asm volatile("" : "+v"(Ff[j]));
-  // FP64: the face's coordinates again, from the wave index and the lane id,
-  // for the stores: holding them through phase 3 cost a spilled register (the
-  // FP32 work type has registers to spare and measured 0.7% slower with this)
-  const int t = sizeof(TW) == 8 ? wave * 64 + (int)__lane_id() : tid;
-  if constexpr (sizeof(TW) == 8) split_face(t, fa, fb);
+  // the face's coordinates again, for the stores
+  const int t = thread();
+  split_face(t, fa, fb);
   const bool inside = t < TA * TB && b0 + fb < ax.ncol;
   if (a0 + fa < 0 && inside) {                // the lower wall face (-1/2): hydro fluxes only
     double fm[3];
@@ -449,7 +477,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
     wf[3 * P + wi] = S(fm[2]);
     wf[4 * P + wi] = S(Ff[6]);
   } else if (a0 + fa < nA && inside) {
-  const unsigned gz = column(b0 + fb) + (unsigned)(a0 + fa) * stride;
+  const unsigned gz = zone_at(b0 + fb, a0 + fa);
   const size_t gi = gz;
   double fm[3];
   fm[CN] = Ff[1]; fm[CT1] = Ff[2]; fm[CT2] = Ff[3];
@@ -483,8 +511,8 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
 #ifdef WM_SWEEP_CLOCK
   stamp[6] = clock64();
   stamp[7] = __smid();
-  if (a.clk[AXIS] && (tid & 63) == 0) {
-    unsigned long long* o = a.clk[AXIS] + ((size_t)blk * (SW_THREADS / 64) + tid / 64) * 8;
+  if (a.clk[AXIS] && (t & 63) == 0) {
+    unsigned long long* o = a.clk[AXIS] + ((size_t)blk * (SW_THREADS / 64) + t / 64) * 8;
 #pragma unroll
     for (int q = 0; q < 8; ++q) o[q] = stamp[q];
   }

@@ -41,15 +41,14 @@ __host__ __device__ __forceinline__ void sched_fence() {
 #endif
 }
 
-// Reciprocal: the hardware estimate (relative error up to 4.6e-8 on MI355X,
-// measured over 2^22 arguments) refined by two Newton steps, exact to rounding.
+// Reciprocal: the hardware estimate r (relative error up to 4.6e-8 on MI355X,
+// measured over 2^22 arguments) times 1 + e + e^2, e = 1 - x r: exact to rounding
+// (the next term is e^3 < 1e-21), with one operation less than two Newton steps.
 __host__ __device__ __forceinline__ double rcp_w(double x) {
 #ifdef __HIP_DEVICE_COMPILE__
-  double r = __builtin_amdgcn_rcp(x);
-  double e = fma(-x, r, 1.0);
-  r = fma(e, r, r);
-  e = fma(-x, r, 1.0);
-  return fma(e, r, r);
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 #else
   return 1.0 / x;
 #endif
@@ -85,32 +84,32 @@ __host__ __device__ __forceinline__ double rcp_1(double x) {
 }
 __host__ __device__ __forceinline__ float rcp_1(float x) { return rcp_w(x); }
 
-// 1/sqrt(x) for x > 0 from the hardware estimate (relative error up to 5.2e-8,
-// measured) and two Newton steps (~1 ulp); sqrt(x) for x >= 0 from one Newton
-// step on 1/sqrt (up to 4.3e-15) and one on the square root itself, which
-// brings it to ~1 ulp (sqrt(0) = 0).
+// 1/sqrt(x) for x > 0 from the hardware estimate y (relative error up to 5.2e-8,
+// measured) times 1 + e/2 + 3 e^2/8, e = 1 - x y^2: the next term is 5 e^3/16 < 1e-21,
+// so ~1 ulp, with three operations less than two Newton steps.  sqrt(x) for
+// x >= 0 the same way from x y (sqrt(0) = 0; a negative x gives a negative value
+// or NaN): at most 0.75 ulp.
 __host__ __device__ __forceinline__ double rsq_nr(double x) {
 #ifdef __HIP_DEVICE_COMPILE__
-  double y = __builtin_amdgcn_rsq(x);
-  double e = fma(-x * y, y, 1.0);
-  y = fma(0.5 * y, e, y);
-  e = fma(-x * y, y, 1.0);
-  return fma(0.5 * y, e, y);
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(0.375, e, 0.5), y);
 #else
   return 1.0 / sqrt(x);
 #endif
 }
 __host__ __device__ __forceinline__ double sqrt_nr(double x) {
 #ifdef __HIP_DEVICE_COMPILE__
-  const double xc = fmax(x, 1e-300);
-  const double y0 = __builtin_amdgcn_rsq(xc);
-  const double y = fma(0.5 * y0, fma(-xc * y0, y0, 1.0), y0);
+  const double y = __builtin_amdgcn_rsq(fmax(x, 1e-300));
   const double r = x * y;
-  return fma(0.5 * y, fma(-r, r, x), r);
+  const double e = fma(-r, y, 1.0);
+  return fma(r * e, fma(0.375, e, 0.5), r);
 #else
   return sqrt(x);
 #endif
 }
+// 1/sqrt(x) for x > 0 that stays finite at x <= 0, where x times it is 0 or negative
+__host__ __device__ __forceinline__ double rsq_pos(double x) { return rsq_nr(fmax(x, 1e-300)); }
 
 // Zone prologue of a sweep (step 2 of the 3D step list): primitives (eq. P),
 // the flux along n (eq. fluxes, total pressure P + |B|^2/2), and the fast,
@@ -152,8 +151,9 @@ __host__ __device__ __forceinline__ void zone_prologue(double rho, double mn, do
   const double dab = fma(-B2, irho, a2), apb = fma(B2, irho, a2);   // a^2 -+ b^2
   const double D = sqrt_nr(fma(dab, dab, (4.0 * a2) * (Bperp2 * irho)));
   const double cf2 = 0.5 * (apb + D);
-  const double cs2 = cf2 > 0.0 ? (a2 * bn2) * rcp_w(cf2) : 0.0;
-  out[Z_CF] = sqrt_nr(cf2);
+  const double icf = rsq_pos(cf2);                                  // 1/c_fast
+  const double cs2 = cf2 > 0.0 ? (a2 * bn2) * (icf * icf) : 0.0;
+  out[Z_CF] = cf2 * icf;
   out[Z_CA] = sqrt_nr(bn2);
   out[Z_CS] = sqrt_nr(cs2);
 }
@@ -162,12 +162,20 @@ __host__ __device__ __forceinline__ void zone_prologue(double rho, double mn, do
 // Jiang-Shu weights alpha_k = d_k / s_k^2 give
 //   omega_0 = s1^2 s2^2 / Q,  omega_2 = 3 s0^2 s1^2 / Q,
 //   Q = s1^2 s2^2 + 6 s0^2 s2^2 + 3 s0^2 s1^2,
-// one reciprocal instead of four divisions.  WENO-Z: alpha_k = d_k (1 + u_k) with
+// one reciprocal instead of four divisions.  With p_ij = s_i^2 s_j^2 and
+// m = p12 + 6 p02 the interpolant is
+//   phi_N = [4 p12 X + (3 p01 - m) Y] / (12 Q),  Q = 3 p01 + m.
+// The 1/12 is left to the caller, who scales the arguments by it (phi_N is
+// homogeneous of degree 1 in them when eps scales with their square): phiN of
+// arguments scaled by WenoScale is phi_N.  WENO-Z: alpha_k = d_k (1 + u_k) with
 // u_k = (tau_5/(eps_Z + IS_k))^2 (the dimensionless ratio squared), or, with `lit`,
 // u_k = tau_5/(eps_Z + IS_k)^2 as Sect. 2.2 prints it.  Always evaluated in FP64:
-// eps_Z (1e-40 in the paper) lies below the FP32 range.
+// eps_Z (1e-40 in the paper) lies below the FP32 range; its arguments are not
+// scaled (the printed form is not homogeneous).
+template <bool WENO_Z> constexpr double WenoScale = WENO_Z ? 1.0 : 1.0 / 12.0;
+
 template <bool WENO_Z, typename T>
-__host__ __device__ __forceinline__ T phiN(T a, T b, T c, T d, T eps, double eps_Z, bool lit) {
+__host__ __device__ __forceinline__ T phiN(T a, T b, T c, T d, T e3, double e3_Z, bool lit) {
   const T t0 = a - b, t1 = a - T(3) * b;
   const T t2 = b - c, t3 = b + c;
   const T t4 = c - d, t5 = T(3) * c - d;
@@ -175,9 +183,7 @@ __host__ __device__ __forceinline__ T phiN(T a, T b, T c, T d, T eps, double eps
   if (!WENO_Z) {
     (void)lit;
     // s_k/3 = eps/3 + IS_k/3: a common factor of the three s_k cancels in the
-    // weights.  phi = [p12 X / 3 + (p01/4 - p12/12 - p02/2) Y] / Q with
-    // p_ij = s_i^2 s_j^2 and Q = p12 + 6 p02 + 3 p01.
-    const T e3 = eps * T(1.0 / 3.0);
+    // weights (e3 = eps/3 at the scale of the arguments)
     T s0 = fma(T(13.0 / 3.0) * t0, t0, fma(t1, t1, e3));
     T s1 = fma(T(13.0 / 3.0) * t2, t2, fma(t3, t3, e3));
     T s2 = fma(T(13.0 / 3.0) * t4, t4, fma(t5, t5, e3));
@@ -188,23 +194,25 @@ __host__ __device__ __forceinline__ T phiN(T a, T b, T c, T d, T eps, double eps
       s0 *= r; s1 *= r; s2 *= r;
     }
     const T p12 = s1 * s2, p02 = s0 * s2, p01 = s0 * s1;
-    const T rq = rcp_1(fma(T(3), p01, fma(T(6), p02, p12)));
-    const T cY = fma(T(0.25), p01, fma(T(-1.0 / 12.0), p12, T(-0.5) * p02));
-    return rq * fma(cY, Y, (p12 * T(1.0 / 3.0)) * X);
+    const T m = fma(T(6), p02, p12);
+    const T rq = rcp_1(fma(T(3), p01, m));
+    return rq * fma(T(4), p12 * X, fma(T(3), p01, -m) * Y);
   } else {
     if constexpr (sizeof(T) == 4)
-      return T(phiN<true, double>(double(a), double(b), double(c), double(d), double(eps), eps_Z, lit));
-    const T IS0 = T(13) * t0 * t0 + T(3) * t1 * t1;
-    const T IS1 = T(13) * t2 * t2 + T(3) * t3 * t3;
-    const T IS2 = T(13) * t4 * t4 + T(3) * t5 * t5;
+      return T(phiN<true, double>(double(a), double(b), double(c), double(d), double(e3), e3_Z, lit));
+    // IS_k/3, and e3_Z = eps_Z/3 (the ratios u_k are those of the IS_k themselves)
+    const T IS0 = fma(T(13.0 / 3.0) * t0, t0, t1 * t1);
+    const T IS1 = fma(T(13.0 / 3.0) * t2, t2, t3 * t3);
+    const T IS2 = fma(T(13.0 / 3.0) * t4, t4, t5 * t5);
     const T tau5 = fabs(IS0 - IS2);
-    // alpha_k P^2 with P = s0 s1 s2, s_k = eps_Z + IS_k: d_k (P^2 + t m_k^2), m_k = P / s_k,
-    // t = tau_5^2 (or tau_5 as printed); the common factor P^2 cancels in the
-    // weights, so one reciprocal serves.  eps_Z >= 1e-50 keeps P^2 >= eps_Z^6 normal.
-    const T s0 = eps_Z + IS0, s1 = eps_Z + IS1, s2 = eps_Z + IS2;
+    // alpha_k P^2 with P = s0 s1 s2, s_k = (eps_Z + IS_k)/3: d_k (P^2 + t m_k^2), m_k = P / s_k,
+    // t = tau_5^2 (or tau_5 as printed, a third of it at this scale); the common
+    // factor P^2 cancels in the weights, so one reciprocal serves.  eps_Z >= 1e-50
+    // keeps P^2 >= (eps_Z/3)^6 normal.
+    const T s0 = e3_Z + IS0, s1 = e3_Z + IS1, s2 = e3_Z + IS2;
     const T m0 = s1 * s2, m1 = s0 * s2, m2 = s0 * s1;
     const T P = s0 * m0, P2 = P * P;
-    const T t = lit ? tau5 : tau5 * tau5;
+    const T t = lit ? tau5 * T(1.0 / 3.0) : tau5 * tau5;
     const T al0 = fma(t * m0, m0, P2), al1 = T(6) * fma(t * m1, m1, P2), al2 = T(3) * fma(t * m2, m2, P2);
     const T inv = rcp_1(al0 + al1 + al2);
     return inv * (al0 * X * T(1.0 / 3.0) + (al2 - T(0.5) * (al0 + al1 + al2)) * Y * T(1.0 / 6.0));
@@ -212,10 +220,11 @@ __host__ __device__ __forceinline__ T phiN(T a, T b, T c, T d, T eps, double eps
 }
 
 // phi^- - phi^+ of eq. (FWENO) from the split values of one characteristic
-// field: v[0..3] = Delta F^+ at i-3/2 .. i+3/2, v[4..7] = Delta F^- at i-1/2 .. i+5/2.
+// field: v[0..3] = Delta F^+ at i-3/2 .. i+3/2, v[4..7] = Delta F^- at i-1/2 .. i+5/2
+// (times WenoScale).
 template <bool WENO_Z, typename T>
-__host__ __device__ __forceinline__ T weno_split(const T v[8], T eps, double eps_Z, bool lit) {
-  return phiN<WENO_Z>(v[7], v[6], v[5], v[4], eps, eps_Z, lit) - phiN<WENO_Z>(v[0], v[1], v[2], v[3], eps, eps_Z, lit);
+__host__ __device__ __forceinline__ T weno_split(const T v[8], T e3, double e3_Z, bool lit) {
+  return phiN<WENO_Z>(v[7], v[6], v[5], v[4], e3, e3_Z, lit) - phiN<WENO_Z>(v[0], v[1], v[2], v[3], e3, e3_Z, lit);
 }
 
 // Eigen-system scalars of Appendix A at one face (always FP64: the
@@ -251,17 +260,21 @@ __host__ __device__ __forceinline__ void face_eig(double rho, double vn, double 
   e.sr = rho * e.isr;
   const double irho = e.isr * e.isr;
   e.a2 = gamma * P * irho;
-  e.cs = sqrt_nr(e.a2);
-  const double ia2 = rcp_w(e.a2);
+  // one reciprocal square root each for (c_s, 1/a^2) and (c_fast, 1/c_fast);
+  // c_slow = a |b_n| / c_fast
+  const double ics = rsq_nr(e.a2);
+  e.cs = e.a2 * ics;
+  const double ia2 = ics * ics;
   const double Bperp2 = Bt1 * Bt1 + Bt2 * Bt2;
   const double b2 = (Bn * Bn + Bperp2) * irho;
   const double dab = e.a2 - b2;
   const double p4 = 4.0 * e.a2 * (Bperp2 * irho);
   const double D = sqrt_nr(dab * dab + p4);
   e.cf2 = 0.5 * (e.a2 + b2 + D);
-  e.cf = sqrt_nr(e.cf2);
-  e.csl2 = e.cf2 > 0.0 ? e.a2 * (Bn * Bn * irho) * rcp_w(e.cf2) : 0.0;
-  e.csl = sqrt_nr(e.csl2);
+  const double icf = rsq_pos(e.cf2);
+  e.cf = e.cf2 * icf;
+  e.csl = e.cs * (fabs(Bn) * e.isr) * icf;
+  e.csl2 = e.csl * e.csl;
   if (Bperp2 > ph.eps_B) {
     const double ib = rsq_nr(Bperp2);
     e.by = Bt1 * ib;
@@ -298,38 +311,41 @@ __host__ __device__ __forceinline__ void face_eig(double rho, double vn, double 
 // (R L = I), eq. (FWENO).  L and R follow Appendix A: m = 1, 2, 3 take the
 // upper signs and 7, 6, 5 the lower; m = 2, 6 are the Alfven waves and m = 3, 5
 // the slow waves.  `al(m)` gives the Lax-Friedrichs speed of field m (0-based),
-// `dl(j, k)` reads interface difference j of interface k.  Projections, split
+// `row(k)` points at the differences of interface k, PITCH values apart (0..6
+// Delta F, 7..13 Delta q).  Projections, split
 // and weights run in T; the eigen scalars and the back-projection in FP64.
-// corr is added to (the caller passes the central term F_c in it).
-template <bool WENO_Z, typename T, class AL, class DL>
-__host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, DL dl, const Phys& ph,
+// corr is added to: the caller passes the central term F_c in it, in FP64 without
+// its part (Delta F_{i-1/2} - Delta F_{i+3/2})/12, added here.
+template <bool WENO_Z, int PITCH, typename T, class AL, class ROW>
+__host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, ROW row, const Phys& ph,
                                                    double corr[7]) {
-  const T eps = T(ph.eps);
-  const double epsZ = ph.eps_Z;
+  constexpr double SC = WenoScale<WENO_Z>;   // carried by the left rows
+  const T e3 = T(ph.eps * (SC * SC / 3.0));
+  const double e3Z = ph.eps_Z * (1.0 / 3.0);
   const bool lit = ph.weno_z == 2;
-  const double gm1 = -e.omg;
   const double sra = e.sr * e.cs;
+  const double qa2 = e.qa2 * SC;
+  // Gamma_f, Gamma_s, Gamma_a and the squares of the speeds are formed in the pair
+  // that uses them, not held from face_eig: the fast pair's peak decides the
+  // registers
+  const double hv2 = 0.5 * e.v2;
   T vu[8], vl[8];
   // The fast and slow left rows share W = (g1 v2, omg vn, omg vt1, omg vt2,
-  // omg Bt1, omg Bt2, gm1): fast S = qa2 (af W + sra as beta), slow S = qa2 (as W
-  // - sra af beta) with beta = (0, 0, 0, 0, by, bz, 0), and the entropy row is
-  // e0/2 - 2 qa2 W (ht = 2 qa2 (gamma - 1)).  The projections W.dF, W.dq of the
-  // five interfaces are formed once, in the fast pair, and reused.
-  // W.d = g1 v2 d0 + omg (vn d1 + vt1 d2 + vt2 d3 + Bt1 d4 + Bt2 d5) + gm1 d6, with the
-  // uniform factors applied after the per-lane sum (fewer live registers than W itself)
-  const T w0 = T(e.g1 * e.v2), wv[5] = {T(e.vn), T(e.vt1), T(e.vt2), T(e.Bt1), T(e.Bt2)};
-  const T omgT = T(e.omg), gm1T = T(gm1);
+  // omg Bt1, omg Bt2, gm1) = omg (-v2/2, vn, vt1, vt2, Bt1, Bt2, -1): fast S = qa2 (af W +
+  // sra as beta), slow S = qa2 (as W - sra af beta) with beta = (0, 0, 0, 0, by, bz, 0),
+  // and the entropy row is e0/2 - 2 qa2 W.  The projections of the five
+  // interfaces on W/omg are formed once, in the fast pair, and reused.
+  const T w0 = T(-hv2), wv[5] = {T(e.vn), T(e.vt1), T(e.vt2), T(e.Bt1), T(e.Bt2)};
   auto wdot = [&](const T* d) {
-    T in = wv[0] * d[1];
+    T in = fma(w0, d[0], -d[6]);
 #pragma unroll
-    for (int j = 1; j < 5; ++j) in += wv[j] * d[1 + j];
-    return omgT * in + (w0 * d[0] + gm1T * d[6]);
+    for (int j = 0; j < 5; ++j) in = fma(wv[j], d[1 + j], in);
+    return in;
   };
   T WF[5], Wq[5];
   // Split values of a pair whose left rows are S + A (upper, lambda = v - c) and
   // S - A (lower), at interface k = 0..4 (i-3/2 .. i+5/2) from the projections
-  // sF = S.dF, sq = S.dq, aF = A.dF, aq = A.dq (dl(j, k): j = 0..6 Delta F,
-  // 7..13 Delta q).  Lax-Friedrichs: Delta F^+- = (Delta F^s +- alpha Delta q^s)/2,
+  // sF = S.dF, sq = S.dq, aF = A.dF, aq = A.dq.  Lax-Friedrichs: Delta F^+- = (Delta F^s +- alpha Delta q^s)/2,
   // the 1/2 carried by the rows; vu[0..3] / vu[4..7] feed phi^+ / phi^-.
   auto split_k = [&](int k, T sF, T sq, T aF, T aq, T alu, T all) {
     const T uF = sF + aF, uq = sq + aq, lF = sF - aF, lq = sq - aq;
@@ -338,15 +354,23 @@ __host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, DL d
   };
   // ---- fast pair (m = 1, 7)
   {
-    const T cW = T(e.qa2 * e.af), cBy = T(e.qa2 * (sra * e.as) * e.by), cBz = T(e.qa2 * (sra * e.as) * e.bz);
-    const T A[4] = {T(e.qa2 * e.Gf), T(-e.qa2 * (e.af * e.cf)), T(e.qa2 * (e.csl * e.as * e.by * e.s)),
-                    T(e.qa2 * (e.csl * e.as * e.bz * e.s))};
+    const double Gf = e.af * e.cf * e.vn - e.as * e.csl * e.s * (e.by * e.vt1 + e.bz * e.vt2);
+    const T cW = T(qa2 * e.omg * e.af), cBy = T(qa2 * (sra * e.as) * e.by), cBz = T(qa2 * (sra * e.as) * e.bz);
+    const T A[4] = {T(qa2 * Gf), T(-qa2 * (e.af * e.cf)), T(qa2 * (e.csl * e.as * e.by * e.s)),
+                    T(qa2 * (e.csl * e.as * e.bz * e.s))};
     const T alu = al(0), all = al(6);
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
+      const T* d = row(k);
       T dF[7], dq[7];
 #pragma unroll
-      for (int j = 0; j < 7; ++j) { dF[j] = dl(j, k); dq[j] = dl(7 + j, k); }
+      for (int j = 0; j < 7; ++j) { dF[j] = d[j * PITCH]; dq[j] = d[(7 + j) * PITCH]; }
+      if constexpr (sizeof(T) == 8) {   // the differences' part of the central term
+        if (k == 1 || k == 3) {
+#pragma unroll
+          for (int j = 0; j < 7; ++j) corr[j] = fma(k == 1 ? 1.0 / 12.0 : -1.0 / 12.0, dF[j], corr[j]);
+        }
+      }
       const T wF = wdot(dF), wq = wdot(dq);
       WF[k] = wF;
       Wq[k] = wq;
@@ -356,8 +380,8 @@ __host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, DL d
       split_k(k, cW * wF + (cBy * dF[4] + cBz * dF[5]), cW * wq + (cBy * dq[4] + cBz * dq[5]), aF, aq, alu, all);
       sched_fence();
     }
-    const double fu = double(weno_split<WENO_Z>(vu, eps, epsZ, lit));
-    const double fl = double(weno_split<WENO_Z>(vl, eps, epsZ, lit));
+    const double fu = double(weno_split<WENO_Z>(vu, e3, e3Z, lit));
+    const double fl = double(weno_split<WENO_Z>(vl, e3, e3Z, lit));
     const double sp = fu + fl, sm = fu - fl;
     corr[0] += e.af * sp;
     corr[1] += e.af * e.vn * sp - e.af * e.cf * sm;
@@ -365,20 +389,22 @@ __host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, DL d
     corr[3] += e.af * e.vt2 * sp + e.csl * e.as * e.bz * e.s * sm;
     corr[4] += e.cs * e.as * e.by * e.isr * sp;
     corr[5] += e.cs * e.as * e.bz * e.isr * sp;
-    corr[6] += e.af * (0.5 * e.v2 + e.cf2 - e.g2 * e.a2) * sp - e.Gf * sm;
+    corr[6] += e.af * (hv2 + e.cf * e.cf - e.g2 * (e.cs * e.cs)) * sp - Gf * sm;
   }
   sched_fence();
   // ---- slow pair (m = 3, 5)
   {
-    const T cW = T(e.qa2 * e.as), cBy = T(-e.qa2 * (sra * e.af) * e.by), cBz = T(-e.qa2 * (sra * e.af) * e.bz);
-    const T A[4] = {T(e.qa2 * e.Gs), T(-e.qa2 * (e.as * e.csl)), T(-e.qa2 * (e.cf * e.af * e.by * e.s)),
-                    T(-e.qa2 * (e.cf * e.af * e.bz * e.s))};
+    const double Gs = e.as * e.csl * e.vn + e.af * e.cf * e.s * (e.by * e.vt1 + e.bz * e.vt2);
+    const T cW = T(qa2 * e.omg * e.as), cBy = T(-qa2 * (sra * e.af) * e.by), cBz = T(-qa2 * (sra * e.af) * e.bz);
+    const T A[4] = {T(qa2 * Gs), T(-qa2 * (e.as * e.csl)), T(-qa2 * (e.cf * e.af * e.by * e.s)),
+                    T(-qa2 * (e.cf * e.af * e.bz * e.s))};
     const T alu = al(2), all = al(4);
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
+      const T* d = row(k);
       T dF[6], dq[6];
 #pragma unroll
-      for (int j = 0; j < 6; ++j) { dF[j] = dl(j, k); dq[j] = dl(7 + j, k); }
+      for (int j = 0; j < 6; ++j) { dF[j] = d[j * PITCH]; dq[j] = d[(7 + j) * PITCH]; }
       T aF = A[0] * dF[0], aq = A[0] * dq[0];
 #pragma unroll
       for (int j = 1; j < 4; ++j) { aF += A[j] * dF[j]; aq += A[j] * dq[j]; }
@@ -386,8 +412,8 @@ __host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, DL d
               all);
       sched_fence();
     }
-    const double fu = double(weno_split<WENO_Z>(vu, eps, epsZ, lit));
-    const double fl = double(weno_split<WENO_Z>(vl, eps, epsZ, lit));
+    const double fu = double(weno_split<WENO_Z>(vu, e3, e3Z, lit));
+    const double fl = double(weno_split<WENO_Z>(vl, e3, e3Z, lit));
     const double sp = fu + fl, sm = fu - fl;
     corr[0] += e.as * sp;
     corr[1] += e.as * e.vn * sp - e.as * e.csl * sm;
@@ -395,50 +421,54 @@ __host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, DL d
     corr[3] += e.as * e.vt2 * sp - e.cf * e.af * e.bz * e.s * sm;
     corr[4] += -e.cs * e.af * e.by * e.isr * sp;
     corr[5] += -e.cs * e.af * e.bz * e.isr * sp;
-    corr[6] += e.as * (0.5 * e.v2 + e.csl2 - e.g2 * e.a2) * sp - e.Gs * sm;
+    corr[6] += e.as * (hv2 + e.csl * e.csl - e.g2 * (e.cs * e.cs)) * sp - Gs * sm;
   }
   sched_fence();
   // ---- entropy (m = 4): L = (1 - tau v^2/2, tau v, tau B_t, -tau), times 1/2, = e0/2 - 2 qa2 W
   {
-    const T cE = T(-2.0 * e.qa2);
+    const T cE = T(-2.0 * qa2 * e.omg);
     const T a4 = al(3);
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-      const T sF = T(0.5) * dl(0, k) + cE * WF[k], sq = T(0.5) * dl(7, k) + cE * Wq[k];
+      const T* d = row(k);
+      const T sF = T(0.5 * SC) * d[0] + cE * WF[k], sq = T(0.5 * SC) * d[7 * PITCH] + cE * Wq[k];
       if (k <= 3) vu[k] = sF + a4 * sq;
       if (k >= 1) vu[3 + k] = sF - a4 * sq;
       sched_fence();
     }
-    const double f4 = double(weno_split<WENO_Z>(vu, eps, epsZ, lit));
+    const double f4 = double(weno_split<WENO_Z>(vu, e3, e3Z, lit));
     corr[0] += f4;
     corr[1] += e.vn * f4;
     corr[2] += e.vt1 * f4;
     corr[3] += e.vt2 * f4;
-    corr[6] += 0.5 * e.v2 * f4;
+    corr[6] += hv2 * f4;
   }
   sched_fence();
   // ---- Alfven pair (m = 2, 6): L = (Ga/2, 0, -bz s/2, by s/2, -+sr bz/2, +-sr by/2, 0)
   {
-    const T S0 = T(0.25 * e.Ga), S2 = T(-0.25 * e.bz * e.s), S3 = T(0.25 * e.by * e.s);
-    const T A4 = T(-0.25 * e.sr * e.bz), A5 = T(0.25 * e.sr * e.by);
+    constexpr double Q = 0.25 * SC;
+    const double Ga = e.s * (e.bz * e.vt1 - e.by * e.vt2);
+    const T S0 = T(Q * Ga), S2 = T(-Q * e.bz * e.s), S3 = T(Q * e.by * e.s);
+    const T A4 = T(-Q * e.sr * e.bz), A5 = T(Q * e.sr * e.by);
     const T alu = al(1), all = al(5);
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-      const T sF = S0 * dl(0, k) + S2 * dl(2, k) + S3 * dl(3, k);
-      const T sq = S0 * dl(7, k) + S2 * dl(9, k) + S3 * dl(10, k);
-      const T aF = A4 * dl(4, k) + A5 * dl(5, k);
-      const T aq = A4 * dl(11, k) + A5 * dl(12, k);
+      const T* d = row(k);
+      const T sF = S0 * d[0] + S2 * d[2 * PITCH] + S3 * d[3 * PITCH];
+      const T sq = S0 * d[7 * PITCH] + S2 * d[9 * PITCH] + S3 * d[10 * PITCH];
+      const T aF = A4 * d[4 * PITCH] + A5 * d[5 * PITCH];
+      const T aq = A4 * d[11 * PITCH] + A5 * d[12 * PITCH];
       split_k(k, sF, sq, aF, aq, alu, all);
       sched_fence();
     }
-    const double fu = double(weno_split<WENO_Z>(vu, eps, epsZ, lit));
-    const double fl = double(weno_split<WENO_Z>(vl, eps, epsZ, lit));
+    const double fu = double(weno_split<WENO_Z>(vu, e3, e3Z, lit));
+    const double fl = double(weno_split<WENO_Z>(vl, e3, e3Z, lit));
     const double sp = fu + fl, sm = fu - fl;
     corr[2] += -e.bz * e.s * sp;
     corr[3] += e.by * e.s * sp;
     corr[4] += -e.bz * e.isr * sm;
     corr[5] += e.by * e.isr * sm;
-    corr[6] += -e.Ga * sp;
+    corr[6] += -Ga * sp;
   }
 }
 

@@ -351,6 +351,7 @@ SweepPlan sweep_plan(const wm_patch* p, int mask) {
     x.div_tb = (one + x.tb - 1) / x.tb;
     x.ncol = ncol;
     x.ntile = (n + x.ta - 1) / x.ta;
+    x.inv_ntile = 1.0 / x.ntile;
     x.blk0 = blk;
     if (mask >> d & 1) blk += (unsigned)x.ntile * (unsigned)((ncol + x.tb - 1) / x.tb);
   }
