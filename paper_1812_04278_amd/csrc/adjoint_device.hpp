@@ -46,66 +46,53 @@ __host__ __device__ __forceinline__ void reload_fence() {
 #endif
 }
 
-struct FaceEigBar {
-  double vn, vt1, vt2, Bt1, Bt2;
-  double a2, cs, sr, isr, cf, cf2, csl, csl2;
-  double by, bz, af, as;
-  double v2, Gf, Ga, Gs, qa2, tau;
-  __host__ __device__ void zero() {
-    vn = vt1 = vt2 = Bt1 = Bt2 = a2 = cs = sr = isr = cf = cf2 = csl = csl2 = 0.0;
-    by = bz = af = as = v2 = Gf = Ga = Gs = qa2 = tau = 0.0;
+// Cotangents of the face eigen-system in terms of thirteen of its scalars; each
+// pair's reverse takes the others through their definitions at once (Gamma_f,
+// Gamma_s, Gamma_a, v^2, c^2 by the members below, q = 1/(4 a^2), tau and c_s by
+// a^2, sqrt(rho) and its reciprocal by rho), so that no more stay live across the
+// next pair.
+struct EigCot {
+  double rho, vn, vt1, vt2, Bt1, Bt2, a2, cf, csl, by, bz, af, as;
+  __host__ __device__ __forceinline__ void zero() {
+    rho = vn = vt1 = vt2 = Bt1 = Bt2 = a2 = cf = csl = by = bz = af = as = 0.0;
   }
-  // pin_*: the members that the reverse of one pair writes
-  __host__ __device__ __forceinline__ void pin_fast_slow_common() {
-    pin(vn); pin(vt1); pin(vt2); pin(Bt1); pin(Bt2); pin(a2); pin(cs); pin(sr); pin(isr); pin(cf); pin(csl);
-    pin(by); pin(bz); pin(af); pin(as); pin(v2); pin(qa2);
+  __host__ __device__ __forceinline__ void pin_all() {
+    pin(rho); pin(vn); pin(vt1); pin(vt2); pin(Bt1); pin(Bt2); pin(a2); pin(cf); pin(csl); pin(by); pin(bz);
+    pin(af); pin(as);
   }
-  __host__ __device__ __forceinline__ void pin_fast() { pin_fast_slow_common(); pin(cf2); pin(Gf); }
-  __host__ __device__ __forceinline__ void pin_slow() { pin_fast_slow_common(); pin(csl2); pin(Gs); }
-  __host__ __device__ __forceinline__ void pin_alfven() { pin(bz); pin(by); pin(isr); pin(Ga); pin(sr); }
-  __host__ __device__ __forceinline__ void pin_entropy() {
-    pin(vn); pin(vt1); pin(vt2); pin(v2); pin(Bt1); pin(Bt2); pin(tau);
+  __host__ __device__ __forceinline__ void add_v2(const FaceEig& e, double l) {
+    vn += 2.0 * e.vn * l; vt1 += 2.0 * e.vt1 * l; vt2 += 2.0 * e.vt2 * l;
+  }
+  __host__ __device__ __forceinline__ void add_bv(const FaceEig& e, double l) {   // bv = by vt1 + bz vt2
+    by += l * e.vt1; vt1 += l * e.by; bz += l * e.vt2; vt2 += l * e.bz;
+  }
+  // q = 1/(4 a^2) and c_s = sqrt(a^2)
+  __host__ __device__ __forceinline__ void add_q(const FaceEig& e, double l) { a2 -= 4.0 * e.qa2 * e.qa2 * l; }
+  __host__ __device__ __forceinline__ void add_cs(const FaceEig& e, double l) { a2 += 2.0 * e.qa2 * e.cs * l; }
+  // sqrt(rho), 1/sqrt(rho)
+  __host__ __device__ __forceinline__ void add_sr(const FaceEig& e, double l) { rho += 0.5 * e.isr * l; }
+  __host__ __device__ __forceinline__ void add_isr(const FaceEig& e, double l) {
+    rho -= 0.5 * e.isr * e.isr * e.isr * l;
   }
 };
 
-// Reverse of face_eig: out[0..7] += d/d(rho, vn, vt1, vt2, Bn, Bt1, Bt2, P).
+// Reverse of face_eig: out[0..7] = d/d(rho, vn, vt1, vt2, Bn, Bt1, Bt2, P).
 __host__ __device__ __forceinline__ void face_eig_vjp(const double fp[8], const Phys& ph, const FaceEig& e,
-                                                      FaceEigBar eb, double out[8]) {
-  const double rho = fp[0], vn = fp[1], vt1 = fp[2], vt2 = fp[3], Bn = fp[4], Bt1 = fp[5], Bt2 = fp[6], P = fp[7];
+                                                      const EigCot& eb, double out[8]) {
+  const double rho = fp[0], Bn = fp[4], Bt1 = fp[5], Bt2 = fp[6], P = fp[7];
   const double gamma = ph.gamma;
   const double isr = rsq_nr(rho);
   const double irho = isr * isr;
-  const double a2 = e.a2;
-  const double ia2 = rcp_w(a2);
+  const double a2 = gamma * P * irho;
   const double Bp2 = Bt1 * Bt1 + Bt2 * Bt2;
   const double b2 = (Bn * Bn + Bp2) * irho;
   const double dab = a2 - b2;
   const double p4 = 4.0 * a2 * (Bp2 * irho);   // as in face_eig
-  const double Q = dab * dab + p4;
-  const double D = sqrt_nr(Q);
+  const double D = sqrt_nr(dab * dab + p4);
   const double cf2 = 0.5 * (a2 + b2 + D);
-  const double bv = e.by * vt1 + e.bz * vt2;
-  const double s = e.s;
-  double l_vn = eb.vn, l_vt1 = eb.vt1, l_vt2 = eb.vt2, l_Bt1 = eb.Bt1, l_Bt2 = eb.Bt2;
-  double l_a2 = eb.a2, l_cf = eb.cf, l_cf2 = eb.cf2, l_csl = eb.csl, l_csl2 = eb.csl2;
-  double l_by = eb.by, l_bz = eb.bz, l_af = eb.af, l_as = eb.as, l_v2 = eb.v2;
-  double l_isr = eb.isr, l_sr = eb.sr, l_cs = eb.cs;
-  double l_bv = 0.0, l_ia2 = 0.0, l_Bp2 = 0.0, l_b2 = 0.0, l_dab = 0.0, l_D = 0.0, l_irho = 0.0;
-  double l_rho = 0.0, l_Bn = 0.0, l_P = 0.0;
-  // Gs = as csl vn + af cf s bv
-  l_as += eb.Gs * e.csl * vn; l_csl += eb.Gs * e.as * vn; l_vn += eb.Gs * e.as * e.csl;
-  l_af += eb.Gs * e.cf * s * bv; l_cf += eb.Gs * e.af * s * bv; l_bv += eb.Gs * e.af * e.cf * s;
-  // Ga = s (bz vt1 - by vt2)
-  l_bz += eb.Ga * s * vt1; l_vt1 += eb.Ga * s * e.bz; l_by -= eb.Ga * s * vt2; l_vt2 -= eb.Ga * s * e.by;
-  // Gf = af cf vn - as csl s bv
-  l_af += eb.Gf * e.cf * vn; l_cf += eb.Gf * e.af * vn; l_vn += eb.Gf * e.af * e.cf;
-  l_as -= eb.Gf * e.csl * s * bv; l_csl -= eb.Gf * e.as * s * bv; l_bv -= eb.Gf * e.as * e.csl * s;
-  // bv = by vt1 + bz vt2
-  l_by += l_bv * vt1; l_vt1 += l_bv * e.by; l_bz += l_bv * vt2; l_vt2 += l_bv * e.bz;
-  // v2
-  l_vn += 2.0 * vn * l_v2; l_vt1 += 2.0 * vt1 * l_v2; l_vt2 += 2.0 * vt2 * l_v2;
-  // qa2 = ia2/4, tau = (gamma-1) ia2
-  l_ia2 += 0.25 * eb.qa2 + (gamma - 1.0) * eb.tau;
+  double l_Bt1 = eb.Bt1, l_Bt2 = eb.Bt2, l_a2 = eb.a2, l_rho = eb.rho;
+  double l_cf2 = 0.0, l_csl2 = 0.0, l_Bp2 = 0.0, l_b2 = 0.0, l_dab = 0.0, l_D = 0.0, l_irho = 0.0;
+  double l_Bn = 0.0, l_P = 0.0;
   // alpha_f, alpha_s (non-degenerate branch, unclamped interior)
   if (D >= ph.eps_B * ph.eps_B) {
     const double iD = rcp_w(D);
@@ -113,31 +100,31 @@ __host__ __device__ __forceinline__ void face_eig_vjp(const double fp[8], const 
     double cfa, csa;   // the forward's clamped alpha^2 (same arithmetic), for the interior test
     alpha_sq(dab, D, p4, cfa, csa);
     double l_r = 0.0;
-    if (cfa > 0.0 && cfa < 1.0 && e.af > 0.0) l_r += l_af * 0.25 * rcp_w(e.af);
-    if (csa > 0.0 && csa < 1.0 && e.as > 0.0) l_r -= l_as * 0.25 * rcp_w(e.as);
+    if (cfa > 0.0 && cfa < 1.0 && e.af > 0.0) l_r += eb.af * 0.25 * rcp_w(e.af);
+    if (csa > 0.0 && csa < 1.0 && e.as > 0.0) l_r -= eb.as * 0.25 * rcp_w(e.as);
     l_dab += l_r * iD;
     l_D -= l_r * r * iD;
   }
   // beta
   if (Bp2 > ph.eps_B) {
     const double ib = rsq_nr(Bp2);
-    l_Bt1 += l_by * ib;
-    l_Bt2 += l_bz * ib;
-    l_Bp2 -= 0.5 * ib * ib * ib * (l_by * Bt1 + l_bz * Bt2);
+    l_Bt1 += eb.by * ib;
+    l_Bt2 += eb.bz * ib;
+    l_Bp2 -= 0.5 * ib * ib * ib * (eb.by * Bt1 + eb.bz * Bt2);
   }
   // csl = sqrt(csl2)
-  if (e.csl > 0.0) l_csl2 += l_csl * 0.5 * rcp_w(e.csl);
+  if (e.csl > 0.0) l_csl2 += eb.csl * 0.5 * rcp_w(e.csl);
   // csl2 = a2 Bn^2 irho / cf2
   if (cf2 > 0.0) {
     const double icf2 = rcp_w(cf2);
     const double lN = l_csl2 * icf2;
-    l_cf2 -= l_csl2 * e.csl2 * icf2;
+    l_cf2 -= l_csl2 * (e.csl * e.csl) * icf2;
     l_a2 += lN * Bn * Bn * irho;
     l_Bn += lN * 2.0 * a2 * Bn * irho;
     l_irho += lN * a2 * Bn * Bn;
   }
   // cf = sqrt(cf2)
-  if (e.cf > 0.0) l_cf2 += l_cf * 0.5 * rcp_w(e.cf);
+  if (e.cf > 0.0) l_cf2 += eb.cf * 0.5 * rcp_w(e.cf);
   // cf2 = (a2 + b2 + D)/2
   l_a2 += 0.5 * l_cf2; l_b2 += 0.5 * l_cf2; l_D += 0.5 * l_cf2;
   // D = sqrt(dab^2 + 4 a2 Bp2 irho)
@@ -154,17 +141,12 @@ __host__ __device__ __forceinline__ void face_eig_vjp(const double fp[8], const 
   l_Bn += 2.0 * Bn * irho * l_b2; l_Bp2 += irho * l_b2; l_irho += (Bn * Bn + Bp2) * l_b2;
   // Bp2
   l_Bt1 += 2.0 * Bt1 * l_Bp2; l_Bt2 += 2.0 * Bt2 * l_Bp2;
-  // ia2 = 1/a2, cs = sqrt(a2)
-  l_a2 -= ia2 * ia2 * l_ia2;
-  if (e.cs > 0.0) l_a2 += l_cs * 0.5 * rcp_w(e.cs);
   // a2 = gamma P irho
   l_P += gamma * irho * l_a2; l_irho += gamma * P * l_a2;
-  // irho = isr^2, sr = rho isr, isr = rho^(-1/2)
-  l_isr += 2.0 * isr * l_irho;
-  l_rho += isr * l_sr; l_isr += rho * l_sr;
-  l_rho -= 0.5 * isr * isr * isr * l_isr;
-  out[0] += l_rho; out[1] += l_vn; out[2] += l_vt1; out[3] += l_vt2;
-  out[4] += l_Bn; out[5] += l_Bt1; out[6] += l_Bt2; out[7] += l_P;
+  // irho = 1/rho
+  l_rho -= irho * irho * l_irho;
+  out[0] = l_rho; out[1] = eb.vn; out[2] = eb.vt1; out[3] = eb.vt2;
+  out[4] = l_Bn; out[5] = l_Bt1; out[6] = l_Bt2; out[7] = l_P;
 }
 
 // ---------------------------------------------------------------------------
@@ -291,80 +273,98 @@ struct PairShape {
 };
 
 // Split values, phi and its gradient for one row: from the projections uF, uq
-// (interfaces 0..4) to f and the cotangents lP (of uF), lQ (of uq) and of alpha.
+// (interfaces 0..4) to f, the cotangents g[0..3] of Delta F^+ and g[4..7] of
+// Delta F^- (of uF at interface k: g[k] + g[3 + k], of uq al times their
+// difference, where they exist) and the cotangent of alpha.
 template <bool WZ>
 __host__ __device__ __forceinline__ void row_split_grad(const double uF[5], const double uq[5], double al, double lf,
-                                                        double eps, double epsZ, bool lit, double& f, double lP[5],
-                                                        double lQ[5], double& lal) {
-  double v[8];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) v[k] = uF[k] + al * uq[k];
-#pragma unroll
-  for (int k = 1; k < 5; ++k) v[3 + k] = uF[k] - al * uq[k];
-  double g[8], g4[4], pa, pb;
-  phiN_val_grad<WZ>(v[7], v[6], v[5], v[4], eps, epsZ, lit, pa, g4);
+                                                        double eps, double epsZ, bool lit, double& f, double g[8],
+                                                        double& lal) {
+  double g4[4], pa, pb;
+  phiN_val_grad<WZ>(uF[4] - al * uq[4], uF[3] - al * uq[3], uF[2] - al * uq[2], uF[1] - al * uq[1], eps, epsZ, lit,
+                    pa, g4);
   g[7] = g4[0] * lf; g[6] = g4[1] * lf; g[5] = g4[2] * lf; g[4] = g4[3] * lf;
-  phiN_val_grad<WZ>(v[0], v[1], v[2], v[3], eps, epsZ, lit, pb, g4);
+  sched_fence();
+  phiN_val_grad<WZ>(uF[0] + al * uq[0], uF[1] + al * uq[1], uF[2] + al * uq[2], uF[3] + al * uq[3], eps, epsZ, lit,
+                    pb, g4);
   g[0] = -g4[0] * lf; g[1] = -g4[1] * lf; g[2] = -g4[2] * lf; g[3] = -g4[3] * lf;
   f = pa - pb;
 #pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    const double pk = k <= 3 ? g[k] : 0.0, mk = k >= 1 ? g[3 + k] : 0.0;
-    lP[k] = pk + mk;
-    lQ[k] = al * (pk - mk);
-    lal += uq[k] * (pk - mk);
-  }
+  for (int k = 0; k < 5; ++k)
+    lal += uq[k] * (k == 0 ? g[0] : (k == 4 ? -g[7] : g[k] - g[3 + k]));
+  sched_fence();
 }
 
-// Forward and reverse of two pairs at once: one read of the differences per
-// interface serves both, and one barrier round per interface carries both
-// pairs' cotangents (emit(k, lD[14])).
-template <class PA, bool TWOA, class PB, bool TWOB, bool WZ, class DL, class EMIT>
-__host__ __device__ __forceinline__ void pair2_rev(const PairRows& ra, const PairRows& rb, DL dl, double eps,
-                                                   double epsZ, bool lit, PairCot& ca, PairCot& cb, EMIT emit) {
-  double uFa[5], uqa[5], lFa[5], lqa[5], uFb[5], uqb[5], lFb[5], lqb[5];
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    double d[14];
-#pragma unroll
-    for (int j = 0; j < 14; ++j) d[j] = dl(j, k);
-    PA::proj(ra, d, uFa[k], uqa[k], lFa[k], lqa[k]);
-    PB::proj(rb, d, uFb[k], uqb[k], lFb[k], lqb[k]);
-    sched_fence();
+struct PairGrad {
+  double u[8], l[8];   // row_split_grad's g of the upper and lower row
+};
+// Cotangents of the projections at interface k, summed and subtracted over the two
+// rows: sF, aF of S.dF and A.dF, sq, aq of S.dq and A.dq.
+template <bool TWO>
+__host__ __device__ __forceinline__ void pair_sums(const PairRows& r, const PairGrad& g, int k, double& sF, double& aF,
+                                                   double& sq, double& aq) {
+  auto lP = [](const double* v, int i) { return i == 0 ? v[0] : (i == 4 ? v[7] : v[i] + v[3 + i]); };
+  auto lQ = [](const double* v, int i) { return i == 0 ? v[0] : (i == 4 ? -v[7] : v[i] - v[3 + i]); };
+  const double Pu = lP(g.u, k), Qu = r.alu * lQ(g.u, k);
+  if (TWO) {
+    const double Pl = lP(g.l, k), Ql = r.all * lQ(g.l, k);
+    sF = Pu + Pl; aF = Pu - Pl; sq = Qu + Ql; aq = Qu - Ql;
+  } else {
+    sF = aF = Pu; sq = aq = Qu;
   }
-  double lPua[5], lQua[5], lPla[5], lQla[5], lPub[5], lQub[5], lPlb[5], lQlb[5];
-  row_split_grad<WZ>(uFa, uqa, ra.alu, ra.lfu, eps, epsZ, lit, ca.fu, lPua, lQua, ca.lalu);
-  if (TWOA) row_split_grad<WZ>(lFa, lqa, ra.all, ra.lfl, eps, epsZ, lit, ca.fl, lPla, lQla, ca.lall);
-  row_split_grad<WZ>(uFb, uqb, rb.alu, rb.lfu, eps, epsZ, lit, cb.fu, lPub, lQub, cb.lalu);
-  if (TWOB) row_split_grad<WZ>(lFb, lqb, rb.all, rb.lfl, eps, epsZ, lit, cb.fl, lPlb, lQlb, cb.lall);
+}
+// Forward and reverse of one pair up to the cotangents of its rows.  row(k) points
+// at the differences of interface k, PITCH values apart; they are read again for
+// the row cotangents rather than held.
+template <class PA, bool TWO, bool WZ, int PITCH, class ROW>
+__host__ __device__ __forceinline__ void pair_rev(const PairRows& r, ROW row, double eps, double epsZ, bool lit,
+                                                  PairCot& c, PairGrad& g) {
+  {
+    double uF[5], uq[5], lF[5], lq[5];
 #pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    if (!TWOA) { lPla[k] = 0.0; lQla[k] = 0.0; }
-    if (!TWOB) { lPlb[k] = 0.0; lQlb[k] = 0.0; }
+    for (int k = 0; k < 5; ++k) {
+      const double* p = row(k);
+      double d[14];
+#pragma unroll
+      for (int j = 0; j < 14; ++j) d[j] = p[j * PITCH];
+      PA::proj(r, d, uF[k], uq[k], lF[k], lq[k]);
+      sched_fence();
+    }
+    row_split_grad<WZ>(uF, uq, r.alu, r.lfu, eps, epsZ, lit, c.fu, g.u, c.lalu);
+    if (TWO) row_split_grad<WZ>(lF, lq, r.all, r.lfl, eps, epsZ, lit, c.fl, g.l, c.lall);
   }
-  // cotangents of the rows (a second read of the differences, no synchronisation) ...
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    pin(g.u[j]);
+    if (TWO) pin(g.l[j]);
+  }
   reload_fence();
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
-    double d[14];
+    const double* p = row(k);
+    double d[14], sF, aF, sq, aq;
 #pragma unroll
-    for (int j = 0; j < 14; ++j) d[j] = dl(j, k);
-    PA::rowcot(d, lPua[k] + lPla[k], lPua[k] - lPla[k], lQua[k] + lQla[k], lQua[k] - lQla[k], ca);
-    PB::rowcot(d, lPub[k] + lPlb[k], lPub[k] - lPlb[k], lQub[k] + lQlb[k], lQub[k] - lQlb[k], cb);
+    for (int j = 0; j < 14; ++j) d[j] = p[j * PITCH];
+    pair_sums<TWO>(r, g, k, sF, aF, sq, aq);
+    PA::rowcot(d, sF, aF, sq, aq, c);
     sched_fence();
   }
 #pragma unroll
-  for (int j = 0; j < 7; ++j) { pin(ca.lS[j]); pin(cb.lS[j]); }
+  for (int j = 0; j < 7; ++j) pin(c.lS[j]);
 #pragma unroll
-  for (int j = 0; j < 4; ++j) { pin(ca.lA[j]); pin(cb.lA[j]); }
-  // ... then those of the interface differences, one barrier-separated round per k
+  for (int j = 0; j < 4; ++j) pin(c.lA[j]);
+}
+
+// The pair's cotangents of the interface differences: emit(k, lD[14]), k = 0..4.
+template <class PA, bool TWO, class EMIT>
+__host__ __device__ __forceinline__ void pair_emit(const PairRows& r, const PairGrad& g, EMIT emit) {
 #pragma unroll
   for (int k = 0; k < 5; ++k) {
-    double lD[14];
+    double lD[14], sF, aF, sq, aq;
+    pair_sums<TWO>(r, g, k, sF, aF, sq, aq);
 #pragma unroll
     for (int j = 0; j < 14; ++j) lD[j] = 0.0;
-    PA::difcot(ra, lPua[k] + lPla[k], lPua[k] - lPla[k], lQua[k] + lQla[k], lQua[k] - lQla[k], lD);
-    PB::difcot(rb, lPub[k] + lPlb[k], lPub[k] - lPlb[k], lQub[k] + lQlb[k], lQub[k] - lQlb[k], lD);
+    PA::difcot(r, sF, aF, sq, aq, lD);
     emit(k, lD);
   }
 }
@@ -373,189 +373,150 @@ __host__ __device__ __forceinline__ void pair2_rev(const PairRows& ra, const Pai
 // rows and right-vector cotangents of each pair (Appendix A), with the
 // reverse of the row construction into the eigen-scalar cotangents eb
 // ---------------------------------------------------------------------------
-// fast pair (m = 1, 7): S = qa2 t, A = qa2 u
-template <class ALF, class LAM>
-__host__ __device__ __forceinline__ void fast_rows(const FaceEig& e, ALF alf, LAM lamf, PairRows& r) {
-  const double gm1 = -e.omg, omg = e.omg, qa2 = e.qa2, sra = e.sr * e.cs, s = e.s;
-  const double t[7] = {e.af * e.g1 * e.v2, omg * e.af * e.vn, omg * e.af * e.vt1, omg * e.af * e.vt2,
-                       omg * e.af * e.Bt1 + sra * e.as * e.by, omg * e.af * e.Bt2 + sra * e.as * e.bz, gm1 * e.af};
-  const double u[4] = {e.Gf, -(e.af * e.cf), e.csl * e.as * e.by * s, e.csl * e.as * e.bz * s};
-#pragma unroll
-  for (int j = 0; j < 7; ++j) r.S[j] = qa2 * t[j];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) r.A[j] = qa2 * u[j];
-  const double lam[7] = {lamf(0), lamf(1), lamf(2), lamf(3), lamf(4), lamf(5), lamf(6)};
-  const double Rs6 = e.af * (0.5 * e.v2 + e.cf2 - e.g2 * e.a2);
-  // corr[0..6] = af sp; af vn sp - af cf sm; af vt1 sp + csl as by s sm; af vt2 sp + csl as bz s sm;
-  //              cs as by isr sp; cs as bz isr sp; Rs6 sp - Gf sm   (sp = fu + fl, sm = fu - fl)
-  const double lsp = e.af * lam[0] + e.af * e.vn * lam[1] + e.af * e.vt1 * lam[2] + e.af * e.vt2 * lam[3] +
-                     e.cs * e.as * e.isr * (e.by * lam[4] + e.bz * lam[5]) + Rs6 * lam[6];
-  const double lsm = -e.af * e.cf * lam[1] + e.csl * e.as * s * (e.by * lam[2] + e.bz * lam[3]) - e.Gf * lam[6];
+// fast pair (m = 1, 7) and slow pair (m = 3, 5).  With (x, y, c, o, G, z) = (alpha_f,
+// alpha_s, c_f, c_s, Gamma_f, +1) for the fast and (alpha_s, alpha_f, c_s, c_f, Gamma_s, -1)
+// for the slow pair (c_s the slow speed here), W = omg (-v2/2, vn, vt1, vt2, Bt1, Bt2, -1):
+//   S = q (x W + z sra y beta),  A = q (G, -x c, z o y s by, z o y s bz),  q = 1/(4 a^2),
+// and the right columns add to corr, with sp = fu + fl, sm = fu - fl,
+//   x sp;  x vn sp - x c sm;  x vt1 sp + z o y s by sm;  x vt2 sp + z o y s bz sm;
+//   z cs y isr by sp;  z cs y isr bz sp;  x (v2/2 + c^2 - g2 a^2) sp - G sm.
+template <bool FAST> struct Magneto {
+  double x, y, c, o, G, bv, zo, zs;   // zo = z o y s, zs = z y
+  __host__ __device__ __forceinline__ explicit Magneto(const FaceEig& e) {
+    bv = e.by * e.vt1 + e.bz * e.vt2;
+    if (FAST) { x = e.af; y = e.as; c = e.cf; o = e.csl; }
+    else      { x = e.as; y = e.af; c = e.csl; o = e.cf; }
+    zs = FAST ? y : -y;
+    zo = zs * o * e.s;
+    G = x * c * e.vn - zo * bv;
+  }
+};
+template <bool FAST, class ALF>
+__host__ __device__ __forceinline__ void magneto_rows(const FaceEig& e, ALF alf, const double lam[7], PairRows& r) {
+  const Magneto<FAST> m(e);
+  const double q = e.qa2, qw = q * e.omg * m.x, qb = q * (e.sr * e.cs) * m.zs, hv2 = 0.5 * e.v2;
+  r.S[0] = -qw * hv2; r.S[1] = qw * e.vn; r.S[2] = qw * e.vt1; r.S[3] = qw * e.vt2;
+  r.S[4] = qw * e.Bt1 + qb * e.by; r.S[5] = qw * e.Bt2 + qb * e.bz; r.S[6] = -qw;
+  r.A[0] = q * m.G; r.A[1] = -q * (m.x * m.c); r.A[2] = q * m.zo * e.by; r.A[3] = q * m.zo * e.bz;
+  const double lb = e.by * lam[2] + e.bz * lam[3], lB = e.by * lam[4] + e.bz * lam[5];
+  const double Rs6 = hv2 + m.c * m.c - e.g2 * (e.cs * e.cs);
+  const double lsp = m.x * (lam[0] + e.vn * lam[1] + e.vt1 * lam[2] + e.vt2 * lam[3] + Rs6 * lam[6]) +
+                     e.cs * e.isr * m.zs * lB;
+  const double lsm = -m.x * m.c * lam[1] + m.zo * lb - m.G * lam[6];
   r.lfu = lsp + lsm;
   r.lfl = lsp - lsm;
-  r.alu = alf(0);
-  r.all = alf(6);
+  r.alu = alf(FAST ? 0 : 2);
+  r.all = alf(FAST ? 6 : 4);
 }
-template <class LAM>
-__host__ __device__ __forceinline__ void fast_post(const FaceEig& e, LAM lamf, const PairCot& c, FaceEigBar& eb) {
-  const double gm1 = -e.omg, omg = e.omg, qa2 = e.qa2, sra = e.sr * e.cs, s = e.s;
-  const double t[7] = {e.af * e.g1 * e.v2, omg * e.af * e.vn, omg * e.af * e.vt1, omg * e.af * e.vt2,
-                       omg * e.af * e.Bt1 + sra * e.as * e.by, omg * e.af * e.Bt2 + sra * e.as * e.bz, gm1 * e.af};
-  const double u[4] = {e.Gf, -(e.af * e.cf), e.csl * e.as * e.by * s, e.csl * e.as * e.bz * s};
-  const double lam[7] = {lamf(0), lamf(1), lamf(2), lamf(3), lamf(4), lamf(5), lamf(6)};
-  const double sp = c.fu + c.fl, sm = c.fu - c.fl;
-  eb.af += sp * (lam[0] + e.vn * lam[1] + e.vt1 * lam[2] + e.vt2 * lam[3] +
-                 (0.5 * e.v2 + e.cf2 - e.g2 * e.a2) * lam[6]) - sm * e.cf * lam[1];
-  eb.vn += e.af * sp * lam[1]; eb.vt1 += e.af * sp * lam[2]; eb.vt2 += e.af * sp * lam[3];
-  eb.cf -= e.af * sm * lam[1];
-  eb.cf2 += e.af * sp * lam[6]; eb.v2 += 0.5 * e.af * sp * lam[6]; eb.a2 -= e.g2 * e.af * sp * lam[6];
-  eb.csl += sm * e.as * s * (e.by * lam[2] + e.bz * lam[3]);
-  eb.as += sm * e.csl * s * (e.by * lam[2] + e.bz * lam[3]) + sp * e.cs * e.isr * (e.by * lam[4] + e.bz * lam[5]);
-  eb.by += sm * e.csl * e.as * s * lam[2] + sp * e.cs * e.as * e.isr * lam[4];
-  eb.bz += sm * e.csl * e.as * s * lam[3] + sp * e.cs * e.as * e.isr * lam[5];
-  eb.cs += sp * e.as * e.isr * (e.by * lam[4] + e.bz * lam[5]);
-  eb.isr += sp * e.cs * e.as * (e.by * lam[4] + e.bz * lam[5]);
-  eb.Gf -= sm * lam[6];
-  // rows S = qa2 t, A = qa2 u
-  double lt[7], lu[4];
-#pragma unroll
-  for (int j = 0; j < 7; ++j) { eb.qa2 += c.lS[j] * t[j]; lt[j] = qa2 * c.lS[j]; }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) { eb.qa2 += c.lA[j] * u[j]; lu[j] = qa2 * c.lA[j]; }
-  eb.af += lt[0] * e.g1 * e.v2 + omg * (lt[1] * e.vn + lt[2] * e.vt1 + lt[3] * e.vt2 + lt[4] * e.Bt1 +
-                                        lt[5] * e.Bt2) + gm1 * lt[6];
-  eb.v2 += lt[0] * e.af * e.g1;
-  eb.vn += lt[1] * omg * e.af; eb.vt1 += lt[2] * omg * e.af; eb.vt2 += lt[3] * omg * e.af;
-  eb.Bt1 += lt[4] * omg * e.af; eb.Bt2 += lt[5] * omg * e.af;
-  eb.sr += e.cs * e.as * (lt[4] * e.by + lt[5] * e.bz);
-  eb.cs += e.sr * e.as * (lt[4] * e.by + lt[5] * e.bz);
-  eb.as += sra * (lt[4] * e.by + lt[5] * e.bz);
-  eb.by += sra * e.as * lt[4]; eb.bz += sra * e.as * lt[5];
-  eb.Gf += lu[0];
-  eb.af -= lu[1] * e.cf; eb.cf -= lu[1] * e.af;
-  eb.csl += e.as * s * (lu[2] * e.by + lu[3] * e.bz);
-  eb.as += e.csl * s * (lu[2] * e.by + lu[3] * e.bz);
-  eb.by += e.csl * e.as * s * lu[2]; eb.bz += e.csl * e.as * s * lu[3];
-}
-
-// slow pair (m = 3, 5): S = qa2 t, A = qa2 u
-template <class ALF, class LAM>
-__host__ __device__ __forceinline__ void slow_rows(const FaceEig& e, ALF alf, LAM lamf, PairRows& r) {
-  const double gm1 = -e.omg, omg = e.omg, qa2 = e.qa2, sra = e.sr * e.cs, s = e.s;
-  const double t[7] = {e.as * e.g1 * e.v2, omg * e.as * e.vn, omg * e.as * e.vt1, omg * e.as * e.vt2,
-                       omg * e.as * e.Bt1 - sra * e.af * e.by, omg * e.as * e.Bt2 - sra * e.af * e.bz, gm1 * e.as};
-  const double u[4] = {e.Gs, -(e.as * e.csl), -(e.cf * e.af * e.by * s), -(e.cf * e.af * e.bz * s)};
-#pragma unroll
-  for (int j = 0; j < 7; ++j) r.S[j] = qa2 * t[j];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) r.A[j] = qa2 * u[j];
-  const double lam[7] = {lamf(0), lamf(1), lamf(2), lamf(3), lamf(4), lamf(5), lamf(6)};
-  const double Rs6 = e.as * (0.5 * e.v2 + e.csl2 - e.g2 * e.a2);
-  // corr += as sp; as vn sp - as csl sm; as vt1 sp - cf af by s sm; as vt2 sp - cf af bz s sm;
-  //         -cs af by isr sp; -cs af bz isr sp; Rs6 sp - Gs sm
-  const double lsp = e.as * lam[0] + e.as * e.vn * lam[1] + e.as * e.vt1 * lam[2] + e.as * e.vt2 * lam[3] -
-                     e.cs * e.af * e.isr * (e.by * lam[4] + e.bz * lam[5]) + Rs6 * lam[6];
-  const double lsm = -e.as * e.csl * lam[1] - e.cf * e.af * s * (e.by * lam[2] + e.bz * lam[3]) - e.Gs * lam[6];
-  r.lfu = lsp + lsm;
-  r.lfl = lsp - lsm;
-  r.alu = alf(2);
-  r.all = alf(4);
-}
-template <class LAM>
-__host__ __device__ __forceinline__ void slow_post(const FaceEig& e, LAM lamf, const PairCot& c, FaceEigBar& eb) {
-  const double gm1 = -e.omg, omg = e.omg, qa2 = e.qa2, sra = e.sr * e.cs, s = e.s;
-  const double t[7] = {e.as * e.g1 * e.v2, omg * e.as * e.vn, omg * e.as * e.vt1, omg * e.as * e.vt2,
-                       omg * e.as * e.Bt1 - sra * e.af * e.by, omg * e.as * e.Bt2 - sra * e.af * e.bz, gm1 * e.as};
-  const double u[4] = {e.Gs, -(e.as * e.csl), -(e.cf * e.af * e.by * s), -(e.cf * e.af * e.bz * s)};
-  const double lam[7] = {lamf(0), lamf(1), lamf(2), lamf(3), lamf(4), lamf(5), lamf(6)};
-  const double sp = c.fu + c.fl, sm = c.fu - c.fl;
-  eb.as += sp * (lam[0] + e.vn * lam[1] + e.vt1 * lam[2] + e.vt2 * lam[3] +
-                 (0.5 * e.v2 + e.csl2 - e.g2 * e.a2) * lam[6]) - sm * e.csl * lam[1];
-  eb.vn += e.as * sp * lam[1]; eb.vt1 += e.as * sp * lam[2]; eb.vt2 += e.as * sp * lam[3];
-  eb.csl -= e.as * sm * lam[1];
-  eb.csl2 += e.as * sp * lam[6]; eb.v2 += 0.5 * e.as * sp * lam[6]; eb.a2 -= e.g2 * e.as * sp * lam[6];
-  eb.cf -= sm * e.af * s * (e.by * lam[2] + e.bz * lam[3]);
-  eb.af -= sm * e.cf * s * (e.by * lam[2] + e.bz * lam[3]) + sp * e.cs * e.isr * (e.by * lam[4] + e.bz * lam[5]);
-  eb.by -= sm * e.cf * e.af * s * lam[2] + sp * e.cs * e.af * e.isr * lam[4];
-  eb.bz -= sm * e.cf * e.af * s * lam[3] + sp * e.cs * e.af * e.isr * lam[5];
-  eb.cs -= sp * e.af * e.isr * (e.by * lam[4] + e.bz * lam[5]);
-  eb.isr -= sp * e.cs * e.af * (e.by * lam[4] + e.bz * lam[5]);
-  eb.Gs -= sm * lam[6];
-  double lt[7], lu[4];
-#pragma unroll
-  for (int j = 0; j < 7; ++j) { eb.qa2 += c.lS[j] * t[j]; lt[j] = qa2 * c.lS[j]; }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) { eb.qa2 += c.lA[j] * u[j]; lu[j] = qa2 * c.lA[j]; }
-  eb.as += lt[0] * e.g1 * e.v2 + omg * (lt[1] * e.vn + lt[2] * e.vt1 + lt[3] * e.vt2 + lt[4] * e.Bt1 +
-                                        lt[5] * e.Bt2) + gm1 * lt[6];
-  eb.v2 += lt[0] * e.as * e.g1;
-  eb.vn += lt[1] * omg * e.as; eb.vt1 += lt[2] * omg * e.as; eb.vt2 += lt[3] * omg * e.as;
-  eb.Bt1 += lt[4] * omg * e.as; eb.Bt2 += lt[5] * omg * e.as;
-  eb.sr -= e.cs * e.af * (lt[4] * e.by + lt[5] * e.bz);
-  eb.cs -= e.sr * e.af * (lt[4] * e.by + lt[5] * e.bz);
-  eb.af -= sra * (lt[4] * e.by + lt[5] * e.bz);
-  eb.by -= sra * e.af * lt[4]; eb.bz -= sra * e.af * lt[5];
-  eb.Gs += lu[0];
-  eb.as -= lu[1] * e.csl; eb.csl -= lu[1] * e.as;
-  eb.cf -= e.af * s * (lu[2] * e.by + lu[3] * e.bz);
-  eb.af -= e.cf * s * (lu[2] * e.by + lu[3] * e.bz);
-  eb.by -= e.cf * e.af * s * lu[2]; eb.bz -= e.cf * e.af * s * lu[3];
+template <bool FAST>
+__host__ __device__ __forceinline__ void magneto_post(const FaceEig& e, const double lam[7], const PairCot& p,
+                                                      EigCot& eb) {
+  const Magneto<FAST> m(e);
+  const double q = e.qa2, sra = e.sr * e.cs, z = FAST ? 1.0 : -1.0, hv2 = 0.5 * e.v2;
+  const double sp = p.fu + p.fl, sm = p.fu - p.fl;
+  const double lb = e.by * lam[2] + e.bz * lam[3], lB = e.by * lam[4] + e.bz * lam[5];
+  // right columns
+  double lx = sp * (lam[0] + e.vn * lam[1] + e.vt1 * lam[2] + e.vt2 * lam[3] +
+                    (hv2 + m.c * m.c - e.g2 * (e.cs * e.cs)) * lam[6]) - sm * m.c * lam[1];
+  const double xs = m.x * sp;
+  eb.vn += xs * lam[1]; eb.vt1 += xs * lam[2]; eb.vt2 += xs * lam[3];
+  eb.a2 -= e.g2 * xs * lam[6];
+  double lv2 = 0.5 * xs * lam[6];
+  double lc = 2.0 * m.c * xs * lam[6] - m.x * sm * lam[1];
+  double lzo = sm * lb;                          // cotangent of zo
+  double lzs = e.cs * e.isr * sp * lB;           // of zs
+  eb.by += sm * m.zo * lam[2] + sp * e.cs * e.isr * m.zs * lam[4];
+  eb.bz += sm * m.zo * lam[3] + sp * e.cs * e.isr * m.zs * lam[5];
+  double lcs = e.isr * m.zs * sp * lB;
+  eb.add_isr(e, e.cs * m.zs * sp * lB);
+  double lG = -sm * lam[6];
+  // rows
+  const double LW = e.omg * (e.vn * p.lS[1] + e.vt1 * p.lS[2] + e.vt2 * p.lS[3] + e.Bt1 * p.lS[4] + e.Bt2 * p.lS[5] -
+                             hv2 * p.lS[0] - p.lS[6]);
+  const double LB = e.by * p.lS[4] + e.bz * p.lS[5], LC = e.by * p.lA[2] + e.bz * p.lA[3];
+  eb.add_q(e, m.x * LW + sra * m.zs * LB + m.G * p.lA[0] - m.x * m.c * p.lA[1] + m.zo * LC);
+  const double qw = q * e.omg * m.x;
+  lx += q * LW - q * m.c * p.lA[1];
+  lv2 -= 0.5 * qw * p.lS[0];
+  eb.vn += qw * p.lS[1]; eb.vt1 += qw * p.lS[2]; eb.vt2 += qw * p.lS[3];
+  eb.Bt1 += qw * p.lS[4]; eb.Bt2 += qw * p.lS[5];
+  lzs += q * sra * LB;
+  eb.by += q * (sra * m.zs * p.lS[4] + m.zo * p.lA[2]);
+  eb.bz += q * (sra * m.zs * p.lS[5] + m.zo * p.lA[3]);
+  eb.add_sr(e, q * e.cs * m.zs * LB);
+  lcs += q * e.sr * m.zs * LB;
+  lc -= q * m.x * p.lA[1];
+  lzo += q * LC;
+  lG += q * p.lA[0];
+  // G = x c vn - zo bv
+  lx += lG * m.c * e.vn;
+  lc += lG * m.x * e.vn;
+  eb.vn += lG * m.x * m.c;
+  lzo -= lG * m.bv;
+  eb.add_bv(e, -lG * m.zo);
+  // zo = zs o s, zs = z y
+  lzs += lzo * m.o * e.s;
+  const double lo = lzo * m.zs * e.s, ly = z * lzs;
+  if (FAST) { eb.af += lx; eb.as += ly; eb.cf += lc; eb.csl += lo; }
+  else      { eb.as += lx; eb.af += ly; eb.csl += lc; eb.cf += lo; }
+  eb.add_cs(e, lcs);
+  eb.add_v2(e, lv2);
 }
 
 // Alfven pair (m = 2, 6): S = (Ga/4, 0, -bz s/4, by s/4, 0, 0, 0), A = (-sr bz/4, sr by/4) on components 4, 5
-template <class ALF, class LAM>
-__host__ __device__ __forceinline__ void alfven_rows(const FaceEig& e, ALF alf, LAM lamf, PairRows& r) {
-  const double s = e.s;
-  r.S[0] = 0.25 * e.Ga; r.S[1] = 0.0; r.S[2] = -0.25 * e.bz * s; r.S[3] = 0.25 * e.by * s;
+template <class ALF>
+__host__ __device__ __forceinline__ void alfven_rows(const FaceEig& e, ALF alf, const double lam[7], PairRows& r) {
+  const double s = e.s, Ga = s * (e.bz * e.vt1 - e.by * e.vt2);
+  r.S[0] = 0.25 * Ga; r.S[1] = 0.0; r.S[2] = -0.25 * e.bz * s; r.S[3] = 0.25 * e.by * s;
   r.S[4] = 0.0; r.S[5] = 0.0; r.S[6] = 0.0;
   r.A[0] = -0.25 * e.sr * e.bz; r.A[1] = 0.25 * e.sr * e.by; r.A[2] = 0.0; r.A[3] = 0.0;
   // corr += (0, 0, -bz s sp, by s sp, -bz isr sm, by isr sm, -Ga sp)
-  const double lsp = -e.bz * s * lamf(2) + e.by * s * lamf(3) - e.Ga * lamf(6);
-  const double lsm = -e.bz * e.isr * lamf(4) + e.by * e.isr * lamf(5);
+  const double lsp = s * (e.by * lam[3] - e.bz * lam[2]) - Ga * lam[6];
+  const double lsm = e.isr * (e.by * lam[5] - e.bz * lam[4]);
   r.lfu = lsp + lsm;
   r.lfl = lsp - lsm;
   r.alu = alf(1);
   r.all = alf(5);
 }
-template <class LAM>
-__host__ __device__ __forceinline__ void alfven_post(const FaceEig& e, LAM lamf, const PairCot& c, FaceEigBar& eb) {
+__host__ __device__ __forceinline__ void alfven_post(const FaceEig& e, const double lam[7], const PairCot& c,
+                                                     EigCot& eb) {
   const double s = e.s;
-  const double lam2 = lamf(2), lam3 = lamf(3), lam4 = lamf(4), lam5 = lamf(5), lam6 = lamf(6);
   const double sp = c.fu + c.fl, sm = c.fu - c.fl;
-  eb.bz += -s * sp * lam2 - e.isr * sm * lam4;
-  eb.by += s * sp * lam3 + e.isr * sm * lam5;
-  eb.isr += sm * (-e.bz * lam4 + e.by * lam5);
-  eb.Ga -= sp * lam6;
-  eb.Ga += 0.25 * c.lS[0];
-  eb.bz += -0.25 * s * c.lS[2] - 0.25 * e.sr * c.lA[0];
-  eb.by += 0.25 * s * c.lS[3] + 0.25 * e.sr * c.lA[1];
-  eb.sr += -0.25 * e.bz * c.lA[0] + 0.25 * e.by * c.lA[1];
+  eb.bz -= s * (sp * lam[2] + 0.25 * c.lS[2]) + e.isr * sm * lam[4] + 0.25 * e.sr * c.lA[0];
+  eb.by += s * (sp * lam[3] + 0.25 * c.lS[3]) + e.isr * sm * lam[5] + 0.25 * e.sr * c.lA[1];
+  eb.add_isr(e, sm * (e.by * lam[5] - e.bz * lam[4]));
+  eb.add_sr(e, 0.25 * (e.by * c.lA[1] - e.bz * c.lA[0]));
+  const double lGa = s * (0.25 * c.lS[0] - sp * lam[6]);   // Ga = s (bz vt1 - by vt2)
+  eb.bz += lGa * e.vt1; eb.vt1 += lGa * e.bz; eb.by -= lGa * e.vt2; eb.vt2 -= lGa * e.by;
 }
 
-// entropy (m = 4): the single row L/2 = (1/2 - tau v^2/4, tau vn/2, tau vt1/2, tau vt2/2, tau Bt1/2, tau Bt2/2, -tau/2)
-template <class ALF, class LAM>
-__host__ __device__ __forceinline__ void entropy_rows(const FaceEig& e, ALF alf, LAM lamf, PairRows& r) {
-  const double ht = 0.5 * e.tau;
+// entropy (m = 4): the single row L/2 = (1/2 - tau v^2/4, tau vn/2, tau vt1/2, tau vt2/2, tau Bt1/2, tau Bt2/2, -tau/2),
+// tau = (gamma - 1)/a^2 = -4 omg q
+template <class ALF>
+__host__ __device__ __forceinline__ void entropy_rows(const FaceEig& e, ALF alf, const double lam[7], PairRows& r) {
+  const double ht = -2.0 * e.omg * e.qa2;
   r.S[0] = 0.5 - 0.5 * ht * e.v2; r.S[1] = ht * e.vn; r.S[2] = ht * e.vt1; r.S[3] = ht * e.vt2;
   r.S[4] = ht * e.Bt1; r.S[5] = ht * e.Bt2; r.S[6] = -ht;
   r.A[0] = r.A[1] = r.A[2] = r.A[3] = 0.0;
   // corr += (f4, vn f4, vt1 f4, vt2 f4, 0, 0, v2/2 f4)
-  r.lfu = lamf(0) + e.vn * lamf(1) + e.vt1 * lamf(2) + e.vt2 * lamf(3) + 0.5 * e.v2 * lamf(6);
+  r.lfu = lam[0] + e.vn * lam[1] + e.vt1 * lam[2] + e.vt2 * lam[3] + 0.5 * e.v2 * lam[6];
   r.lfl = 0.0;
   r.alu = alf(3);
   r.all = r.alu;
 }
-template <class LAM>
-__host__ __device__ __forceinline__ void entropy_post(const FaceEig& e, LAM lamf, const PairCot& c, FaceEigBar& eb) {
-  const double ht = 0.5 * e.tau;
+__host__ __device__ __forceinline__ void entropy_post(const FaceEig& e, const double lam[7], const PairCot& c,
+                                                      EigCot& eb) {
+  const double ht = -2.0 * e.omg * e.qa2;
   const double f4 = c.fu;
-  eb.vn += f4 * lamf(1); eb.vt1 += f4 * lamf(2); eb.vt2 += f4 * lamf(3); eb.v2 += 0.5 * f4 * lamf(6);
+  eb.vn += f4 * lam[1] + ht * c.lS[1];
+  eb.vt1 += f4 * lam[2] + ht * c.lS[2];
+  eb.vt2 += f4 * lam[3] + ht * c.lS[3];
+  eb.Bt1 += ht * c.lS[4];
+  eb.Bt2 += ht * c.lS[5];
+  eb.add_v2(e, 0.5 * (f4 * lam[6] - ht * c.lS[0]));
   const double lht = -0.5 * e.v2 * c.lS[0] + e.vn * c.lS[1] + e.vt1 * c.lS[2] + e.vt2 * c.lS[3] +
                      e.Bt1 * c.lS[4] + e.Bt2 * c.lS[5] - c.lS[6];
-  eb.v2 -= 0.5 * ht * c.lS[0];
-  eb.vn += ht * c.lS[1]; eb.vt1 += ht * c.lS[2]; eb.vt2 += ht * c.lS[3]; eb.Bt1 += ht * c.lS[4];
-  eb.Bt2 += ht * c.lS[5];
-  eb.tau += 0.5 * lht;
+  eb.add_q(e, -2.0 * e.omg * lht);
 }
 
 using FastShape = PairShape<0, 4, true, 127>;
@@ -563,42 +524,92 @@ using SlowShape = PairShape<0, 4, true, 127>;
 using AlfvenShape = PairShape<4, 2, true, 13>;
 using EntropyShape = PairShape<0, 0, false, 127>;
 
+// New names for the eigen scalars that the pairs use: the compiler may not keep
+// products of them from one pair, or from a pair's rows, for the next.
+__host__ __device__ __forceinline__ void renew(FaceEig& e, double lam[7]) {
+  pin(e.vn); pin(e.vt1); pin(e.vt2); pin(e.Bt1); pin(e.Bt2); pin(e.by); pin(e.bz); pin(e.s); pin(e.af); pin(e.as);
+  pin(e.cf); pin(e.csl); pin(e.cs); pin(e.sr); pin(e.isr); pin(e.qa2);
+#pragma unroll
+  for (int j = 0; j < 7; ++j) pin(lam[j]);
+  e.v2 = e.vn * e.vn + e.vt1 * e.vt1 + e.vt2 * e.vt2;
+}
+
 // Reverse of face_corr (FP64) at one face: given the eigen scalars e, the
-// Lax-Friedrichs speeds alf(m), the differences dl and the cotangent lamf(j)
-// of corr, accumulates the cotangents of the eigen scalars (eb), of the LF
-// speeds (lal[7]) and, via emit (five rounds per group), of the interface
-// differences.  The face-state cotangents follow from face_eig_vjp(eb).  The
-// pairs run in two groups, fast with slow and Alfven with entropy.
-template <bool WZ, class ALF, class LAM, class DL, class EMIT>
-__host__ __device__ __forceinline__ void face_corr_vjp(const FaceEig& e, ALF alf, LAM lamf, DL dl, const Phys& ph,
-                                                       FaceEigBar& eb, double lal[7], EMIT emit) {
+// Lax-Friedrichs speeds alf(m), the differences (row, PITCH) and the cotangent lam
+// of corr, forms the cotangents of the eigen scalars (eb), of the LF speeds
+// (lal[7]) and, via emit (five calls per pair), of the interface differences.  The
+// face-state cotangents follow from face_eig_vjp(eb).  One pair at a time: two at
+// once share the reads of the differences but need twice the registers, and two
+// waves per SIMD are worth more than those reads.
+template <bool WZ, int PITCH, class ALF, class ROW, class EMIT>
+__host__ __device__ __forceinline__ void face_corr_vjp(FaceEig& e, ALF alf, double lam[7], ROW row,
+                                                       const Phys& ph, EigCot& eb, double lal[7], EMIT emit) {
+  const double eps = ph.eps, epsZ = ph.eps_Z;
+  const bool lit = ph.weno_z == 2;
+  eb.zero();
   {
-    PairRows rf, rs;
-    fast_rows(e, alf, lamf, rf);
-    slow_rows(e, alf, lamf, rs);
-    PairCot cf, cs;
-    pair2_rev<FastShape, true, SlowShape, true, WZ>(rf, rs, dl, ph.eps, ph.eps_Z, ph.weno_z == 2, cf, cs, emit);
-    fast_post(e, lamf, cf, eb);
-    slow_post(e, lamf, cs, eb);
-    lal[0] += cf.lalu; lal[6] += cf.lall; lal[2] += cs.lalu; lal[4] += cs.lall;
+    renew(e, lam);
+    PairRows r;
+    entropy_rows(e, alf, lam, r);
+    PairCot c;
+    PairGrad g;
+    pair_rev<EntropyShape, false, WZ, PITCH>(r, row, eps, epsZ, lit, c, g);
+    renew(e, lam);
+    entropy_post(e, lam, c, eb);
+    lal[3] = c.lalu;
+    eb.pin_all();
+    pin(lal[3]);
+    sched_fence();
+    pair_emit<EntropyShape, false>(r, g, emit);
   }
-  eb.pin_fast();
-  eb.pin_slow();
-  pin(lal[0]); pin(lal[6]); pin(lal[2]); pin(lal[4]);
   sched_fence();
   {
-    PairRows ra, rn;
-    alfven_rows(e, alf, lamf, ra);
-    entropy_rows(e, alf, lamf, rn);
-    PairCot ca, cn;
-    pair2_rev<AlfvenShape, true, EntropyShape, false, WZ>(ra, rn, dl, ph.eps, ph.eps_Z, ph.weno_z == 2, ca, cn, emit);
-    alfven_post(e, lamf, ca, eb);
-    entropy_post(e, lamf, cn, eb);
-    lal[1] += ca.lalu; lal[5] += ca.lall; lal[3] += cn.lalu;
+    renew(e, lam);
+    PairRows r;
+    alfven_rows(e, alf, lam, r);
+    PairCot c;
+    PairGrad g;
+    pair_rev<AlfvenShape, true, WZ, PITCH>(r, row, eps, epsZ, lit, c, g);
+    renew(e, lam);
+    alfven_post(e, lam, c, eb);
+    lal[1] = c.lalu; lal[5] = c.lall;
+    eb.pin_all();
+    pin(lal[1]); pin(lal[5]);
+    sched_fence();
+    pair_emit<AlfvenShape, true>(r, g, emit);
   }
-  eb.pin_alfven();
-  eb.pin_entropy();
-  pin(lal[1]); pin(lal[5]); pin(lal[3]);
+  sched_fence();
+  {
+    renew(e, lam);
+    PairRows r;
+    magneto_rows<false>(e, alf, lam, r);
+    PairCot c;
+    PairGrad g;
+    pair_rev<SlowShape, true, WZ, PITCH>(r, row, eps, epsZ, lit, c, g);
+    renew(e, lam);
+    magneto_post<false>(e, lam, c, eb);
+    lal[2] = c.lalu; lal[4] = c.lall;
+    eb.pin_all();
+    pin(lal[2]); pin(lal[4]);
+    sched_fence();
+    pair_emit<SlowShape, true>(r, g, emit);
+  }
+  sched_fence();
+  {
+    renew(e, lam);
+    PairRows r;
+    magneto_rows<true>(e, alf, lam, r);
+    PairCot c;
+    PairGrad g;
+    pair_rev<FastShape, true, WZ, PITCH>(r, row, eps, epsZ, lit, c, g);
+    renew(e, lam);
+    magneto_post<true>(e, lam, c, eb);
+    lal[0] = c.lalu; lal[6] = c.lall;
+    eb.pin_all();
+    pin(lal[0]); pin(lal[6]);
+    sched_fence();
+    pair_emit<FastShape, true>(r, g, emit);
+  }
 }
 
 // ---------------------------------------------------------------------------

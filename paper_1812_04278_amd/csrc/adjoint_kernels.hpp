@@ -89,163 +89,167 @@ struct AdjSweepArgs {
   const double* lam_T;   // [2][N] cotangent of this sweep's transport fluxes T^n_t1, T^n_t2
   double* lam_h;         // [5][N] += zone cotangents of rho, m_x, m_y, m_z, E
   double* lam_Bz;        // [3][N] += zone cotangents of the zone field B_x, B_y, B_z
+  SweepAxis ax;          // tile; ntile: the tiles of this launch
   int tile0;             // tile index along the axis of block 0 of this launch
   int tstride;           // tile index step between consecutive blocks along the axis
+  unsigned nblk, per_xcd;   // blocks of this launch, an eighth of them rounded up
+  double inv_nx;
 };
+
+// x += v in LDS by the LDS unit (no value returns to the lane)
+__device__ __forceinline__ void lds_add(double* x, double v) {
+  __hip_atomic_fetch_add(x, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 
 constexpr int ADJ_NP = 11;   // cotangents of zone primitives and speeds (P_* order)
-// One thread per face; one 256-face tile per CU (LDS), so one wave per SIMD
-// with up to 512 registers per thread.
+constexpr int ADJ_NR = ADJ_NP + 7;   // and of the flux components
 constexpr int ADJ_THREADS = 256;
-// adjoint tiles: TA faces along the sweep axis times TB across it, TA * TB = ADJ_THREADS
-template <int AXIS> struct AdjTile { static constexpr int TA = 16, TB = 16; };
-template <> struct AdjTile<0> { static constexpr int TA = 64, TB = 4; };
+// Zones and interfaces a tile may hold: 80 KB of LDS for the values, so that two
+// blocks of 256 faces share a CU (two waves per SIMD).
+constexpr int ADJ_ZONES = 280, ADJ_FACES = 276;
 
-template <int AXIS>
-struct AdjLds {
-  static constexpr int TA = AdjTile<AXIS>::TA, TB = AdjTile<AXIS>::TB;
-  static constexpr int NC = (TA + SW_HL + SW_HR) * TB, NIF = (TA + 4) * TB, NF = TA * TB;
-  static constexpr size_t bytes = sizeof(double) * (size_t)(SW_NQ * NC + SW_NP * NC + ADJ_NP * NC + SW_NQ * NIF + 7 * NF);
-};
-
-// One block: TA x TB faces of one plane.  Every zone that a face of the tile
-// touches (positions 0 .. tav+4 along the axis) gets its cotangent added to
-// lam_h / lam_Bz by exactly one thread of the block; positions that wrap onto the
-// same zone (a tile that spans the whole axis) are summed first.  Blocks of
-// one launch touch disjoint zones (the host launches the tiles of an axis in
-// conflict-free classes), so the additions need no atomics and the order of
-// accumulation is fixed.
+// One block: ta x tb faces of one axis, numbered like the forward sweep's.  Every
+// zone that a face of the tile touches (positions 0 .. tav+4 along the axis) gets
+// its cotangent added to lam_h / lam_Bz by exactly one thread of the block;
+// positions that wrap onto the same zone (a tile that spans the whole axis) are
+// summed first.  Blocks of one launch touch disjoint zones (the host launches the
+// tiles of an axis in conflict-free classes), so the additions need no atomics
+// and the order of accumulation is fixed.
+//
+// Bound by latency: dependent FP64 chains and LDS round trips between barriers.
+// One pair at a time and thirteen eigen cotangents instead of twenty-three bring a
+// lane under 256 registers, and the zone cotangents take the place of the zone
+// values and differences once those are spent, so that 80 KB of LDS hold a tile
+// and a second wave per SIMD fills the waits: at 128^3 an axis took 744-790 us with
+// one wave per SIMD (147 KB, 446 registers, two pairs at once) and takes 505-550
+// now, 53% of it VALU issue; at 48^3 73-78 and 37-39, where one tile spans the axis
+// and the two or three launches of its classes become one.
 template <int AXIS, bool WZ>
-__global__ __launch_bounds__(ADJ_THREADS, 1) void adj_sweep_kernel(AdjSweepArgs a) {
-  constexpr int TA = AdjTile<AXIS>::TA, TB = AdjTile<AXIS>::TB;
-  constexpr int NA = TA + SW_HL + SW_HR;
-  constexpr int NI = TA + 4;
-  constexpr int NC = NA * TB;
-  constexpr int NIF = NI * TB;
-  constexpr int NF = TA * TB;
-  // LDS: zone q/F (later the differences) | zone primitives and speeds | their
-  //      cotangents | interface-difference cotangents | face flux cotangents
-  __shared__ double Q[SW_NQ * NC];
-  __shared__ double Pz[SW_NP * NC];
-  __shared__ double PB[ADJ_NP * NC];
-  __shared__ double LD[SW_NQ * NIF];
-  __shared__ double LF[7 * NF];
+__global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs a) {
+  constexpr int NC = ADJ_ZONES, ND = ADJ_FACES;
+  // LDS: zone q/F, then the differences (14 rows) | zone primitives and speeds (8) |
+  //      interface-difference cotangents (14); the zone cotangents of the face
+  //      state, speeds and flux means (18 rows) over the first two at the end
+  __shared__ double lds[(SW_NQ + SW_NPF) * NC + SW_NQ * ND];
+  double* Q = lds;
+  double* Pz = lds + SW_NQ * NC;
+  double* LD = lds + (SW_NQ + SW_NPF) * NC;
+  double* PB = lds;
+  static_assert(ADJ_NR <= SW_NQ + SW_NPF && ND <= NC, "aliases fit");
   const Grid& g = a.g;
+  const SweepAxis& ax = a.ax;
   const int nA = AXIS == 0 ? g.nx : (AXIS == 1 ? g.ny : g.nz);
-  const int nB = AXIS == 0 ? g.ny : g.nx;
-  const int a0 = (a.tile0 + blockIdx.x * a.tstride) * TA;
-  const int b0 = blockIdx.y * TB;
-  const int c = blockIdx.z;
-  const int tav = min(TA, nA - a0);            // valid faces (and own zones) along the axis
+  const int TA = ax.ta, TB = ax.tb, NA = TA + SW_HL + SW_HR, NI = TA + 4;
+  const int ncell = NA * TB;
   constexpr int CN = AXIS, CT1 = (AXIS + 1) % 3, CT2 = (AXIS + 2) % 3;
-  auto cidx = [](int aa, int bb) { return AXIS == 0 ? bb * NA + aa : aa * TB + bb; };
-  auto iidx = [](int ia, int bb) { return AXIS == 0 ? bb * NI + ia : ia * TB + bb; };
-  auto fidx = [](int fa, int bb) { return AXIS == 0 ? bb * TA + fa : fa * TB + bb; };
-  auto gindex = [&](int aa_global, int bb_global) {
-    int i, j, k;
-    if (AXIS == 0)      { i = aa_global; j = bb_global; k = c; }
-    else if (AXIS == 1) { i = bb_global; j = aa_global; k = c; }
-    else                { i = bb_global; j = c;         k = aa_global; }
-    return g.at(i, j, k);
+  auto mul = [](int x, int y) { return (int)__umul24((unsigned)x, (unsigned)y); };
+  auto cidx = [&](int aa, int bb) { return AXIS == 0 ? mul(bb, NA) + aa : mul(aa, TB) + bb; };
+  auto iidx = [&](int ia, int bb) { return AXIS == 0 ? mul(bb, NI) + ia : mul(ia, TB) + bb; };
+  auto quot = [](int n, unsigned div) { return (int)(__umul24((unsigned)n, div) >> SW_DIV_SHIFT); };
+  auto split_cell = [&](int cell, int& aa, int& bb) {
+    if (AXIS == 0) { bb = quot(cell, ax.div_na); aa = cell - mul(bb, NA); }
+    else           { aa = quot(cell, ax.div_tb); bb = cell - mul(aa, TB); }
+  };
+  // Blocks go to the 8 XCDs in turn: each XCD takes a run of neighbouring column
+  // groups, whose lines of memory its L2 then fetches once (a group of 4 columns
+  // uses 32 of a line's 128 bytes).
+  const unsigned blk = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
+  if (blk >= a.nblk) return;
+  const unsigned grp = (unsigned)__builtin_amdgcn_readfirstlane((int)quot_by(blk, ax.inv_ntile));
+  const int a0 = (a.tile0 + (int)(blk - grp * (unsigned)ax.ntile) * a.tstride) * TA;
+  const int b0 = (int)grp * TB;
+  const int tav = min(TA, nA - a0);            // valid faces (and own zones) along the axis
+  const unsigned plane = (unsigned)g.nx * (unsigned)g.ny;
+  auto zone_at = [&](int q, int ia) -> size_t {
+    if (AXIS == 0) return (unsigned)q * (unsigned)g.nx + (unsigned)ia;
+    if (AXIS == 2) return (unsigned)q + (unsigned)ia * plane;
+    const unsigned z = quot_by((unsigned)q, a.inv_nx);
+    return (unsigned)q + z * (plane - (unsigned)g.nx) + (unsigned)mul(ia, g.nx);
+  };
+  // sweep frame: rho, m_n, m_t1, m_t2, E, B_n, B_t1, B_t2
+  auto load_zone = [&](size_t gi, double u[8]) {
+    u[0] = a.hydro[gi];
+    u[1] = a.hydro[(1 + CN) * g.N + gi];
+    u[2] = a.hydro[(1 + CT1) * g.N + gi];
+    u[3] = a.hydro[(1 + CT2) * g.N + gi];
+    u[4] = a.hydro[4 * g.N + gi];
+    u[5] = a.bcell[CN * g.N + gi];
+    u[6] = a.bcell[CT1 * g.N + gi];
+    u[7] = a.bcell[CT2 * g.N + gi];
   };
 
-  const int tid = threadIdx.x;                   // face of this thread
-  // ---- (0) global loads first: the states of this thread's cells (the same
-  //          cells it handles in (4), kept in registers) and the right-hand-side
-  //          cotangents of its face, so that the latencies overlap
+  // ---- (0) the face of this thread and its incoming cotangents: flux divergence
+  // transposed, lam_F_v(face i+1/2) = (lam_k_v(i+1) - lam_k_v(i))/h, in the sweep
+  // frame; the B_t components carry the transport-flux cotangents.  Threads past
+  // the tile's faces repeat face 0 and add nothing.
+  const bool active = (int)threadIdx.x < TA * TB;
   int fa, fb;
-  if (AXIS == 0) { fa = tid % TA; fb = tid / TA; }
-  else           { fb = tid % TB; fa = tid / TB; }
-  const bool valid = fa < tav && b0 + fb < nB;
-  constexpr int NCELL = (NC + ADJ_THREADS - 1) / ADJ_THREADS;
-  double uz[NCELL][8];   // sweep frame: rho, m_n, m_t1, m_t2, E, B_n, B_t1, B_t2
-#pragma unroll
-  for (int k = 0; k < NCELL; ++k) {
-    const int cell = min(threadIdx.x + k * ADJ_THREADS, (unsigned)NC - 1);
-    int aa, bb;
-    if (AXIS == 0) { aa = cell % NA; bb = cell / NA; }
-    else           { bb = cell % TB; aa = cell / TB; }
-    const size_t gi = gindex(wrap(a0 - SW_HL + aa, nA), min(b0 + bb, nB - 1));
-    const double m[3] = {a.hydro[g.N + gi], a.hydro[2 * g.N + gi], a.hydro[3 * g.N + gi]};
-    const double B[3] = {a.bcell[gi], a.bcell[g.N + gi], a.bcell[2 * g.N + gi]};
-    double* u = uz[k];
-    u[0] = a.hydro[gi]; u[1] = m[CN]; u[2] = m[CT1]; u[3] = m[CT2]; u[4] = a.hydro[4 * g.N + gi];
-    u[5] = B[CN]; u[6] = B[CT1]; u[7] = B[CT2];
-  }
-  double lk0[5], lk1[5], lT[2];
   {
-    const int ia = wrap(a0 + fa, nA), ia1 = wrap(a0 + fa + 1, nA);
-    const int ib = min(b0 + fb, nB - 1);
-    const size_t g0 = gindex(ia, ib), g1 = gindex(ia1, ib);
+    const int t = active ? threadIdx.x : 0;
+    if (AXIS == 0) { fb = quot(t, ax.div_ta); fa = t - mul(fb, TA); }
+    else           { fa = quot(t, ax.div_tb); fb = t - mul(fa, TB); }
+  }
+  double lam[7];
+  {
+    const int q = min(b0 + fb, ax.ncol - 1);
+    const size_t g0 = zone_at(q, wrap_near(a0 + fa, nA)), g1 = zone_at(q, wrap_near(a0 + fa + 1, nA));
+    double lg[5];
 #pragma unroll
-    for (int v = 0; v < 5; ++v) { lk0[v] = a.lam_k[v * g.N + g0]; lk1[v] = a.lam_k[v * g.N + g1]; }
-    lT[0] = a.lam_T[g0];
-    lT[1] = a.lam_T[g.N + g0];
+    for (int v = 0; v < 5; ++v) lg[v] = (a.lam_k[v * g.N + g1] - a.lam_k[v * g.N + g0]) * a.inv_h;
+    const double msk = active && fa < tav && b0 + fb < ax.ncol ? 1.0 : 0.0;
+    lam[0] = msk * lg[0];
+    lam[1] = msk * lg[1 + CN];
+    lam[2] = msk * lg[1 + CT1];
+    lam[3] = msk * lg[1 + CT2];
+    lam[4] = msk * a.lam_T[g0];
+    lam[5] = msk * a.lam_T[g.N + g0];
+    lam[6] = msk * lg[4];
   }
 
   // ---- (1) forward zone prologue into LDS
-#pragma unroll
-  for (int k = 0; k < NCELL; ++k) {   // branch-free: surplus threads repeat the last cell (equal values)
-    const int cell = min(threadIdx.x + k * ADJ_THREADS, (unsigned)NC - 1);
-    const double* u = uz[k];
-    double z[Z_NVAR];
+  for (int cell = threadIdx.x; cell < ncell; cell += ADJ_THREADS) {
+    int aa, bb;
+    split_cell(cell, aa, bb);
+    double u[8], z[Z_NVAR];
+    load_zone(zone_at(min(b0 + bb, ax.ncol - 1), wrap_near(a0 - SW_HL + aa, nA)), u);
     zone_prologue(u[0], u[1], u[2], u[3], u[4], u[5], u[6], u[7], a.ph.gamma, z);
 #pragma unroll
     for (int v = 0; v < SW_NQ; ++v) Q[v * NC + cell] = z[v];
-    const int pv[SW_NP] = {Z_RHO, Z_VN, Z_VT1, Z_VT2, Z_BN, Z_BT1, Z_BT2, Z_P, Z_CF, Z_CA, Z_CS};
+    const int pv[SW_NPF] = {Z_VN, Z_VT1, Z_VT2, Z_BN, Z_P, Z_CF, Z_CA, Z_CS};
 #pragma unroll
-    for (int v = 0; v < SW_NP; ++v) Pz[v * NC + cell] = z[pv[v]];
+    for (int v = 0; v < SW_NPF; ++v) Pz[v * NC + cell] = z[pv[v]];
   }
   __syncthreads();
 
-  // ---- (2) per face: own interface differences, incoming flux cotangents
+  // ---- (2) the difference of the face's own interface and of the four of a
+  // column beyond its faces' own (lanes fa < 4), as in the forward sweep
   const int cL = cidx(fa + 2, fb), cR = cidx(fa + 3, fb);
+  double f_rho, f_bt1, f_bt2;
   {
-    // zone variables: q in Q rows 0..6, F in rows 7..13; differences: Delta F
-    // in rows 0..6, Delta q in rows 7..13
-    constexpr int NV = SW_NQ;
-    auto src_row = [](int v) { return v < 7 ? v + 7 : v - 7; };
-    auto dst_row = [](int v) { return v; };
-    double d0[NV], d1[NV];
-    {
-      const int c0 = cidx(fa, fb), c1 = cidx(fa + 1, fb);
+    double d0[SW_NQ], d1[SW_NQ], f_q[7];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) d0[v] = Q[src_row(v) * NC + c1] - Q[src_row(v) * NC + c0];
-      if (fa < 4) {
-        const int c2 = cidx(TA + fa, fb), c3 = cidx(TA + fa + 1, fb);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) d1[v] = Q[src_row(v) * NC + c3] - Q[src_row(v) * NC + c2];
-      }
+    for (int v = 0; v < SW_NQ; ++v) {
+      const double L = Q[v * NC + cL], R = Q[v * NC + cR];
+      d0[v] = R - L;
+      if (v < 7) f_q[v] = 0.5 * (L + R);
     }
-    // incoming cotangents: flux divergence transposed, lam_F_v(face i+1/2) = (lam_k_v(i+1) - lam_k_v(i))/h,
-    // in the sweep frame; the B_t components carry the transport-flux cotangents
-    double lam[7];
-    {
-      double lg[5];
+    f_rho = f_q[Z_RHO]; f_bt1 = f_q[Z_BT1]; f_bt2 = f_q[Z_BT2];
+    const int ie = fa < 2 ? fa : TA + fa;
+    if (fa < 4) {
+      const int c2 = cidx(ie, fb), c3 = cidx(ie + 1, fb);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) lg[v] = (lk1[v] - lk0[v]) * a.inv_h;
-      const double lm[3] = {lg[1], lg[2], lg[3]};
-      const double msk = valid ? 1.0 : 0.0;
-      lam[0] = msk * lg[0];
-      lam[1] = msk * lm[CN];
-      lam[2] = msk * lm[CT1];
-      lam[3] = msk * lm[CT2];
-      lam[4] = msk * lT[0];
-      lam[5] = msk * lT[1];
-      lam[6] = msk * lg[4];
+      for (int v = 0; v < SW_NQ; ++v) d1[v] = Q[v * NC + c3] - Q[v * NC + c2];
     }
     __syncthreads();
+    // stored as (Delta F, Delta q): rows 0..6 flux, 7..13 state
 #pragma unroll
-    for (int v = 0; v < NV; ++v) Q[dst_row(v) * NIF + iidx(fa, fb)] = d0[v];
+    for (int v = 0; v < SW_NQ; ++v) Q[(v < 7 ? v + 7 : v - 7) * ND + iidx(fa + 2, fb)] = d0[v];
     if (fa < 4) {
 #pragma unroll
-      for (int v = 0; v < NV; ++v) Q[dst_row(v) * NIF + iidx(TA + fa, fb)] = d1[v];
+      for (int v = 0; v < SW_NQ; ++v) Q[(v < 7 ? v + 7 : v - 7) * ND + iidx(ie, fb)] = d1[v];
     }
-#pragma unroll
-    for (int v = 0; v < 7; ++v) LF[v * NF + fidx(fa, fb)] = lam[v];
   }
-  for (int t = threadIdx.x; t < SW_NQ * NIF; t += ADJ_THREADS) LD[t] = 0.0;
-  for (int t = threadIdx.x; t < ADJ_NP * NC; t += ADJ_THREADS) PB[t] = 0.0;
+  for (int t = threadIdx.x; t < SW_NQ * ND; t += ADJ_THREADS) LD[t] = 0.0;
   __syncthreads();
 
   // ---- (3) per-face reverse; interface cotangents in barrier-separated sub-rounds
@@ -254,131 +258,133 @@ __global__ __launch_bounds__(ADJ_THREADS, 1) void adj_sweep_kernel(AdjSweepArgs 
   auto sgm = [](int m) { return m < 3 ? -1 : (m == 3 ? 0 : 1); };
   auto spi = [](int m) { return (m == 0 || m == 6) ? 0 : ((m == 1 || m == 5) ? 1 : 2); };
   auto xarg = [&](int m, int cz) {
-    const double v = Pz[P_VN * NC + cz];
-    return sgm(m) == 0 ? v : v + sgm(m) * Pz[(P_CF + spi(m)) * NC + cz];
+    const double v = Pz[FP_VN * NC + cz];
+    return sgm(m) == 0 ? v : v + sgm(m) * Pz[(FP_CF + spi(m)) * NC + cz];
   };
   auto alf = [&](int m) { return fmax(fabs(xarg(m, cL)), fabs(xarg(m, cR))); };
-  auto lamf = [&](int j) { return LF[j * NF + fidx(fa, fb)]; };
-  auto dl = [&](int j, int k) -> double { return Q[j * NIF + iidx(fa + k, fb)]; };
-  // round k: every face adds its cotangent of interface difference fa + k
+  auto mean = [&](int v) { return 0.5 * (Pz[v * NC + cL] + Pz[v * NC + cR]); };
+  const double* dl0 = Q + iidx(fa, fb);
+  double* ld0 = LD + iidx(fa, fb);
+  const int dstep = AXIS == 0 ? 1 : TB;
+  auto row = [&](int k) -> const double* { return dl0 + k * dstep; };
+  // round k: every face adds its cotangent of interface difference fa + k (a
+  // barrier before each fixes the order of the additions to an interface)
   auto emit = [&](int k, const double* v) {
     __syncthreads();
+    if (active) {
+      double* l = ld0 + k * dstep;
 #pragma unroll
-    for (int j = 0; j < SW_NQ; ++j) LD[j * NIF + iidx(fa + k, fb)] += v[j];
+      for (int j = 0; j < SW_NQ; ++j) lds_add(l + j * ND, v[j]);
+    }
   };
-  double lal[7] = {0, 0, 0, 0, 0, 0, 0};
-  double lfp[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  {
-    // eigen scalars of the face state (the mean of the two zones' primitives)
-    auto eig = [&]() {
-      double fp[8];
-#pragma unroll
-      for (int v = 0; v < 8; ++v) fp[v] = 0.5 * (Pz[v * NC + cL] + Pz[v * NC + cR]);
-      FaceEig e;
-      face_eig(fp[0], fp[1], fp[2], fp[3], fp[4], fp[5], fp[6], fp[7], a.ph, e);
-      return e;
-    };
-    const FaceEig e = eig();
-    FaceEigBar eb;
-    eb.zero();
-    face_corr_vjp<WZ>(e, alf, lamf, dl, a.ph, eb, lal, emit);
-    double fp[8];
-#pragma unroll
-    for (int v = 0; v < 8; ++v) fp[v] = 0.5 * (Pz[v * NC + cL] + Pz[v * NC + cR]);
-    face_eig_vjp(fp, a.ph, e, eb, lfp);
-  }
-  // zone-primitive cotangents of zones L (i) and R (i+1): face-state means,
-  // LF speeds (branch of the larger argument; ties -> L) and transport-flux means
   double pl[ADJ_NP], pr[ADJ_NP];
+  {
+    const double fp[8] = {f_rho, mean(FP_VN), mean(FP_VT1), mean(FP_VT2), mean(FP_BN), f_bt1, f_bt2, mean(FP_P)};
+    FaceEig e;
+    face_eig(fp[0], fp[1], fp[2], fp[3], fp[4], fp[5], fp[6], fp[7], a.ph, e);
+    EigCot eb;
+    double lal[7], lfp[8];
+    face_corr_vjp<WZ, ND>(e, alf, lam, row, a.ph, eb, lal, emit);
+    {
+      pin(f_rho); pin(f_bt1); pin(f_bt2);   // nothing of face_eig is held for its reverse
+      const double fq[8] = {f_rho, mean(FP_VN), mean(FP_VT1), mean(FP_VT2), mean(FP_BN), f_bt1, f_bt2, mean(FP_P)};
+      face_eig_vjp(fq, a.ph, e, eb, lfp);
+    }
+    // zone-primitive cotangents of zones L (i) and R (i+1): face-state means,
+    // LF speeds (branch of the larger argument; ties -> L) and transport-flux means
 #pragma unroll
-  for (int v = 0; v < ADJ_NP; ++v) { pl[v] = v < 8 ? 0.5 * lfp[v] : 0.0; pr[v] = pl[v]; }
+    for (int v = 0; v < ADJ_NP; ++v) { pl[v] = v < 8 ? 0.5 * lfp[v] : 0.0; pr[v] = pl[v]; }
 #pragma unroll
-  for (int m = 0; m < 7; ++m) {
-    const double xl = xarg(m, cL), xr = xarg(m, cR);
-    const bool left = fabs(xl) >= fabs(xr);
-    const double x = left ? xl : xr;
-    const double sx = x > 0.0 ? 1.0 : (x < 0.0 ? -1.0 : 0.0);
-    // to the zone of the larger argument (weights instead of a pointer select,
-    // which would move pl, pr to scratch memory)
-    const double gl = left ? lal[m] * sx : 0.0, gr = left ? 0.0 : lal[m] * sx;
-    pl[P_VN] += gl;
-    pr[P_VN] += gr;
-    if (sgm(m) != 0) {
-      pl[P_CF + spi(m)] += gl * sgm(m);
-      pr[P_CF + spi(m)] += gr * sgm(m);
+    for (int m = 0; m < 7; ++m) {
+      const double xl = xarg(m, cL), xr = xarg(m, cR);
+      const bool left = fabs(xl) >= fabs(xr);
+      const double x = left ? xl : xr;
+      const double sx = x > 0.0 ? 1.0 : (x < 0.0 ? -1.0 : 0.0);
+      // to the zone of the larger argument (weights instead of a pointer select,
+      // which would move pl, pr to scratch memory)
+      const double gl = left ? lal[m] * sx : 0.0, gr = left ? 0.0 : lal[m] * sx;
+      pl[P_VN] += gl;
+      pr[P_VN] += gr;
+      if (sgm(m) != 0) {
+        pl[P_CF + spi(m)] += gl * sgm(m);
+        pr[P_CF + spi(m)] += gr * sgm(m);
+      }
+    }
+    const double BnL = Pz[FP_BN * NC + cL], BnR = Pz[FP_BN * NC + cR];
+    pl[P_BN] += 0.5 * (lam[4] * Pz[FP_VT1 * NC + cL] + lam[5] * Pz[FP_VT2 * NC + cL]);
+    pr[P_BN] += 0.5 * (lam[4] * Pz[FP_VT1 * NC + cR] + lam[5] * Pz[FP_VT2 * NC + cR]);
+    pl[P_VT1] += 0.5 * lam[4] * BnL; pr[P_VT1] += 0.5 * lam[4] * BnR;
+    pl[P_VT2] += 0.5 * lam[5] * BnL; pr[P_VT2] += 0.5 * lam[5] * BnR;
+  }
+  // zone sums, over the spent zone values: zone L's part is stored (position fa + 2
+  // of face fa; the five positions that are no face's zone L are cleared), then
+  // zone R's added.  The central term F_c = (F_L + F_R)/2 + (Delta F_{i-1/2} - Delta F_{i+3/2})/12
+  // gives half of lam to both zones and +- lam/12 to the differences of
+  // interfaces fa + 1 and fa + 3.
+  __syncthreads();
+  if (active) {
+#pragma unroll
+    for (int j = 0; j < 7; ++j) ld0[j * ND + dstep] += (1.0 / 12.0) * lam[j];
+  }
+  __syncthreads();
+  if (active) {
+#pragma unroll
+    for (int j = 0; j < 7; ++j) ld0[j * ND + 3 * dstep] -= (1.0 / 12.0) * lam[j];
+#pragma unroll
+    for (int v = 0; v < ADJ_NP; ++v) PB[v * NC + cL] = pl[v];
+#pragma unroll
+    for (int j = 0; j < 7; ++j) PB[(ADJ_NP + j) * NC + cL] = 0.5 * lam[j];
+    if (fa < 5) {
+      const int cz = cidx(fa < 2 ? fa : TA + fa, fb);
+#pragma unroll
+      for (int v = 0; v < ADJ_NR; ++v) PB[v * NC + cz] = 0.0;
     }
   }
-  {
-    const double ltc1 = lamf(4), ltc2 = lamf(5);
-    const double BnL = Pz[P_BN * NC + cL], BnR = Pz[P_BN * NC + cR];
-    pl[P_BN] += 0.5 * (ltc1 * Pz[P_VT1 * NC + cL] + ltc2 * Pz[P_VT2 * NC + cL]);
-    pr[P_BN] += 0.5 * (ltc1 * Pz[P_VT1 * NC + cR] + ltc2 * Pz[P_VT2 * NC + cR]);
-    pl[P_VT1] += 0.5 * ltc1 * BnL; pr[P_VT1] += 0.5 * ltc1 * BnR;
-    pl[P_VT2] += 0.5 * ltc2 * BnL; pr[P_VT2] += 0.5 * ltc2 * BnR;
-  }
-  // cotangent sums of this thread's cells in (4), loaded ahead of the sub-rounds
-  const int span = tav + SW_HL + SW_HR;          // positions touched by the valid faces
-  const int nz_own = min(span, nA);              // distinct zones among them
-  double lm[NCELL][8];
-  size_t gcell[NCELL];
-  bool own[NCELL];
-#pragma unroll
-  for (int k = 0; k < NCELL; ++k) {
-    const int cell = threadIdx.x + k * ADJ_THREADS;
-    int aa, bb;
-    if (AXIS == 0) { aa = cell % NA; bb = cell / NA; }
-    else           { bb = cell % TB; aa = cell / TB; }
-    own[k] = cell < NC && aa < nz_own && b0 + bb < nB;
-    gcell[k] = own[k] ? gindex(wrap(a0 - SW_HL + aa, nA), b0 + bb) : 0;
-#pragma unroll
-    for (int v = 0; v < 8; ++v) lm[k][v] = own[k] ? (v < 5 ? a.lam_h : a.lam_Bz - 5 * g.N)[v * g.N + gcell[k]] : 0.0;
-  }
-  // two sub-rounds: zone L, then zone R
   __syncthreads();
+  if (active) {
 #pragma unroll
-  for (int v = 0; v < ADJ_NP; ++v) PB[v * NC + cL] += pl[v];
-  __syncthreads();
+    for (int v = 0; v < ADJ_NP; ++v) PB[v * NC + cR] += pr[v];
 #pragma unroll
-  for (int v = 0; v < ADJ_NP; ++v) PB[v * NC + cR] += pr[v];
+    for (int j = 0; j < 7; ++j) PB[(ADJ_NP + j) * NC + cR] += 0.5 * lam[j];
+  }
   __syncthreads();
 
   // ---- (4) per zone: gather, prologue reverse, add
+  const int span = tav + SW_HL + SW_HR;          // positions touched by the valid faces
+  const int nz_own = min(span, nA);              // distinct zones among them
   // cotangents of the prologue outputs at tile position aa (lz += ...)
   auto gather = [&](int aa, int bb, double* lz) {
+    const int ii = iidx(aa, bb), cz = cidx(aa, bb);
+    // interface differences: D(ia) = X(ia+1) - X(ia)
+    if (aa >= 1) {
 #pragma unroll
-    for (int j = 0; j < 7; ++j) {
-      double lFj = 0.0, lqj = 0.0;
-      // interface differences: D(ia) = X(ia+1) - X(ia)
-      if (aa >= 1) { lFj += LD[j * NIF + iidx(aa - 1, bb)]; lqj += LD[(7 + j) * NIF + iidx(aa - 1, bb)]; }
-      if (aa < NI) { lFj -= LD[j * NIF + iidx(aa, bb)]; lqj -= LD[(7 + j) * NIF + iidx(aa, bb)]; }
-      // central term: face f (local) uses zones f+1 (-1/12), f+2 (7/12), f+3 (7/12), f+4 (-1/12)
-      const int f1 = aa - 1, f2 = aa - 2, f3 = aa - 3, f4 = aa - 4;
-      if (f1 >= 0 && f1 < TA) lFj -= LF[j * NF + fidx(f1, bb)] * (1.0 / 12.0);
-      if (f2 >= 0 && f2 < TA) lFj += LF[j * NF + fidx(f2, bb)] * (7.0 / 12.0);
-      if (f3 >= 0 && f3 < TA) lFj += LF[j * NF + fidx(f3, bb)] * (7.0 / 12.0);
-      if (f4 >= 0 && f4 < TA) lFj -= LF[j * NF + fidx(f4, bb)] * (1.0 / 12.0);
-      lz[Z_F0 + j] += lFj;
-      lz[Z_RHO + j] += lqj;
+      for (int j = 0; j < 7; ++j) {
+        lz[Z_F0 + j] += LD[j * ND + ii - dstep];
+        lz[Z_RHO + j] += LD[(7 + j) * ND + ii - dstep];
+      }
     }
-    const int cz = cidx(aa, bb);
-    lz[Z_RHO] += PB[P_RHO * NC + cz];
-    lz[Z_VN] += PB[P_VN * NC + cz];
-    lz[Z_VT1] += PB[P_VT1 * NC + cz];
-    lz[Z_VT2] += PB[P_VT2 * NC + cz];
-    lz[Z_BN] += PB[P_BN * NC + cz];
-    lz[Z_BT1] += PB[P_BT1 * NC + cz];
-    lz[Z_BT2] += PB[P_BT2 * NC + cz];
-    lz[Z_P] += PB[P_P * NC + cz];
-    lz[Z_CF] += PB[P_CF * NC + cz];
-    lz[Z_CA] += PB[P_CA * NC + cz];
-    lz[Z_CS] += PB[P_CS * NC + cz];
-  };
+    if (aa < NI) {
 #pragma unroll
-  for (int k = 0; k < NCELL; ++k) {   // branch-free over the cells (the stores are predicated)
-    const int cell = min(threadIdx.x + k * ADJ_THREADS, (unsigned)NC - 1);
+      for (int j = 0; j < 7; ++j) {
+        lz[Z_F0 + j] -= LD[j * ND + ii];
+        lz[Z_RHO + j] -= LD[(7 + j) * ND + ii];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 7; ++j) lz[Z_F0 + j] += PB[(ADJ_NP + j) * NC + cz];
+    const int zv[ADJ_NP] = {Z_RHO, Z_VN, Z_VT1, Z_VT2, Z_BN, Z_BT1, Z_BT2, Z_P, Z_CF, Z_CA, Z_CS};
+#pragma unroll
+    for (int v = 0; v < ADJ_NP; ++v) lz[zv[v]] += PB[v * NC + cz];
+  };
+  for (int cell = threadIdx.x; cell < ncell; cell += ADJ_THREADS) {
     int aa, bb;
-    if (AXIS == 0) { aa = cell % NA; bb = cell / NA; }
-    else           { bb = cell % TB; aa = cell / TB; }
+    split_cell(cell, aa, bb);
+    if (aa >= nz_own || b0 + bb >= ax.ncol) continue;
+    const size_t gi = zone_at(b0 + bb, wrap_near(a0 - SW_HL + aa, nA));
+    double u[8], lm[8];
+    load_zone(gi, u);
+#pragma unroll
+    for (int v = 0; v < 8; ++v) lm[v] = (v < 5 ? a.lam_h : a.lam_Bz - 5 * g.N)[v * g.N + gi];
     double lz[Z_NVAR];
 #pragma unroll
     for (int v = 0; v < Z_NVAR; ++v) lz[v] = 0.0;
@@ -386,16 +392,14 @@ __global__ __launch_bounds__(ADJ_THREADS, 1) void adj_sweep_kernel(AdjSweepArgs 
     if (span > nA)   // a tile that wraps onto itself: other positions of the same zone
       for (int q = aa + nA; q < span; q += nA) gather(q, bb, lz);
     double lu[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    zone_prologue_vjp(uz[k], a.ph.gamma, lz, lu);
+    zone_prologue_vjp(u, a.ph.gamma, lz, lu);
     double out[8];
     out[0] = lu[0];
     out[1 + CN] = lu[1]; out[1 + CT1] = lu[2]; out[1 + CT2] = lu[3];
     out[4] = lu[4];
     out[5 + CN] = lu[5]; out[5 + CT1] = lu[6]; out[5 + CT2] = lu[7];
-    if (own[k]) {
 #pragma unroll
-      for (int v = 0; v < 8; ++v) (v < 5 ? a.lam_h : a.lam_Bz - 5 * g.N)[v * g.N + gcell[k]] = lm[k][v] + out[v];
-    }
+    for (int v = 0; v < 8; ++v) (v < 5 ? a.lam_h : a.lam_Bz - 5 * g.N)[v * g.N + gi] = lm[v] + out[v];
   }
 }
 

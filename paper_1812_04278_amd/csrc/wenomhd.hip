@@ -145,7 +145,7 @@ enum AdjOff { A_U1 = 0, A_U2 = 11, A_BZ = 22, A_LT = 25, A_LBZ = 31, A_LK = 34, 
 // sides).  Classes: even tiles, odd tiles, and the tile left over (nt odd:
 // the last; nt even with a short last tile: tile nt-2).
 struct TileRun { int first, stride, count; };
-struct TilePlan { TileRun run[4]; int n; };
+struct TilePlan { TileRun run[4]; int n; SweepAxis ax; };
 
 bool plan_disjoint(int n, int TA, const TilePlan& pl) {
   std::vector<int> stamp(n, -1);
@@ -333,6 +333,47 @@ SweepAxis choose_tile(int n, int ncol, int max_zones, bool xacross, size_t es) {
   return best;
 }
 
+void set_divisors(SweepAxis& x, int ncol) {
+  const unsigned one = 1u << SW_DIV_SHIFT;
+  x.div_ta = (one + x.ta - 1) / x.ta;
+  x.div_na = (one + x.ta + 4) / (x.ta + 5);
+  x.div_tb = (one + x.tb - 1) / x.tb;
+  x.ncol = ncol;
+}
+
+// Tile and launch classes of the adjoint sweep of an axis of n zones: the least
+// time by the rounds of blocks (two per CU) that its classes take, a short launch
+// counting a fifth of a round.  A tile that spans the axis needs one class.  Across
+// the y and z axes short rows are weighed down a little: an XCD fetches a line once
+// for its neighbouring blocks, so 2 and 4 columns ran alike (5.25 and 5.27 ms per
+// 128^3 step adjoint; blocks dealt to the XCDs in turn, 5.79 and, 2 columns, 6.76).
+TilePlan adjoint_plan(int n, int ncol, bool xacross) {
+  TilePlan best{};
+  double best_cost = 0.0;
+  for (int nt = 1; nt <= n; ++nt) {
+    const int ta = std::max(5, (n + nt - 1) / nt);
+    if (nt > 1 && ta < 12) break;
+    if (ta > ADJ_THREADS || ta + 5 > ADJ_ZONES || ta + 4 > ADJ_FACES) continue;
+    int tb = std::min(std::min(ADJ_THREADS / ta, ADJ_ZONES / (ta + 5)), ncol);
+    while (tb > 1 && (ta + 4) * tb > ADJ_FACES) --tb;
+    TilePlan pl = plan_tiles(n, ta);
+    double cost = 0.0;
+    for (int c = 0; c < pl.n; ++c) {
+      const double rounds = (double)pl.run[c].count * ((ncol + tb - 1) / tb) / 512.0;
+      cost += (rounds < 4.0 ? std::ceil(rounds) : rounds + 0.5) + 0.2;
+    }
+    cost *= !xacross || tb >= 8 ? 1.0 : (tb >= 4 ? 1.02 : 1.06);
+    if (best.n == 0 || cost < best_cost) {
+      best = pl;
+      best.ax.ta = ta;
+      best.ax.tb = tb;
+      best_cost = cost;
+    }
+  }
+  set_divisors(best.ax, ncol);
+  return best;
+}
+
 // The launch of the axes in `mask` (bit d: axis d).
 SweepPlan sweep_plan(const wm_patch* p, int mask) {
   const Grid& g = p->g;
@@ -345,11 +386,7 @@ SweepPlan sweep_plan(const wm_patch* p, int mask) {
     const int n = n3[d] + g.wall[d], ncol = (int)(g.N / n3[d]);
     SweepAxis& x = pl.ax[d];
     x = choose_tile(n, ncol, zones, d != 0, es);
-    const unsigned one = 1u << SW_DIV_SHIFT;
-    x.div_ta = (one + x.ta - 1) / x.ta;
-    x.div_na = (one + x.ta + 4) / (x.ta + 5);
-    x.div_tb = (one + x.tb - 1) / x.tb;
-    x.ncol = ncol;
+    set_divisors(x, ncol);
     x.ntile = (n + x.ta - 1) / x.ta;
     x.inv_ntile = 1.0 / x.ntile;
     x.blk0 = blk;
@@ -532,15 +569,18 @@ wm_status launch_adj_sweep(wm_patch* p, const double* hydro, const double* bcell
   a.lam_T = lam_T;
   a.lam_h = acc_h;
   a.lam_Bz = lam_Bz;
-  const int nB = AXIS == 0 ? p->g.ny : p->g.nx;
-  const int nC = AXIS == 2 ? p->g.ny : p->g.nz;
-  constexpr int TB = AdjTile<AXIS>::TB;
   const TilePlan& pl = p->adj_plan[AXIS];
+  a.ax = pl.ax;
+  a.inv_nx = 1.0 / p->g.nx;
   const long r = prof_begin(p, K_OTHER);
   for (int c = 0; c < pl.n; ++c) {   // classes in order: each launch adds into disjoint zones
     a.tile0 = pl.run[c].first;
     a.tstride = pl.run[c].stride;
-    const dim3 grid(pl.run[c].count, (nB + TB - 1) / TB, nC);
+    a.ax.ntile = pl.run[c].count;
+    a.ax.inv_ntile = 1.0 / a.ax.ntile;
+    a.nblk = (unsigned)a.ax.ntile * (unsigned)((a.ax.ncol + a.ax.tb - 1) / a.ax.tb);
+    a.per_xcd = (a.nblk + 7) / 8;
+    const dim3 grid(8 * a.per_xcd);
     if (p->ph.weno_z) hipLaunchKernelGGL((adj_sweep_kernel<AXIS, true>), grid, dim3(ADJ_THREADS), 0, p->stream, a);
     else hipLaunchKernelGGL((adj_sweep_kernel<AXIS, false>), grid, dim3(ADJ_THREADS), 0, p->stream, a);
     WM_LAUNCH_CHECK("adjoint sweep kernel");
@@ -738,10 +778,9 @@ wm_status wm_patch_create(const wm_config* cfg, void* hip_stream, void* scratch_
   setup_patch(p, cfg, hip_stream, scratch_buf, L);
   if (cfg->nx >= 3 && cfg->ny >= 3 && cfg->nz >= 3) {
     const int n3[3] = {cfg->nx, cfg->ny, cfg->nz};
-    const int ta[3] = {AdjTile<0>::TA, AdjTile<1>::TA, AdjTile<2>::TA};
     for (int d = 0; d < 3; ++d) {
-      p->adj_plan[d] = plan_tiles(n3[d], ta[d]);
-      if (!plan_disjoint(n3[d], ta[d], p->adj_plan[d])) {
+      p->adj_plan[d] = adjoint_plan(n3[d], (int)(p->g.N / n3[d]), d != 0);
+      if (!plan_disjoint(n3[d], p->adj_plan[d].ax.ta, p->adj_plan[d])) {
         delete p;
         return fail(WM_ERR_ARG, "internal: adjoint tile classes overlap");
       }
