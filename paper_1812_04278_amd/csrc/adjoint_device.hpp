@@ -9,6 +9,8 @@
 // (beta, sgn(B_n), alpha_f = alpha_s = 1/sqrt2) have zero derivative, and
 // sqrt(0) contributes nothing.
 #pragma once
+#include <type_traits>
+
 #include "mhd_device.hpp"
 
 namespace wm {
@@ -17,9 +19,6 @@ namespace wm {
 // phi_N: value and gradient with respect to its four arguments (Sect. 2.2).
 // With omega = alpha/sum, g = X/3, h = Y/6 (X = a-2b+c, Y = b-2c+d) and
 // W = g omega_0 + h omega_2, dphi/dalpha_k = (G_k - W)/sum, G = (g, 0, h).
-// Jiang-Shu: s_k = eps + IS_k, alpha_k = d_k/s_k^2, so
-//   dphi/ds_0 = (2 omega_0/s_0)(W - g), dphi/ds_1 = (2 omega_1/s_1) W,
-//   dphi/ds_2 = (2 omega_2/s_2)(W - h).
 // WENO-Z: alpha_k = d_k (1 + r_k^2), r_k = tau_5/(eps_Z + IS_k), tau_5 = |IS_0 - IS_2|.
 // ---------------------------------------------------------------------------
 
@@ -159,27 +158,40 @@ __host__ __device__ __forceinline__ void phiN_val_grad(double a, double b, doubl
   const double t2 = b - c, t3 = b + c;
   const double t4 = c - d, t5 = 3.0 * c - d;
   const double X = t0 - t2, Y = t2 - t4;   // a - 2b + c, b - 2c + d
-  const double g = X * (1.0 / 3.0), h = Y * (1.0 / 6.0);
-  double w0, w2, l0, l1, l2;   // normalised weights 0, 2 and dphi/dIS_k
   if constexpr (!WZ) {
+    // As phiN, with s_k = (eps + IS_k)/3, S_k = s_k^2, c = 3 p01 - m and Q = 3 p01 + m:
+    // phi = (4 p12 X + c Y)/(12 Q), and with A = Y/12 - phi, B = Y/12 + phi,
+    // C = X/3 - Y/12 - phi
+    //   dphi/ds_0 = (6 s_0/Q)(S_1 A - 2 S_2 B),  dphi/ds_1 = (2 s_1/Q)(S_2 C + 3 S_0 A),
+    //   dphi/ds_2 = (2 s_2/Q)(S_1 C - 6 S_0 B).
     (void)epsZ;
     (void)lit;
-    const double s0 = eps + 13.0 * t0 * t0 + 3.0 * t1 * t1;
-    const double s1 = eps + 13.0 * t2 * t2 + 3.0 * t3 * t3;
-    const double s2 = eps + 13.0 * t4 * t4 + 3.0 * t5 * t5;
-    // 1/s_k from one reciprocal of s0 s1 s2 (s_k >= eps, so the product stays normal)
-    const double s12 = s1 * s2, r = rcp_w(s0 * s12);
-    const double i0 = s12 * r, i1 = s0 * s2 * r, i2 = s0 * s1 * r;
-    const double al0 = i0 * i0, al1 = 6.0 * i1 * i1, al2 = 3.0 * i2 * i2;
-    const double isum = rcp_w(al0 + al1 + al2);
-    w0 = al0 * isum;
-    const double w1 = al1 * isum;
-    w2 = al2 * isum;
-    const double W = g * w0 + h * w2;
-    l0 = 2.0 * w0 * i0 * (W - g);
-    l1 = 2.0 * w1 * i1 * W;
-    l2 = 2.0 * w2 * i2 * (W - h);
+    const double e3 = eps * (1.0 / 3.0);
+    const double T0 = (13.0 / 3.0) * t0, T2 = (13.0 / 3.0) * t2, T4 = (13.0 / 3.0) * t4;
+    const double s0 = fma(T0, t0, fma(t1, t1, e3));
+    const double s1 = fma(T2, t2, fma(t3, t3, e3));
+    const double s2 = fma(T4, t4, fma(t5, t5, e3));
+    const double S0 = s0 * s0, S1 = s1 * s1, S2 = s2 * s2;
+    const double p12 = S1 * S2, p02 = S0 * S2, p01 = S0 * S1;
+    const double m = fma(6.0, p02, p12);
+    const double rq = rcp_w(fma(3.0, p01, m));
+    const double cX = p12 * (rq * (1.0 / 3.0)), cY = fma(3.0, p01, -m) * (rq * (1.0 / 12.0));
+    val = fma(cX, X, cY * Y);
+    const double y = Y * (1.0 / 12.0);
+    const double A = y - val, B = y + val, C = fma(X, 1.0 / 3.0, -B);
+    const double r4 = 4.0 * rq;
+    // twice dphi/ds_k
+    const double l0 = 3.0 * (s0 * r4) * fma(-2.0, S2 * B, S1 * A);
+    const double l1 = (s1 * r4) * fma(3.0, S0 * A, S2 * C);
+    const double l2 = (s2 * r4) * fma(-6.0, S0 * B, S1 * C);
+    // ds_k by its two squares: 2 (13/3) t dt and 2 t' dt'
+    const double u0 = l0 * T0, v0 = l0 * t1, u1 = l1 * T2, v1 = l1 * t3, u2 = l2 * T4, v2 = l2 * t5;
+    gr[0] = cX + (u0 + v0);
+    gr[1] = fma(-2.0, cX, cY) - u0 - 3.0 * v0 + (u1 + v1);
+    gr[2] = fma(-2.0, cY, cX) - u1 + v1 + (u2 + 3.0 * v2);
+    gr[3] = cY - (u2 + v2);
   } else {
+    const double g = X * (1.0 / 3.0), h = Y * (1.0 / 6.0);
     // WENO-Z: alpha_k = d_k (1 + u_k), q_k = 1/(eps_Z + IS_k), r_k = tau5 q_k, tau5 = |IS_0 - IS_2|,
     // u_k = r_k^2, or u_k = tau5 q_k^2 = r_k q_k as printed (`lit`).  Both give
     // du_k/dIS_k = -2 u_k q_k; du_k/dtau5 is 2 r_k q_k, or q_k^2 as printed.
@@ -194,27 +206,26 @@ __host__ __device__ __forceinline__ void phiN_val_grad(double a, double b, doubl
     const double u0 = r0 * s0, u1 = r1 * s1, u2 = r2 * s2;
     const double al0 = 1.0 + u0, al1 = 6.0 * (1.0 + u1), al2 = 3.0 * (1.0 + u2);
     const double isum = rcp_w(al0 + al1 + al2);
-    w0 = al0 * isum;
-    w2 = al2 * isum;
+    const double w0 = al0 * isum, w2 = al2 * isum;   // normalised weights 0, 2
     const double W = g * w0 + h * w2;
     // dphi/du_k = (G_k - W)/sum(alpha) * d_k, G = (g, 0, h)
     const double M0 = (g - W) * isum, M1 = -W * isum * 6.0, M2 = (h - W) * isum * 3.0;
     const double ct = lit ? 1.0 : 2.0;   // du_k/dtau5 = ct s_k q_k
     const double ltau = ct * (M0 * s0 * q0 + M1 * s1 * q1 + M2 * s2 * q2);   // dphi/dtau5
     const double sg = dIS > 0.0 ? 1.0 : (dIS < 0.0 ? -1.0 : 0.0);
-    l0 = -2.0 * M0 * u0 * q0 + sg * ltau;
-    l1 = -2.0 * M1 * u1 * q1;
-    l2 = -2.0 * M2 * u2 * q2 - sg * ltau;
+    const double l0 = -2.0 * M0 * u0 * q0 + sg * ltau;   // dphi/dIS_k
+    const double l1 = -2.0 * M1 * u1 * q1;
+    const double l2 = -2.0 * M2 * u2 * q2 - sg * ltau;
+    const double cX = w0 * (1.0 / 3.0), cY = (w2 - 0.5) * (1.0 / 6.0);
+    val = cX * X + cY * Y;
+    // dIS_0/da = 26 t0 + 6 t1, dIS_0/db = -26 t0 - 18 t1
+    // dIS_1/db = 26 t2 + 6 t3, dIS_1/dc = -26 t2 + 6 t3
+    // dIS_2/dc = 26 t4 + 18 t5, dIS_2/dd = -26 t4 - 6 t5
+    gr[0] = cX + l0 * (26.0 * t0 + 6.0 * t1);
+    gr[1] = -2.0 * cX + cY + l0 * (-26.0 * t0 - 18.0 * t1) + l1 * (26.0 * t2 + 6.0 * t3);
+    gr[2] = cX - 2.0 * cY + l1 * (-26.0 * t2 + 6.0 * t3) + l2 * (26.0 * t4 + 18.0 * t5);
+    gr[3] = cY + l2 * (-26.0 * t4 - 6.0 * t5);
   }
-  const double cX = w0 * (1.0 / 3.0), cY = (w2 - 0.5) * (1.0 / 6.0);
-  val = cX * X + cY * Y;
-  // dIS_0/da = 26 t0 + 6 t1, dIS_0/db = -26 t0 - 18 t1
-  // dIS_1/db = 26 t2 + 6 t3, dIS_1/dc = -26 t2 + 6 t3
-  // dIS_2/dc = 26 t4 + 18 t5, dIS_2/dd = -26 t4 - 6 t5
-  gr[0] = cX + l0 * (26.0 * t0 + 6.0 * t1);
-  gr[1] = -2.0 * cX + cY + l0 * (-26.0 * t0 - 18.0 * t1) + l1 * (26.0 * t2 + 6.0 * t3);
-  gr[2] = cX - 2.0 * cY + l1 * (-26.0 * t2 + 6.0 * t3) + l2 * (26.0 * t4 + 18.0 * t5);
-  gr[3] = cY + l2 * (-26.0 * t4 - 6.0 * t5);
 }
 
 // ---------------------------------------------------------------------------
@@ -355,18 +366,12 @@ __host__ __device__ __forceinline__ void pair_rev(const PairRows& r, ROW row, do
   for (int j = 0; j < 4; ++j) pin(c.lA[j]);
 }
 
-// The pair's cotangents of the interface differences: emit(k, lD[14]), k = 0..4.
-template <class PA, bool TWO, class EMIT>
-__host__ __device__ __forceinline__ void pair_emit(const PairRows& r, const PairGrad& g, EMIT emit) {
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    double lD[14], sF, aF, sq, aq;
-    pair_sums<TWO>(r, g, k, sF, aF, sq, aq);
-#pragma unroll
-    for (int j = 0; j < 14; ++j) lD[j] = 0.0;
-    PA::difcot(r, sF, aF, sq, aq, lD);
-    emit(k, lD);
-  }
+// Adds the pair's cotangents of the differences of interface k to lD.
+template <class PA, bool TWO>
+__host__ __device__ __forceinline__ void pair_difcot(const PairRows& r, const PairGrad& g, int k, double lD[14]) {
+  double sF, aF, sq, aq;
+  pair_sums<TWO>(r, g, k, sF, aF, sq, aq);
+  PA::difcot(r, sF, aF, sq, aq, lD);
 }
 
 // ---------------------------------------------------------------------------
@@ -519,8 +524,7 @@ __host__ __device__ __forceinline__ void entropy_post(const FaceEig& e, const do
   eb.add_q(e, -2.0 * e.omg * lht);
 }
 
-using FastShape = PairShape<0, 4, true, 127>;
-using SlowShape = PairShape<0, 4, true, 127>;
+using MagnetoShape = PairShape<0, 4, true, 127>;
 using AlfvenShape = PairShape<4, 2, true, 13>;
 using EntropyShape = PairShape<0, 0, false, 127>;
 
@@ -548,68 +552,70 @@ __host__ __device__ __forceinline__ void face_corr_vjp(FaceEig& e, ALF alf, doub
   const bool lit = ph.weno_z == 2;
   eb.zero();
   {
+    // the entropy row's gradient waits for the Alfven pair's, so that one round of
+    // additions carries both (its row is formed again)
+    PairGrad gn, ga;
+    {
+      renew(e, lam);
+      PairRows r;
+      entropy_rows(e, alf, lam, r);
+      PairCot c;
+      pair_rev<EntropyShape, false, WZ, PITCH>(r, row, eps, epsZ, lit, c, gn);
+      renew(e, lam);
+      entropy_post(e, lam, c, eb);
+      lal[3] = c.lalu;
+      eb.pin_all();
+      pin(lal[3]);
+      sched_fence();
+    }
     renew(e, lam);
-    PairRows r;
-    entropy_rows(e, alf, lam, r);
+    PairRows ra, rn;
+    alfven_rows(e, alf, lam, ra);
     PairCot c;
-    PairGrad g;
-    pair_rev<EntropyShape, false, WZ, PITCH>(r, row, eps, epsZ, lit, c, g);
-    renew(e, lam);
-    entropy_post(e, lam, c, eb);
-    lal[3] = c.lalu;
-    eb.pin_all();
-    pin(lal[3]);
-    sched_fence();
-    pair_emit<EntropyShape, false>(r, g, emit);
-  }
-  sched_fence();
-  {
-    renew(e, lam);
-    PairRows r;
-    alfven_rows(e, alf, lam, r);
-    PairCot c;
-    PairGrad g;
-    pair_rev<AlfvenShape, true, WZ, PITCH>(r, row, eps, epsZ, lit, c, g);
+    pair_rev<AlfvenShape, true, WZ, PITCH>(ra, row, eps, epsZ, lit, c, ga);
     renew(e, lam);
     alfven_post(e, lam, c, eb);
     lal[1] = c.lalu; lal[5] = c.lall;
     eb.pin_all();
     pin(lal[1]); pin(lal[5]);
     sched_fence();
-    pair_emit<AlfvenShape, true>(r, g, emit);
+    renew(e, lam);
+    entropy_rows(e, alf, lam, rn);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      double lD[14] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+      pair_difcot<EntropyShape, false>(rn, gn, k, lD);
+      pair_difcot<AlfvenShape, true>(ra, ga, k, lD);
+      emit(k, lD);
+    }
   }
   sched_fence();
-  {
+  auto magneto = [&](auto fast) {
+    constexpr bool FAST = decltype(fast)::value;
     renew(e, lam);
     PairRows r;
-    magneto_rows<false>(e, alf, lam, r);
+    magneto_rows<FAST>(e, alf, lam, r);
     PairCot c;
     PairGrad g;
-    pair_rev<SlowShape, true, WZ, PITCH>(r, row, eps, epsZ, lit, c, g);
+    pair_rev<MagnetoShape, true, WZ, PITCH>(r, row, eps, epsZ, lit, c, g);
     renew(e, lam);
-    magneto_post<false>(e, lam, c, eb);
-    lal[2] = c.lalu; lal[4] = c.lall;
+    magneto_post<FAST>(e, lam, c, eb);
+    double& lu = lal[FAST ? 0 : 2];
+    double& ll = lal[FAST ? 6 : 4];
+    lu = c.lalu; ll = c.lall;
     eb.pin_all();
-    pin(lal[2]); pin(lal[4]);
+    pin(lu); pin(ll);
     sched_fence();
-    pair_emit<SlowShape, true>(r, g, emit);
-  }
-  sched_fence();
-  {
-    renew(e, lam);
-    PairRows r;
-    magneto_rows<true>(e, alf, lam, r);
-    PairCot c;
-    PairGrad g;
-    pair_rev<FastShape, true, WZ, PITCH>(r, row, eps, epsZ, lit, c, g);
-    renew(e, lam);
-    magneto_post<true>(e, lam, c, eb);
-    lal[0] = c.lalu; lal[6] = c.lall;
-    eb.pin_all();
-    pin(lal[0]); pin(lal[6]);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+      double lD[14] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+      pair_difcot<MagnetoShape, true>(r, g, k, lD);
+      emit(k, lD);
+    }
     sched_fence();
-    pair_emit<FastShape, true>(r, g, emit);
-  }
+  };
+  magneto(std::false_type{});
+  magneto(std::true_type{});
 }
 
 // ---------------------------------------------------------------------------

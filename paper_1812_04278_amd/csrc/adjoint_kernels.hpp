@@ -121,9 +121,11 @@ constexpr int ADJ_ZONES = 280, ADJ_FACES = 276;
 // lane under 256 registers, and the zone cotangents take the place of the zone
 // values and differences once those are spent, so that 80 KB of LDS hold a tile
 // and a second wave per SIMD fills the waits: at 128^3 an axis took 744-790 us with
-// one wave per SIMD (147 KB, 446 registers, two pairs at once) and takes 505-550
-// now, 53% of it VALU issue; at 48^3 73-78 and 37-39, where one tile spans the axis
-// and the two or three launches of its classes become one.
+// one wave per SIMD (147 KB, 446 registers, two pairs at once), 505-550 with two,
+// and 445-495 with columns of 64 faces to a wave, one reciprocal for a weight's
+// value and gradient, and the entropy row's additions carried by the Alfven
+// pair's; at 48^3 73-78, 37-39 and 35-37, where one tile spans the axis and the two
+// or three launches of its classes become one.
 template <int AXIS, bool WZ>
 __global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs a) {
   constexpr int NC = ADJ_ZONES, ND = ADJ_FACES;
@@ -143,8 +145,10 @@ __global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs 
   const int ncell = NA * TB;
   constexpr int CN = AXIS, CT1 = (AXIS + 1) % 3, CT2 = (AXIS + 2) % 3;
   auto mul = [](int x, int y) { return (int)__umul24((unsigned)x, (unsigned)y); };
-  auto cidx = [&](int aa, int bb) { return AXIS == 0 ? mul(bb, NA) + aa : mul(aa, TB) + bb; };
-  auto iidx = [&](int ia, int bb) { return AXIS == 0 ? mul(bb, NI) + ia : mul(ia, TB) + bb; };
+  // In LDS a column's values are neighbours, and so are its faces among the
+  // lanes; only the zones' accesses to memory follow the rows across y and z.
+  auto cidx = [&](int aa, int bb) { return mul(bb, NA) + aa; };
+  auto iidx = [&](int ia, int bb) { return mul(bb, NI) + ia; };
   auto quot = [](int n, unsigned div) { return (int)(__umul24((unsigned)n, div) >> SW_DIV_SHIFT); };
   auto split_cell = [&](int cell, int& aa, int& bb) {
     if (AXIS == 0) { bb = quot(cell, ax.div_na); aa = cell - mul(bb, NA); }
@@ -178,53 +182,56 @@ __global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs 
     u[7] = a.bcell[CT2 * g.N + gi];
   };
 
-  // ---- (0) the face of this thread and its incoming cotangents: flux divergence
-  // transposed, lam_F_v(face i+1/2) = (lam_k_v(i+1) - lam_k_v(i))/h, in the sweep
-  // frame; the B_t components carry the transport-flux cotangents.  Threads past
-  // the tile's faces repeat face 0 and add nothing.
+  // ---- (1) forward zone prologue into LDS, with the cotangents that arrive at the
+  // zone (7 rows, in the place of the difference cotangents)
+  double* stage = LD;
+  static_assert(7 * NC <= SW_NQ * ND, "the staged cotangents fit");
+  for (int cell = threadIdx.x; cell < ncell; cell += ADJ_THREADS) {
+    int aa, bb;
+    split_cell(cell, aa, bb);
+    const int cz = cidx(aa, bb);
+    double u[8], z[Z_NVAR], lk[7];
+    const size_t gi = zone_at(min(b0 + bb, ax.ncol - 1), wrap_near(a0 - SW_HL + aa, nA));
+    load_zone(gi, u);
+#pragma unroll
+    for (int v = 0; v < 7; ++v) lk[v] = (v < 5 ? a.lam_k : a.lam_T - 5 * g.N)[v * g.N + gi];
+    zone_prologue(u[0], u[1], u[2], u[3], u[4], u[5], u[6], u[7], a.ph.gamma, z);
+#pragma unroll
+    for (int v = 0; v < SW_NQ; ++v) Q[v * NC + cz] = z[v];
+    const int pv[SW_NPF] = {Z_VN, Z_VT1, Z_VT2, Z_BN, Z_P, Z_CF, Z_CA, Z_CS};
+#pragma unroll
+    for (int v = 0; v < SW_NPF; ++v) Pz[v * NC + cz] = z[pv[v]];
+#pragma unroll
+    for (int v = 0; v < 7; ++v) stage[v * NC + cz] = lk[v];
+  }
+  // the face of this thread; threads past the tile's faces repeat face 0 and add nothing
   const bool active = (int)threadIdx.x < TA * TB;
   int fa, fb;
   {
     const int t = active ? threadIdx.x : 0;
-    if (AXIS == 0) { fb = quot(t, ax.div_ta); fa = t - mul(fb, TA); }
-    else           { fa = quot(t, ax.div_tb); fb = t - mul(fa, TB); }
-  }
-  double lam[7];
-  {
-    const int q = min(b0 + fb, ax.ncol - 1);
-    const size_t g0 = zone_at(q, wrap_near(a0 + fa, nA)), g1 = zone_at(q, wrap_near(a0 + fa + 1, nA));
-    double lg[5];
-#pragma unroll
-    for (int v = 0; v < 5; ++v) lg[v] = (a.lam_k[v * g.N + g1] - a.lam_k[v * g.N + g0]) * a.inv_h;
-    const double msk = active && fa < tav && b0 + fb < ax.ncol ? 1.0 : 0.0;
-    lam[0] = msk * lg[0];
-    lam[1] = msk * lg[1 + CN];
-    lam[2] = msk * lg[1 + CT1];
-    lam[3] = msk * lg[1 + CT2];
-    lam[4] = msk * a.lam_T[g0];
-    lam[5] = msk * a.lam_T[g.N + g0];
-    lam[6] = msk * lg[4];
-  }
-
-  // ---- (1) forward zone prologue into LDS
-  for (int cell = threadIdx.x; cell < ncell; cell += ADJ_THREADS) {
-    int aa, bb;
-    split_cell(cell, aa, bb);
-    double u[8], z[Z_NVAR];
-    load_zone(zone_at(min(b0 + bb, ax.ncol - 1), wrap_near(a0 - SW_HL + aa, nA)), u);
-    zone_prologue(u[0], u[1], u[2], u[3], u[4], u[5], u[6], u[7], a.ph.gamma, z);
-#pragma unroll
-    for (int v = 0; v < SW_NQ; ++v) Q[v * NC + cell] = z[v];
-    const int pv[SW_NPF] = {Z_VN, Z_VT1, Z_VT2, Z_BN, Z_P, Z_CF, Z_CA, Z_CS};
-#pragma unroll
-    for (int v = 0; v < SW_NPF; ++v) Pz[v * NC + cell] = z[pv[v]];
+    fb = quot(t, ax.div_ta);
+    fa = t - mul(fb, TA);
   }
   __syncthreads();
 
   // ---- (2) the difference of the face's own interface and of the four of a
   // column beyond its faces' own (lanes fa < 4), as in the forward sweep
-  const int cL = cidx(fa + 2, fb), cR = cidx(fa + 3, fb);
-  double f_rho, f_bt1, f_bt2;
+  const int cL = cidx(fa + 2, fb), cR = cL + 1;
+  double f_rho, f_bt1, f_bt2, lam[7];
+  {
+    // incoming cotangents: flux divergence transposed, lam_F_v(face i+1/2) =
+    // (lam_k_v(i+1) - lam_k_v(i))/h, in the sweep frame; the B_t components carry the
+    // transport-flux cotangents
+    const double msk = active && fa < tav && b0 + fb < ax.ncol ? 1.0 : 0.0, mh = msk * a.inv_h;
+    auto lF = [&](int v) { return mh * (stage[v * NC + cR] - stage[v * NC + cL]); };
+    lam[0] = lF(0);
+    lam[1] = lF(1 + CN);
+    lam[2] = lF(1 + CT1);
+    lam[3] = lF(1 + CT2);
+    lam[4] = msk * stage[5 * NC + cL];
+    lam[5] = msk * stage[6 * NC + cL];
+    lam[6] = lF(4);
+  }
   {
     double d0[SW_NQ], d1[SW_NQ], f_q[7];
 #pragma unroll
@@ -265,14 +272,20 @@ __global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs 
   auto mean = [&](int v) { return 0.5 * (Pz[v * NC + cL] + Pz[v * NC + cR]); };
   const double* dl0 = Q + iidx(fa, fb);
   double* ld0 = LD + iidx(fa, fb);
-  const int dstep = AXIS == 0 ? 1 : TB;
-  auto row = [&](int k) -> const double* { return dl0 + k * dstep; };
-  // round k: every face adds its cotangent of interface difference fa + k (a
-  // barrier before each fixes the order of the additions to an interface)
+  auto row = [&](int k) -> const double* { return dl0 + k; };
+  // round k: every face adds its cotangent of interface difference fa + k.  A
+  // barrier before each fixes the order of the additions to an interface; with
+  // columns of 64 faces no other wave adds to a wave's interfaces, and its own
+  // additions keep their order (the barriers cost 8% of an axis at 128^3).
+  const bool own_columns = TA == 64;
+  auto in_order = [&]() {
+    if (own_columns) { reload_fence(); sched_fence(); }
+    else __syncthreads();
+  };
   auto emit = [&](int k, const double* v) {
-    __syncthreads();
+    in_order();
     if (active) {
-      double* l = ld0 + k * dstep;
+      double* l = ld0 + k;
 #pragma unroll
       for (int j = 0; j < SW_NQ; ++j) lds_add(l + j * ND, v[j]);
     }
@@ -321,15 +334,18 @@ __global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs 
   // zone R's added.  The central term F_c = (F_L + F_R)/2 + (Delta F_{i-1/2} - Delta F_{i+3/2})/12
   // gives half of lam to both zones and +- lam/12 to the differences of
   // interfaces fa + 1 and fa + 3.
-  __syncthreads();
+  in_order();
   if (active) {
 #pragma unroll
-    for (int j = 0; j < 7; ++j) ld0[j * ND + dstep] += (1.0 / 12.0) * lam[j];
+    for (int j = 0; j < 7; ++j) lds_add(ld0 + j * ND + 1, (1.0 / 12.0) * lam[j]);
+  }
+  in_order();
+  if (active) {
+#pragma unroll
+    for (int j = 0; j < 7; ++j) lds_add(ld0 + j * ND + 3, (-1.0 / 12.0) * lam[j]);
   }
   __syncthreads();
   if (active) {
-#pragma unroll
-    for (int j = 0; j < 7; ++j) ld0[j * ND + 3 * dstep] -= (1.0 / 12.0) * lam[j];
 #pragma unroll
     for (int v = 0; v < ADJ_NP; ++v) PB[v * NC + cL] = pl[v];
 #pragma unroll
@@ -359,8 +375,8 @@ __global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs 
     if (aa >= 1) {
 #pragma unroll
       for (int j = 0; j < 7; ++j) {
-        lz[Z_F0 + j] += LD[j * ND + ii - dstep];
-        lz[Z_RHO + j] += LD[(7 + j) * ND + ii - dstep];
+        lz[Z_F0 + j] += LD[j * ND + ii - 1];
+        lz[Z_RHO + j] += LD[(7 + j) * ND + ii - 1];
       }
     }
     if (aa < NI) {

@@ -363,6 +363,7 @@ TilePlan adjoint_plan(int n, int ncol, bool xacross) {
       cost += (rounds < 4.0 ? std::ceil(rounds) : rounds + 0.5) + 0.2;
     }
     cost *= !xacross || tb >= 8 ? 1.0 : (tb >= 4 ? 1.02 : 1.06);
+    if (ta == 64) cost *= 0.94;   // each wave adds to its own column: fewer barriers
     if (best.n == 0 || cost < best_cost) {
       best = pl;
       best.ax.ta = ta;
