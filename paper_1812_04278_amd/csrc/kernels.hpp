@@ -732,20 +732,29 @@ __global__ __launch_bounds__(256) void update_kernel(UpdateArgs<S> a) {
     return;
   }
   if (STAGE != 0 || !a.keys) dt = *a.dt;
+  // all loads ahead of the stores: the stores may alias U^n and the accumulator, so
+  // in one loop each variable's loads waited for the one before (eight round trips
+  // to memory at the end of every wave)
+  double un_v[8], acc_v[8];
 #pragma unroll
   for (int v = 0; v < 8; ++v) {
-    const double un = double(nt_load(v < 5 ? a.Un + v * N + c0 : a.bn + (v - 5) * N + c0));
+    un_v[v] = double(nt_load(v < 5 ? a.Un + v * N + c0 : a.bn + (v - 5) * N + c0));
+    acc_v[v] = STAGE > 0 ? double(nt_load(a.acc + v * N + c0)) : 0.0;
+  }
+#pragma unroll
+  for (int v = 0; v < 8; ++v) {
+    const double un = un_v[v];
     double out;
     if constexpr (RK == 3) {
       if constexpr (STAGE == 0) {
         nt_store(a.acc + v * N + c0, S(kv[v]));
         out = un + dt * kv[v];
       } else if constexpr (STAGE == 1) {
-        const double s = double(nt_load(a.acc + v * N + c0)) + kv[v];
+        const double s = acc_v[v] + kv[v];
         nt_store(a.acc + v * N + c0, S(s));
         out = un + (0.25 * dt) * s;
       } else {
-        const double s = double(nt_load(a.acc + v * N + c0)) + 4.0 * kv[v];
+        const double s = acc_v[v] + 4.0 * kv[v];
         out = un + (dt / 6.0) * s;
       }
     } else {
@@ -753,10 +762,10 @@ __global__ __launch_bounds__(256) void update_kernel(UpdateArgs<S> a) {
         nt_store(a.acc + v * N + c0, S(kv[v]));
         out = un + (0.5 * dt) * kv[v];
       } else if constexpr (STAGE < 3) {
-        nt_store(a.acc + v * N + c0, S(double(nt_load(a.acc + v * N + c0)) + 2.0 * kv[v]));
+        nt_store(a.acc + v * N + c0, S(acc_v[v] + 2.0 * kv[v]));
         out = un + (STAGE == 1 ? 0.5 * dt : dt) * kv[v];
       } else {
-        const double s = double(nt_load(a.acc + v * N + c0)) + kv[v];
+        const double s = acc_v[v] + kv[v];
         out = un + (dt / 6.0) * s;
       }
     }
@@ -919,19 +928,23 @@ __global__ __launch_bounds__(256) void update_pair_kernel(UpdateArgs<S> a) {
     return;
   }
   if (STAGE != 0 || !a.keys) dt = *a.dt;
+  // all loads ahead of the stores, as in update_kernel
+  using NV = typename NtV2<S>::T;
+  NV un_v[8], acc_v[8];
 #pragma unroll
   for (int v = 0; v < 8; ++v) {
-    const S* unp = v < 5 ? a.Un + v * N : a.bn + (v - 5) * N;
-    using NV = typename NtV2<S>::T;
-    const NV u = __builtin_nontemporal_load(reinterpret_cast<const NV*>(unp + c0));
-    const double un[2] = {double(u.x), double(u.y)};
-    V2* accp = reinterpret_cast<V2*>(a.acc + v * N + c0);
+    un_v[v] = __builtin_nontemporal_load(
+        reinterpret_cast<const NV*>((v < 5 ? a.Un + v * N : a.bn + (v - 5) * N) + c0));
+    if constexpr (STAGE > 0) acc_v[v] = __builtin_nontemporal_load(reinterpret_cast<const NV*>(a.acc + v * N + c0));
+  }
+#pragma unroll
+  for (int v = 0; v < 8; ++v) {
+    const double un[2] = {double(un_v[v].x), double(un_v[v].y)};
     double out[2], acc_new[2];
     double acc_old[2] = {0.0, 0.0};
     if constexpr (STAGE > 0) {
-      const NV t = __builtin_nontemporal_load(reinterpret_cast<const NV*>(accp));
-      acc_old[0] = double(t.x);
-      acc_old[1] = double(t.y);
+      acc_old[0] = double(acc_v[v].x);
+      acc_old[1] = double(acc_v[v].y);
     }
 #pragma unroll
     for (int z = 0; z < 2; ++z) {
