@@ -435,11 +435,11 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
   // Lax-Friedrichs speed of field m (0-based), read when its pair needs it:
   // max(|v_L + sg c_L|, |v_R + sg c_R|), c = c_f (m = 0, 6), c_A (1, 5), c_s (2, 4), 0 (3)
   auto alf = [&](int m) -> TW {
-    const double vL = PL(FP_VN), vR = PR(FP_VN);
-    if (m == 3) return TW(fmax(fabs(vL), fabs(vR)));
+    const TW vL = Pz[FP_VN * NC + cL], vR = Pz[FP_VN * NC + cR];
+    if (m == 3) return fmax(fabs(vL), fabs(vR));
     const int sp = (m == 0 || m == 6) ? FP_CF : ((m == 1 || m == 5) ? FP_CA : FP_CS);
-    const double sg = m < 3 ? -1.0 : 1.0;
-    return TW(fmax(fabs(vL + sg * PL(sp)), fabs(vR + sg * PR(sp))));
+    const TW lL = Pz[sp * NC + cL], lR = Pz[sp * NC + cR];
+    return m < 3 ? fmax(fabs(vL - lL), fabs(vR - lR)) : fmax(fabs(vL + lL), fabs(vR + lR));
   };
   FaceEig e;
   auto mean = [&](int v) { return 0.5 * (PL(v) + PR(v)); };

@@ -53,15 +53,12 @@ __host__ __device__ __forceinline__ double rcp_w(double x) {
   return 1.0 / x;
 #endif
 }
-// hardware reciprocal without refinement (about 1 ulp), for scale factors
-__host__ __device__ __forceinline__ float rcp_raw(float x) {
-#ifdef __HIP_DEVICE_COMPILE__
-  return __builtin_amdgcn_rcpf(x);
-#else
-  return 1.0f / x;
-#endif
+// 2^-e of a positive FP32 number x in [2^e, 2^(e+1)) (2^127 at x = 0, -inf at inf
+// and NaN), for scale factors: two integer operations where a reciprocal takes
+// four issue slots
+__host__ __device__ __forceinline__ float pow2_scale(float x) {
+  return __builtin_bit_cast(float, 0x7F000000u - (__builtin_bit_cast(unsigned, x) & 0x7F800000u));
 }
-__host__ __device__ __forceinline__ double rcp_raw(double x) { return rcp_w(x); }
 
 __host__ __device__ __forceinline__ float rcp_w(float x) {
 #ifdef __HIP_DEVICE_COMPILE__
@@ -188,9 +185,9 @@ __host__ __device__ __forceinline__ T phiN(T a, T b, T c, T d, T e3, double e3_Z
     T s1 = fma(T(13.0 / 3.0) * t2, t2, fma(t3, t3, e3));
     T s2 = fma(T(13.0 / 3.0) * t4, t4, fma(t5, t5, e3));
     s0 *= s0; s1 *= s1; s2 *= s2;
-    if (sizeof(T) == 4) {   // FP32: normalise so the products cannot overflow; phi is
-      // homogeneous of degree 0 in the s_k, so the scale need not be exact
-      const T r = rcp_raw(fmax(s0, fmax(s1, s2)));
+    if constexpr (sizeof(T) == 4) {   // FP32: normalise so the products cannot overflow; phi is
+      // homogeneous of degree 0 in the s_k, so any scale serves
+      const T r = pow2_scale(fmaxf(s0, fmaxf(s1, s2)));
       s0 *= r; s1 *= r; s2 *= r;
     }
     const T p12 = s1 * s2, p02 = s0 * s2, p01 = s0 * s1;
