@@ -12,6 +12,8 @@
 //                        tiles of one launch touch disjoint zones
 //   adj_bcell_kernel     face-b cotangent += transpose of the fourth-order
 //                        zone interpolation
+//   adj_collect_kernel   that, and the sum of the sweeps' own arrays, where one
+//                        launch holds the sweeps of the three axes
 //   adj_glue kernels     the RK3 stage combinations
 //   init_adj kernels     transpose of the initial-state map (curl_h A, m, E)
 // Accumulation orders are fixed (LDS sub-rounds separated by barriers, no
@@ -31,14 +33,16 @@ namespace wm {
 // rhs_by = -(Ex - Ex[k-1])/h + (Ez - Ez[i-1])/h, rhs_bz = -(Ey - Ey[i-1])/h +
 // (Ex - Ex[j-1])/h with Ez = (Tyx + Tyx[i+1])/2 - (Txy + Txy[j+1])/2,
 // Ex = (Tzy + Tzy[j+1])/2 - (Tyz + Tyz[k+1])/2, Ey = (Txz + Txz[k+1])/2 - (Tzx + Tzx[i+1])/2.
-// It also clears zero3 ([3][N], the zone-B cotangent that the sweeps then add into).
-__global__ __launch_bounds__(256) void adj_emf_kernel(Grid g, double inv_h, const double* lam_k, double* lam_T,
+// It also clears zero3 ([3][N], the zone-B cotangent that the sweeps then add into)
+// and, with FIELD, forms the zone field B of the face field b that they read.
+template <bool FIELD>
+__global__ __launch_bounds__(256) void adj_emf_kernel(Grid g, double inv_h, double inv_nx, double inv_ny,
+                                                      const double* lam_k, double* lam_T, const double* b, double* B,
                                                       double* zero3) {
-  const int i = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int j = blockIdx.y * 4 + (threadIdx.x >> 6);
-  const int k = blockIdx.z;
-  if (i >= g.nx || j >= g.ny) return;
+  int i, j, k;
+  if (!bcell_zone(g, inv_nx, inv_ny, i, j, k)) return;
   const size_t N = g.N;
+  if (FIELD) zone_field(g, b, B, i, j, k);
   {
     const size_t c = g.at(i, j, k);
     zero3[c] = 0.0;
@@ -86,12 +90,15 @@ struct AdjSweepArgs {
   const double* hydro;   // forward state [5][N]
   const double* bcell;   // its zone B [3][N]
   const double* lam_k;   // [8][N] cotangent of the right-hand side (hydro part used)
-  const double* lam_T;   // [2][N] cotangent of this sweep's transport fluxes T^n_t1, T^n_t2
-  double* lam_h;         // [5][N] += zone cotangents of rho, m_x, m_y, m_z, E
-  double* lam_Bz;        // [3][N] += zone cotangents of the zone field B_x, B_y, B_z
-  SweepAxis ax;          // tile; ntile: the tiles of this launch
-  int tile0;             // tile index along the axis of block 0 of this launch
-  int tstride;           // tile index step between consecutive blocks along the axis
+  const double* lam_T;   // [6][N] cotangents of the transport fluxes T^n_t1, T^n_t2 of x, y, z
+  // per axis: the zone cotangents of rho, m_x, m_y, m_z, E and of the zone field, which
+  // are added to, or stored if `store` (an axis of its own arrays, whose tiles span it)
+  double* lam_h[3];      // [5][N]
+  double* lam_Bz[3];     // [3][N]
+  int store[3];
+  SweepAxis ax[3];       // tile; ntile: the tiles of this launch; blk0
+  int tile0[3];          // tile index along the axis of block 0 of this launch
+  int tstride[3];        // tile index step between consecutive blocks along the axis
   unsigned nblk, per_xcd;   // blocks of this launch, an eighth of them rounded up
   double inv_nx;
 };
@@ -126,20 +133,20 @@ constexpr int ADJ_ZONES = 280, ADJ_FACES = 276;
 // value and gradient, and the entropy row's additions carried by the Alfven
 // pair's; at 48^3 73-78, 37-39 and 35-37, where one tile spans the axis and the two
 // or three launches of its classes become one.
+constexpr int ADJ_LDS = (SW_NQ + SW_NPF) * ADJ_ZONES + SW_NQ * ADJ_FACES;   // doubles
 template <int AXIS, bool WZ>
-__global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs a) {
+__device__ __forceinline__ void adj_sweep_tile(const AdjSweepArgs& a, unsigned blk, double* lds) {
   constexpr int NC = ADJ_ZONES, ND = ADJ_FACES;
   // LDS: zone q/F, then the differences (14 rows) | zone primitives and speeds (8) |
   //      interface-difference cotangents (14); the zone cotangents of the face
   //      state, speeds and flux means (18 rows) over the first two at the end
-  __shared__ double lds[(SW_NQ + SW_NPF) * NC + SW_NQ * ND];
   double* Q = lds;
   double* Pz = lds + SW_NQ * NC;
   double* LD = lds + (SW_NQ + SW_NPF) * NC;
   double* PB = lds;
   static_assert(ADJ_NR <= SW_NQ + SW_NPF && ND <= NC, "aliases fit");
   const Grid& g = a.g;
-  const SweepAxis& ax = a.ax;
+  const SweepAxis& ax = a.ax[AXIS];
   const int nA = AXIS == 0 ? g.nx : (AXIS == 1 ? g.ny : g.nz);
   const int TA = ax.ta, TB = ax.tb, NA = TA + SW_HL + SW_HR, NI = TA + 4;
   const int ncell = NA * TB;
@@ -154,13 +161,8 @@ __global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs 
     if (AXIS == 0) { bb = quot(cell, ax.div_na); aa = cell - mul(bb, NA); }
     else           { aa = quot(cell, ax.div_tb); bb = cell - mul(aa, TB); }
   };
-  // Blocks go to the 8 XCDs in turn: each XCD takes a run of neighbouring column
-  // groups, whose lines of memory its L2 then fetches once (a group of 4 columns
-  // uses 32 of a line's 128 bytes).
-  const unsigned blk = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
-  if (blk >= a.nblk) return;
   const unsigned grp = (unsigned)__builtin_amdgcn_readfirstlane((int)quot_by(blk, ax.inv_ntile));
-  const int a0 = (a.tile0 + (int)(blk - grp * (unsigned)ax.ntile) * a.tstride) * TA;
+  const int a0 = (a.tile0[AXIS] + (int)(blk - grp * (unsigned)ax.ntile) * a.tstride[AXIS]) * TA;
   const int b0 = (int)grp * TB;
   const int tav = min(TA, nA - a0);            // valid faces (and own zones) along the axis
   const unsigned plane = (unsigned)g.nx * (unsigned)g.ny;
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs 
     const size_t gi = zone_at(min(b0 + bb, ax.ncol - 1), wrap_near(a0 - SW_HL + aa, nA));
     load_zone(gi, u);
 #pragma unroll
-    for (int v = 0; v < 7; ++v) lk[v] = (v < 5 ? a.lam_k : a.lam_T - 5 * g.N)[v * g.N + gi];
+    for (int v = 0; v < 7; ++v) lk[v] = (v < 5 ? a.lam_k : a.lam_T + (2 * AXIS - 5) * (ptrdiff_t)g.N)[v * g.N + gi];
     zone_prologue(u[0], u[1], u[2], u[3], u[4], u[5], u[6], u[7], a.ph.gamma, z);
 #pragma unroll
     for (int v = 0; v < SW_NQ; ++v) Q[v * NC + cz] = z[v];
@@ -397,10 +399,14 @@ __global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs 
     split_cell(cell, aa, bb);
     if (aa >= nz_own || b0 + bb >= ax.ncol) continue;
     const size_t gi = zone_at(b0 + bb, wrap_near(a0 - SW_HL + aa, nA));
-    double u[8], lm[8];
+    double u[8], lm[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     load_zone(gi, u);
+    double* const lh = a.lam_h[AXIS];
+    double* const lB = a.lam_Bz[AXIS];
+    if (!a.store[AXIS]) {
 #pragma unroll
-    for (int v = 0; v < 8; ++v) lm[v] = (v < 5 ? a.lam_h : a.lam_Bz - 5 * g.N)[v * g.N + gi];
+      for (int v = 0; v < 8; ++v) lm[v] = v < 5 ? lh[v * g.N + gi] : lB[(v - 5) * g.N + gi];
+    }
     double lz[Z_NVAR];
 #pragma unroll
     for (int v = 0; v < Z_NVAR; ++v) lz[v] = 0.0;
@@ -415,7 +421,50 @@ __global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs 
     out[4] = lu[4];
     out[5 + CN] = lu[5]; out[5 + CT1] = lu[6]; out[5 + CT2] = lu[7];
 #pragma unroll
-    for (int v = 0; v < 8; ++v) (v < 5 ? a.lam_h : a.lam_Bz - 5 * g.N)[v * g.N + gi] = lm[v] + out[v];
+    for (int v = 0; v < 8; ++v) (v < 5 ? lh + v * g.N : lB + (v - 5) * g.N)[gi] = lm[v] + out[v];
+  }
+}
+
+// Blocks go to the 8 XCDs in turn:
+// each XCD takes a run of neighbouring column groups, whose lines of memory its L2
+// then fetches once (a group of 4 columns uses 32 of a line's 128 bytes).
+// AXIS 3: the three axes in one launch, x first.
+template <int AXIS, bool WZ>
+__global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs a) {
+  __shared__ double lds[ADJ_LDS];
+  const unsigned blk = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
+  if (blk >= a.nblk) return;
+  if constexpr (AXIS < 3) adj_sweep_tile<AXIS, WZ>(a, blk, lds);
+  else if (blk < a.ax[1].blk0) adj_sweep_tile<0, WZ>(a, blk, lds);
+  else if (blk < a.ax[2].blk0) adj_sweep_tile<1, WZ>(a, blk - a.ax[1].blk0, lds);
+  else adj_sweep_tile<2, WZ>(a, blk - a.ax[2].blk0, lds);
+}
+
+// The sweeps of a small box in one launch: acc_h += the y and z sweeps' parts, and
+// the zone-field cotangents of the three sweeps (x, y, z) through the transpose of
+// the zone interpolation into acc_b.
+__global__ __launch_bounds__(256) void adj_collect_kernel(Grid g, double inv_nx, double inv_ny, const double* y,
+                                                          const double* z, const double* Bx, double* acc_h,
+                                                          double* acc_b) {
+  const unsigned t = blockIdx.x * 256u + threadIdx.x;
+  if (t >= g.N) return;
+  int i, j, k;
+  thread_zone(t, inv_nx, g.nx, inv_ny, g.ny, i, j, k);
+  const size_t N = g.N, c0 = t;
+#pragma unroll
+  for (int v = 0; v < 5; ++v) acc_h[v * N + c0] += y[v * N + c0] + z[v * N + c0];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const double *p0 = Bx + d * N, *p1 = y + (5 + d) * N, *p2 = z + (5 + d) * N;
+    double L[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int o = q - 1;   // j-1, j, j+1, j+2
+      const size_t c = d == 0 ? g.at(wrap(i + o, g.nx), j, k)
+                              : (d == 1 ? g.at(i, wrap(j + o, g.ny), k) : g.at(i, j, wrap(k + o, g.nz)));
+      L[q] = p0[c] + p1[c] + p2[c];
+    }
+    acc_b[d * N + c0] += (-L[3] + 9.0 * L[2] + 9.0 * L[1] - L[0]) * (1.0 / 16.0);
   }
 }
 

@@ -990,18 +990,7 @@ constexpr int BCELL_ROW_ZONES = 64;
 constexpr int BCELL_ROWS = 256 / BCELL_ROW_ZONES;
 inline __host__ __device__ bool bcell_rows(int nx) { return nx % BCELL_ROW_ZONES == 0; }
 template <typename S>
-__global__ __launch_bounds__(256) void bcell_kernel(Grid g, double inv_nx, double inv_ny, const S* b, S* B) {
-  int i, j, k;
-  if (bcell_rows(g.nx)) {
-    i = blockIdx.x * BCELL_ROW_ZONES + threadIdx.x % BCELL_ROW_ZONES;
-    j = blockIdx.y * BCELL_ROWS + threadIdx.x / BCELL_ROW_ZONES;
-    k = blockIdx.z;
-    if (j >= g.ny) return;
-  } else {
-    const unsigned t = blockIdx.x * 256u + threadIdx.x;
-    if (t >= g.N) return;
-    thread_zone(t, inv_nx, g.nx, inv_ny, g.ny, i, j, k);
-  }
+__device__ __forceinline__ void zone_field(const Grid& g, const S* b, S* B, int i, int j, int k) {
   const size_t N = g.N, c0 = g.at(i, j, k);
   const S* bx = b;
   const S* by = b + N;
@@ -1026,6 +1015,25 @@ __global__ __launch_bounds__(256) void bcell_kernel(Grid g, double inv_nx, doubl
   B[c0] = S(interp(vx, sx));
   B[N + c0] = S(interp(vy, sy));
   B[2 * N + c0] = S(interp(vz, sz));
+}
+// Zone of this thread; false: none.
+__device__ __forceinline__ bool bcell_zone(const Grid& g, double inv_nx, double inv_ny, int& i, int& j, int& k) {
+  if (bcell_rows(g.nx)) {
+    i = blockIdx.x * BCELL_ROW_ZONES + threadIdx.x % BCELL_ROW_ZONES;
+    j = blockIdx.y * BCELL_ROWS + threadIdx.x / BCELL_ROW_ZONES;
+    k = blockIdx.z;
+    return j < g.ny;
+  }
+  const unsigned t = blockIdx.x * 256u + threadIdx.x;
+  if (t >= g.N) return false;
+  thread_zone(t, inv_nx, g.nx, inv_ny, g.ny, i, j, k);
+  return true;
+}
+
+template <typename S>
+__global__ __launch_bounds__(256) void bcell_kernel(Grid g, double inv_nx, double inv_ny, const S* b, S* B) {
+  int i, j, k;
+  if (bcell_zone(g, inv_nx, inv_ny, i, j, k)) zone_field(g, b, B, i, j, k);
 }
 
 // b = B0 + curl_h A (first-order differences on the edge potential)

@@ -300,6 +300,10 @@ dim3 lin_grid(size_t n) { return dim3((unsigned)((n + 255) / 256)); }
 
 dim3 zone_grid(const Grid& g) { return dim3((g.nx + 63) / 64, (g.ny + 3) / 4, g.nz); }
 
+dim3 bcell_grid(const Grid& g) {   // blocks of 256 threads, as bcell_zone numbers them
+  return bcell_rows(g.nx) ? dim3(g.nx / BCELL_ROW_ZONES, (g.ny + BCELL_ROWS - 1) / BCELL_ROWS, g.nz) : lin_grid(g.N);
+}
+
 // Runs fn(S{}) with S the patch's storage type.
 template <class Fn>
 wm_status with_storage(const wm_patch* p, Fn&& fn) {
@@ -537,10 +541,8 @@ wm_status launch_update(wm_patch* p, int stage, double* rhs_out, const SpeedKey*
 template <typename S>
 wm_status launch_bcell(wm_patch* p, const S* b, S* B) {
   const long r = prof_begin(p, K_BCELL);
-  const dim3 grid = bcell_rows(p->g.nx)
-                        ? dim3(p->g.nx / BCELL_ROW_ZONES, (p->g.ny + BCELL_ROWS - 1) / BCELL_ROWS, p->g.nz)
-                        : lin_grid(p->g.N);
-  hipLaunchKernelGGL(bcell_kernel<S>, grid, dim3(256), 0, p->stream, p->g, 1.0 / p->g.nx, 1.0 / p->g.ny, b, B);
+  hipLaunchKernelGGL(bcell_kernel<S>, bcell_grid(p->g), dim3(256), 0, p->stream, p->g, 1.0 / p->g.nx,
+                     1.0 / p->g.ny, b, B);
   WM_LAUNCH_CHECK("bcell kernel");
   prof_end(p, r);
   return WM_OK;
@@ -558,9 +560,21 @@ wm_status check_bound(wm_patch* p) {
 }
 
 template <int AXIS>
-wm_status launch_adj_sweep(wm_patch* p, const double* hydro, const double* bcell, const double* lam_k,
-                           const double* lam_T, double* acc_h, double* lam_Bz) {
-  AdjSweepArgs a;
+wm_status launch_adj_kernel(wm_patch* p, AdjSweepArgs& a, unsigned nblk) {
+  a.nblk = nblk;
+  a.per_xcd = (nblk + 7) / 8;
+  const dim3 grid(8 * a.per_xcd);
+  if (p->ph.weno_z) hipLaunchKernelGGL((adj_sweep_kernel<AXIS, true>), grid, dim3(ADJ_THREADS), 0, p->stream, a);
+  else hipLaunchKernelGGL((adj_sweep_kernel<AXIS, false>), grid, dim3(ADJ_THREADS), 0, p->stream, a);
+  return hip_check(hipGetLastError(), "adjoint sweep kernel");
+}
+
+// The adjoint sweeps of the three axes, all into (acc_h, lam_Bz); or, with `apart`
+// (16 arrays), in one launch: x into those, y and z each into 8 arrays of it.
+wm_status launch_adj_sweeps(wm_patch* p, const double* hydro, const double* bcell, const double* lam_k,
+                            const double* lam_T, double* acc_h, double* lam_Bz, double* apart) {
+  const size_t N = p->g.N;
+  AdjSweepArgs a{};
   a.g = p->g;
   a.ph = p->ph;
   a.inv_h = 1.0 / p->cfg.h;
@@ -568,26 +582,57 @@ wm_status launch_adj_sweep(wm_patch* p, const double* hydro, const double* bcell
   a.bcell = bcell;
   a.lam_k = lam_k;
   a.lam_T = lam_T;
-  a.lam_h = acc_h;
-  a.lam_Bz = lam_Bz;
-  const TilePlan& pl = p->adj_plan[AXIS];
-  a.ax = pl.ax;
   a.inv_nx = 1.0 / p->g.nx;
+  auto blocks = [&](int d, const TileRun& run) {   // sets axis d's tiles of one launch
+    SweepAxis& x = a.ax[d];
+    x = p->adj_plan[d].ax;
+    x.ntile = run.count;
+    x.inv_ntile = 1.0 / run.count;
+    a.tile0[d] = run.first;
+    a.tstride[d] = run.stride;
+    return (unsigned)x.ntile * (unsigned)((x.ncol + x.tb - 1) / x.tb);
+  };
   const long r = prof_begin(p, K_OTHER);
-  for (int c = 0; c < pl.n; ++c) {   // classes in order: each launch adds into disjoint zones
-    a.tile0 = pl.run[c].first;
-    a.tstride = pl.run[c].stride;
-    a.ax.ntile = pl.run[c].count;
-    a.ax.inv_ntile = 1.0 / a.ax.ntile;
-    a.nblk = (unsigned)a.ax.ntile * (unsigned)((a.ax.ncol + a.ax.tb - 1) / a.ax.tb);
-    a.per_xcd = (a.nblk + 7) / 8;
-    const dim3 grid(8 * a.per_xcd);
-    if (p->ph.weno_z) hipLaunchKernelGGL((adj_sweep_kernel<AXIS, true>), grid, dim3(ADJ_THREADS), 0, p->stream, a);
-    else hipLaunchKernelGGL((adj_sweep_kernel<AXIS, false>), grid, dim3(ADJ_THREADS), 0, p->stream, a);
-    WM_LAUNCH_CHECK("adjoint sweep kernel");
+  wm_status s = WM_OK;
+  for (int d = 0; d < 3; ++d) {
+    double* own = apart && d > 0 ? apart + 8 * (d - 1) * N : nullptr;
+    a.lam_h[d] = own ? own : acc_h;
+    a.lam_Bz[d] = own ? own + 5 * N : lam_Bz;
+    a.store[d] = own != nullptr;
   }
-  prof_end(p, r);
-  return WM_OK;
+  if (apart) {
+    unsigned n = 0;
+    for (int d = 0; d < 3; ++d) {
+      const unsigned first = n;
+      n += blocks(d, p->adj_plan[d].run[0]);
+      a.ax[d].blk0 = first;
+    }
+    s = launch_adj_kernel<3>(p, a, n);
+  } else {
+    for (int d = 0; d < 3 && s == WM_OK; ++d) {
+      const TilePlan& pl = p->adj_plan[d];
+      for (int c = 0; c < pl.n && s == WM_OK; ++c) {   // classes in order: each launch adds into disjoint zones
+        const unsigned n = blocks(d, pl.run[c]);
+        s = d == 0 ? launch_adj_kernel<0>(p, a, n)
+                   : (d == 1 ? launch_adj_kernel<1>(p, a, n) : launch_adj_kernel<2>(p, a, n));
+      }
+    }
+  }
+  if (s == WM_OK) prof_end(p, r);
+  return s;
+}
+
+// Whether the three adjoint sweeps go in one launch.  They do where a tile spans each
+// axis: every sweep is then one launch of at most a few hundred blocks, one after the
+// other because all add into the same arrays.  In one launch y and z store into arrays
+// of their own (the face fluxes of the forward step, free here; those of an FP32 state
+// are too short) and adj_collect_kernel adds them up; zone B comes with the transport
+// cotangents.  Five launches fewer and no idle tail per sweep: a step's backward takes
+// 113 us against 249 in 16^3, 172 against 263 in 36x31x32, 353 against 386 in 48^3, 610
+// against 638 in 64^3.  With several tiles on an axis, whose classes need launches of
+// their own, the arrays apart would only be more traffic.
+bool adjoint_one_launch(const wm_patch* p) {
+  return !p->f32 && p->adj_plan[0].n == 1 && p->adj_plan[1].n == 1 && p->adj_plan[2].n == 1;
 }
 
 wm_status check_adjoint(wm_patch* p, void* adj) {
@@ -608,16 +653,26 @@ wm_status rhs_vjp_acc(wm_patch* p, double* A, const double* hydro, const double*
   double* Bz = A + A_BZ * N;
   double* lT = A + A_LT * N;
   double* lBz = A + A_LBZ * N;
-  if ((s = launch_bcell<double>(p, bface, Bz)) != WM_OK) return s;
-  hipLaunchKernelGGL(adj_emf_kernel, zone_grid(p->g), dim3(256), 0, p->stream, p->g, 1.0 / p->cfg.h, lam_k, lT,
-                     lBz);
+  const double inv_nx = 1.0 / p->g.nx, inv_ny = 1.0 / p->g.ny;
+  double* apart = adjoint_one_launch(p) ? p->faces<double>() : nullptr;
+  if (!apart && (s = launch_bcell<double>(p, bface, Bz)) != WM_OK) return s;
+  auto emf = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, bcell_grid(p->g), dim3(256), 0, p->stream, p->g, 1.0 / p->cfg.h, inv_nx, inv_ny, lam_k,
+                       lT, bface, Bz, lBz);
+  };
+  if (apart) emf(adj_emf_kernel<true>);
+  else emf(adj_emf_kernel<false>);
   WM_LAUNCH_CHECK("adjoint emf kernel");
-  if ((s = launch_adj_sweep<0>(p, hydro, Bz, lam_k, lT, acc_h, lBz)) != WM_OK) return s;
-  if ((s = launch_adj_sweep<1>(p, hydro, Bz, lam_k, lT + 2 * N, acc_h, lBz)) != WM_OK) return s;
-  if ((s = launch_adj_sweep<2>(p, hydro, Bz, lam_k, lT + 4 * N, acc_h, lBz)) != WM_OK) return s;
+  if ((s = launch_adj_sweeps(p, hydro, Bz, lam_k, lT, acc_h, lBz, apart)) != WM_OK) return s;
   // face b from the zone-B cotangent
-  hipLaunchKernelGGL(adj_bcell_kernel, zone_grid(p->g), dim3(256), 0, p->stream, p->g, lBz, acc_b);
-  WM_LAUNCH_CHECK("adjoint bcell kernel");
+  if (apart) {
+    hipLaunchKernelGGL(adj_collect_kernel, lin_grid(N), dim3(256), 0, p->stream, p->g, inv_nx, inv_ny, apart,
+                       apart + 8 * N, lBz, acc_h, acc_b);
+    WM_LAUNCH_CHECK("adjoint collect kernel");
+  } else {
+    hipLaunchKernelGGL(adj_bcell_kernel, zone_grid(p->g), dim3(256), 0, p->stream, p->g, lBz, acc_b);
+    WM_LAUNCH_CHECK("adjoint bcell kernel");
+  }
   return WM_OK;
 }
 

@@ -3,6 +3,8 @@ through the oracle, at the axis lengths where they can go wrong: the shortest
 axes (a tile longer than the axis, several of its positions on one zone), one
 tile that spans the axis and wraps onto itself, at and past the longest tile
 (256 faces), a short last tile, and column counts no tile divides."""
+import dataclasses
+
 import pytest
 import torch
 
@@ -38,3 +40,20 @@ def test_rhs_vjp_tile_sizes(shape):
     out = p.rhs_vjp(h, b, lam.cuda())
     check8(out.cpu(), ref, str(shape), conditioning_tol(fn, U, lam, ref))
     assert torch.equal(out, p.rhs_vjp(h, b, lam.cuda()))   # fixed order of the additions
+
+
+# one launch of the three sweeps: tiles that span all axes, WENO-Z; the last has two tiles on z
+@pytest.mark.parametrize("shape", [(3, 3, 3), (17, 33, 9), (64, 9, 70), (9, 4, 300)])
+def test_rhs_vjp_weno_z_one_launch(shape):
+    print("adjoint, one launch", shape, flush=True)
+    n = max(max(shape), 8)
+    U, cfg = oracle_state(fields(n + n % 2, seed=5, v_rms=0.8, kmax=2 if n < 64 else 4, crop=shape), h=0.1)
+    cfg = dataclasses.replace(cfg, weights="z")
+    g = torch.Generator().manual_seed(9)
+    lam = torch.randn((8,) + U["rho"].shape, generator=g, dtype=torch.float64)
+    fn = lambda X: mhd.rhs(X, cfg)
+    ref = oracle_vjp(fn, U, lam)
+    p = B.Patch(B.config(nx=cfg.nx, ny=cfg.ny, nz=cfg.nz, h=cfg.h, weights=B.WM_WENO_Z))
+    h, b = to_gpu_state(U)
+    for _ in range(3):   # the arrays of the y and z sweeps are stored into, not added to
+        check8(p.rhs_vjp(h, b, lam.cuda()).cpu(), ref, str(shape), conditioning_tol(fn, U, lam, ref))
