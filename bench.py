@@ -35,10 +35,10 @@ FLOPS_PER_FACE = 2170
 UPDATE_VALUES_PER_ZONE = 21 + 8 + 8 * 2 / 3 + 8 + 8 * 2 / 3
 PEAK_FP64_TFLOPS = 78.6
 PEAK_HBM_GBS = 8000.0
-# HBM bytes per sweep dispatch on the 256^3 FP64 workload, averaged over the
+# HBM bytes per axis sweep on the 256^3 FP64 workload, averaged over the
 # three axes: FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (the factors a plain copy of
 # known size gives), profiles/fp64_step_256cube_pmc_traffic.md.
-SWEEP_TRAFFIC_BYTES_256 = 2.221e9
+SWEEP_TRAFFIC_BYTES_256 = 2.127e9
 
 
 def log(*a):

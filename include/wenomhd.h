@@ -197,8 +197,9 @@ wm_status wm_rk_stage(wm_patch* p, int stage, const double* dt_host);
  * from the zones the first stage's sweeps already evaluate, so the step reads
  * the state once less; dt, and so the step, are bitwise those of
  * wm_compute_dt followed by wm_rk_stage.  The first stage's accumulator
- * scratch holds the partial maxima meanwhile.  If dt_used is non-NULL the
- * stream is synchronised and the dt of the step is returned there. */
+ * scratch, or in small boxes the reduction scratch, holds the partial maxima
+ * meanwhile.  If dt_used is non-NULL the stream is synchronised and the dt of
+ * the step is returned there. */
 wm_status wm_step(wm_patch* p, double* dt_used);
 
 /* For callers that cannot allocate device memory (code under HIP graph
@@ -263,7 +264,9 @@ wm_status wm_debug_rhs(wm_patch* p, void* out);
  * precision).  On a WM_MIXED_F32STATE patch the state arguments (U^n, the
  * stage states, the state of wm_rhs_vjp) are float arrays like the patch's
  * state: they are widened to FP64 on load, and the FP64 method is linearised
- * at the widened states; cotangents are double arrays in every mode. */
+ * at the widened states; cotangents are double arrays in every mode.  In small
+ * boxes the calls also write the face-flux part of the patch's scratch, which
+ * holds nothing from one stage to the next. */
 size_t wm_adjoint_scratch_bytes(const wm_config* cfg);
 
 /* lam_out = (dL/dU)^T lam_k for the semi-discrete right-hand side L of the

@@ -120,8 +120,9 @@ constexpr int ADJ_ZONES = 280, ADJ_FACES = 276;
 // its cotangent added to lam_h / lam_Bz by exactly one thread of the block;
 // positions that wrap onto the same zone (a tile that spans the whole axis) are
 // summed first.  Blocks of one launch touch disjoint zones (the host launches the
-// tiles of an axis in conflict-free classes), so the additions need no atomics
-// and the order of accumulation is fixed.
+// tiles of an axis in conflict-free classes) or, with the three axes in one launch,
+// the arrays of their axis, so the additions need no atomics in memory and the order
+// of accumulation is fixed.
 //
 // Bound by latency: dependent FP64 chains and LDS round trips between barriers.
 // One pair at a time and thirteen eigen cotangents instead of twenty-three bring a

@@ -592,7 +592,7 @@ wm_status launch_adj_sweeps(wm_patch* p, const double* hydro, const double* bcel
     a.tstride[d] = run.stride;
     return (unsigned)x.ntile * (unsigned)((x.ncol + x.tb - 1) / x.tb);
   };
-  const long r = prof_begin(p, K_OTHER);
+  const long r = prof_begin(p, K_OTHER, 3);
   wm_status s = WM_OK;
   for (int d = 0; d < 3; ++d) {
     double* own = apart && d > 0 ? apart + 8 * (d - 1) * N : nullptr;
