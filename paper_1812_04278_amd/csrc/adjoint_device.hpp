@@ -541,7 +541,9 @@ __host__ __device__ __forceinline__ void renew(FaceEig& e, double lam[7]) {
 // Reverse of face_corr (FP64) at one face: given the eigen scalars e, the
 // Lax-Friedrichs speeds alf(m), the differences (row, PITCH) and the cotangent lam
 // of corr, forms the cotangents of the eigen scalars (eb), of the LF speeds
-// (lal[7]) and, via emit (five calls per pair), of the interface differences.  The
+// (lal[7]) and, via emit (five calls per pair), of the interface differences, where
+// the central flux (F_L + F_R)/2 + (Delta F_{i-1/2} - Delta F_{i+3/2})/12 adds its own
+// (lam/12 on differences 1 and 3: with them the emission, not in additions apart).  The
 // face-state cotangents follow from face_eig_vjp(eb).  One pair at a time: two at
 // once share the reads of the differences but need twice the registers, and two
 // waves per SIMD are worth more than those reads.
@@ -584,6 +586,10 @@ __host__ __device__ __forceinline__ void face_corr_vjp(FaceEig& e, ALF alf, doub
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
       double lD[14] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+      if (k == 1 || k == 3) {   // the central term's part
+#pragma unroll
+        for (int j = 0; j < 7; ++j) lD[j] = (k == 1 ? 1.0 / 12.0 : -1.0 / 12.0) * lam[j];
+      }
       pair_difcot<EntropyShape, false>(rn, gn, k, lD);
       pair_difcot<AlfvenShape, true>(ra, ga, k, lD);
       emit(k, lD);

@@ -334,19 +334,7 @@ __device__ __forceinline__ void adj_sweep_tile(const AdjSweepArgs& a, unsigned b
   }
   // zone sums, over the spent zone values: zone L's part is stored (position fa + 2
   // of face fa; the five positions that are no face's zone L are cleared), then
-  // zone R's added.  The central term F_c = (F_L + F_R)/2 + (Delta F_{i-1/2} - Delta F_{i+3/2})/12
-  // gives half of lam to both zones and +- lam/12 to the differences of
-  // interfaces fa + 1 and fa + 3.
-  in_order();
-  if (active) {
-#pragma unroll
-    for (int j = 0; j < 7; ++j) lds_add(ld0 + j * ND + 1, (1.0 / 12.0) * lam[j]);
-  }
-  in_order();
-  if (active) {
-#pragma unroll
-    for (int j = 0; j < 7; ++j) lds_add(ld0 + j * ND + 3, (-1.0 / 12.0) * lam[j]);
-  }
+  // zone R's added.  The central term gives half of lam to both zones.
   __syncthreads();
   if (active) {
 #pragma unroll
