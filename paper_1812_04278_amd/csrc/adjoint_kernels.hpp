@@ -277,10 +277,11 @@ __device__ __forceinline__ void adj_sweep_tile(const AdjSweepArgs& a, unsigned b
   double* ld0 = LD + iidx(fa, fb);
   auto row = [&](int k) -> const double* { return dl0 + k; };
   // round k: every face adds its cotangent of interface difference fa + k.  A
-  // barrier before each fixes the order of the additions to an interface; with
-  // columns of 64 faces no other wave adds to a wave's interfaces, and its own
-  // additions keep their order (the barriers cost 8% of an axis at 128^3).
-  const bool own_columns = TA == 64;
+  // barrier before each fixes the order of the additions to an interface; where a
+  // wave's 64 faces are whole columns (of 64, 32, 16 or 8) no other wave adds to its
+  // interfaces, and its own additions keep their order (the barriers cost 8% of an
+  // axis at 128^3, 3-4% of a step's cotangents in 16^3 and 32^3).
+  const bool own_columns = TA <= 64 && (TA & (TA - 1)) == 0;
   auto in_order = [&]() {
     if (own_columns) { reload_fence(); sched_fence(); }
     else __syncthreads();

@@ -2,7 +2,8 @@
 through the oracle, at the axis lengths where they can go wrong: the shortest
 axes (a tile longer than the axis, several of its positions on one zone), one
 tile that spans the axis and wraps onto itself, at and past the longest tile
-(256 faces), a short last tile, and column counts no tile divides."""
+(256 faces), a short last tile, several whole columns to a wave, and column
+counts no tile divides."""
 import dataclasses
 
 import pytest
@@ -16,7 +17,7 @@ from test_gpu_adjoint import check8, conditioning_tol, oracle_vjp, to_gpu_state
 pytestmark = pytest.mark.gpu
 
 SIZES = [(3, 4, 5), (5, 3, 6), (13, 7, 3), (60, 5, 4), (64, 5, 3), (5, 66, 3), (4, 3, 67), (131, 3, 4), (3, 257, 4), (256, 3, 3),
-         (262, 4, 3), (3, 5, 259)]
+         (262, 4, 3), (3, 5, 259), (16, 32, 8), (8, 33, 16)]
 
 
 @pytest.fixture(scope="module", autouse=True)
