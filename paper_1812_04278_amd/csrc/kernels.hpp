@@ -448,7 +448,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
   double Ff[7];
 #pragma unroll
   for (int j = 0; j < 7; ++j) Ff[j] = Fc[j];
-  face_corr<WENO_Z, ND, TW>(e, alf, row, a.ph, Ff);
+  face_corr<WENO_Z, (sizeof(TW) < sizeof(S)), ND, TW>(e, alf, row, a.ph, Ff);
   // CT transport-flux correction: face mean of B_n v_t (eq. fct1-fct6)
   const double tc1 = 0.5 * (PL(FP_BN) * PL(FP_VT1) + PR(FP_BN) * PR(FP_VT1));
   const double tc2 = 0.5 * (PL(FP_BN) * PL(FP_VT2) + PR(FP_BN) * PR(FP_VT2));
