@@ -229,7 +229,7 @@ template <typename TW> constexpr size_t sweep_p_doubles() {
 // of the eq. (cfl) signal speed over its zones to a.smax_blk (the first stage
 // of a step), a separate instantiation so that the other sweeps carry none of it.
 
-template <int AXIS, bool WENO_Z, typename TW, typename S, bool DTMAX>
+template <int AXIS, bool WENO_Z, typename TW, typename S, bool DTMAX, bool PLAIN>
 __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, double* sQ, double* sP) {
   constexpr int NC = SweepTile<TW>::ZONES;   // LDS pitch of one zone value
   // and of one difference: in the FP32 work type a multiple of 64, so that one
@@ -448,7 +448,7 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
   double Ff[7];
 #pragma unroll
   for (int j = 0; j < 7; ++j) Ff[j] = Fc[j];
-  face_corr<WENO_Z, (sizeof(TW) < sizeof(S)), ND, TW>(e, alf, row, a.ph, Ff);
+  face_corr<WENO_Z, PLAIN, ND, TW>(e, alf, row, a.ph, Ff);
   // CT transport-flux correction: face mean of B_n v_t (eq. fct1-fct6)
   const double tc1 = 0.5 * (PL(FP_BN) * PL(FP_VT1) + PR(FP_BN) * PR(FP_VT1));
   const double tc2 = 0.5 * (PL(FP_BN) * PL(FP_VT2) + PR(FP_BN) * PR(FP_VT2));
@@ -523,15 +523,15 @@ __device__ __forceinline__ void sweep_tile(const SweepArgs<S>& a, unsigned blk, 
 // fills the chip better and the tails of the axes overlap.  At 16^3 and 32^3 an
 // axis alone has too few blocks for 256 CUs and took 8-9 and 9-14 us, three times
 // per stage: a step 111 -> 61 us (16^3) and 133 -> 86 us (32^3).
-template <bool WENO_Z, typename TW, typename S, bool DTMAX>
+template <bool WENO_Z, typename TW, typename S, bool DTMAX, bool PLAIN>
 __global__ __launch_bounds__(SW_THREADS, 3) void sweep_kernel(SweepArgs<S> a) {
   __shared__ double sQ[sweep_q_doubles<TW>()];
   __shared__ double sP[sweep_p_doubles<TW>()];
   const unsigned blk = blockIdx.y * gridDim.x + blockIdx.x;
   if (blk >= a.nblk) return;
-  if (blk < a.ax[1].blk0) sweep_tile<0, WENO_Z, TW, S, DTMAX>(a, blk, sQ, sP);
-  else if (blk < a.ax[2].blk0) sweep_tile<1, WENO_Z, TW, S, DTMAX>(a, blk - a.ax[1].blk0, sQ, sP);
-  else sweep_tile<2, WENO_Z, TW, S, DTMAX>(a, blk - a.ax[2].blk0, sQ, sP);
+  if (blk < a.ax[1].blk0) sweep_tile<0, WENO_Z, TW, S, DTMAX, PLAIN>(a, blk, sQ, sP);
+  else if (blk < a.ax[2].blk0) sweep_tile<1, WENO_Z, TW, S, DTMAX, PLAIN>(a, blk - a.ax[1].blk0, sQ, sP);
+  else sweep_tile<2, WENO_Z, TW, S, DTMAX, PLAIN>(a, blk - a.ax[2].blk0, sQ, sP);
 }
 
 // ---------------------------------------------------------------------------

@@ -179,15 +179,17 @@ __host__ __device__ __forceinline__ void zone_prologue(double rho, double mn, do
 // eps_Z (1e-40 in the paper) lies below the FP32 range; its arguments are not
 // scaled (the printed form is not homogeneous).
 //
-// MIX (FP32 work on an FP64 state): rows, projections and weights keep the unscaled
-// form, whose sequence of FP32 roundings the mixed form's results carry.  The scaled one
+// PLAIN: rows, projections and weights in the unscaled form.  FP32 work on an FP64 state
+// takes it always: the mixed form's results carry its sequence of FP32 roundings.  The scaled one
 // is as accurate (1.4e-9 against FP64 in both), but results of the two lie 2e-9 apart
 // after an RK4 step at Mach 1 (4e-11 in 256^3 at Mach 0.1; with this form 0.1-0.6e-9 and
 // 5e-12).  It costs the mixed step 1.5% (256^3 11.63 against 11.68-11.88 ms).  In an FP32
-// state the difference drowns, and the scaled form stays.
-template <bool WENO_Z, bool MIX> constexpr double WenoScale = WENO_Z || MIX ? 1.0 : 1.0 / 12.0;
+// state the difference drowns, and the scaled form stays.  FP64 work, and FP32 work on an
+// FP32 state, take it for the smallest eps (plain_weights in wenomhd.hip): between equal
+// zones Q is 10 (eps/3)^4, but 10 (eps/432)^4 in the scaled form.
+template <bool WENO_Z, bool PLAIN> constexpr double WenoScale = WENO_Z || PLAIN ? 1.0 : 1.0 / 12.0;
 
-template <bool WENO_Z, bool MIX, typename T>
+template <bool WENO_Z, bool PLAIN, typename T>
 __host__ __device__ __forceinline__ T phiN(T a, T b, T c, T d, T e3, double e3_Z, bool lit) {
   const T t0 = a - b, t1 = a - T(3) * b;
   const T t2 = b - c, t3 = b + c;
@@ -197,7 +199,6 @@ __host__ __device__ __forceinline__ T phiN(T a, T b, T c, T d, T e3, double e3_Z
     (void)lit;
     // s_k/3 = eps/3 + IS_k/3: a common factor of the three s_k cancels in the
     // weights (e3 = eps/3 at the scale of the arguments)
-    static_assert(!MIX || sizeof(T) == 4, "MIX is FP32 work");
     T s0 = fma(T(13.0 / 3.0) * t0, t0, fma(t1, t1, e3));
     T s1 = fma(T(13.0 / 3.0) * t2, t2, fma(t3, t3, e3));
     T s2 = fma(T(13.0 / 3.0) * t4, t4, fma(t5, t5, e3));
@@ -205,11 +206,11 @@ __host__ __device__ __forceinline__ T phiN(T a, T b, T c, T d, T e3, double e3_Z
     if constexpr (sizeof(T) == 4) {   // FP32: normalise so the products cannot overflow; phi is
       // homogeneous of degree 0 in the s_k, so any scale serves
       const T top = fmaxf(s0, fmaxf(s1, s2));
-      const T r = MIX ? rcp_raw(top) : pow2_scale(top);
+      const T r = PLAIN ? rcp_raw(top) : pow2_scale(top);
       s0 *= r; s1 *= r; s2 *= r;
     }
     const T p12 = s1 * s2, p02 = s0 * s2, p01 = s0 * s1;
-    if constexpr (MIX) {   // phi = [p12 X / 3 + (p01/4 - p12/12 - p02/2) Y] / Q
+    if constexpr (PLAIN) {   // phi = [p12 X / 3 + (p01/4 - p12/12 - p02/2) Y] / Q
       const T rq = rcp_1(fma(T(3), p01, fma(T(6), p02, p12)));
       const T cY = fma(T(0.25), p01, fma(T(-1.0 / 12.0), p12, T(-0.5) * p02));
       return rq * fma(cY, Y, (p12 * T(1.0 / 3.0)) * X);
@@ -242,10 +243,10 @@ __host__ __device__ __forceinline__ T phiN(T a, T b, T c, T d, T e3, double e3_Z
 // phi^- - phi^+ of eq. (FWENO) from the split values of one characteristic
 // field: v[0..3] = Delta F^+ at i-3/2 .. i+3/2, v[4..7] = Delta F^- at i-1/2 .. i+5/2
 // (times WenoScale).
-template <bool WENO_Z, bool MIX, typename T>
+template <bool WENO_Z, bool PLAIN, typename T>
 __host__ __device__ __forceinline__ T weno_split(const T v[8], T e3, double e3_Z, bool lit) {
-  return phiN<WENO_Z, MIX>(v[7], v[6], v[5], v[4], e3, e3_Z, lit) -
-         phiN<WENO_Z, MIX>(v[0], v[1], v[2], v[3], e3, e3_Z, lit);
+  return phiN<WENO_Z, PLAIN>(v[7], v[6], v[5], v[4], e3, e3_Z, lit) -
+         phiN<WENO_Z, PLAIN>(v[0], v[1], v[2], v[3], e3, e3_Z, lit);
 }
 
 // Eigen-system scalars of Appendix A at one face (always FP64: the
@@ -337,11 +338,11 @@ __host__ __device__ __forceinline__ void face_eig(double rho, double vn, double 
 // and weights run in T; the eigen scalars and the back-projection in FP64.
 // corr is added to: the caller passes the central term F_c in it, in FP64 without
 // its part (Delta F_{i-1/2} - Delta F_{i+3/2})/12, added here.
-template <bool WENO_Z, bool MIX, int PITCH, typename T, class AL, class ROW>
+template <bool WENO_Z, bool PLAIN, int PITCH, typename T, class AL, class ROW>
 __host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, ROW row, const Phys& ph,
                                                    double corr[7]) {
-  constexpr double SC = WenoScale<WENO_Z, MIX>;   // carried by the left rows
-  const T e3 = MIX ? T(ph.eps) * T(1.0 / 3.0) : T(ph.eps * (SC * SC / 3.0));
+  constexpr double SC = WenoScale<WENO_Z, PLAIN>;   // carried by the left rows
+  const T e3 = PLAIN ? T(ph.eps) * T(1.0 / 3.0) : T(ph.eps * (SC * SC / 3.0));
   const double e3Z = ph.eps_Z * (1.0 / 3.0);
   const bool lit = ph.weno_z == 2;
   const double sra = e.sr * e.cs;
@@ -356,12 +357,12 @@ __host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, ROW 
   // sra as beta), slow S = qa2 (as W - sra af beta) with beta = (0, 0, 0, 0, by, bz, 0),
   // and the entropy row is e0/2 - 2 qa2 W.  The projections of the five
   // interfaces on W/omg are formed once, in the fast pair, and reused.
-  // (MIX: on W, the uniform factors applied after the per-lane sum)
-  const T w0 = MIX ? T(e.g1 * e.v2) : T(-hv2), wv[5] = {T(e.vn), T(e.vt1), T(e.vt2), T(e.Bt1), T(e.Bt2)};
-  const double omg = MIX ? 1.0 : e.omg;   // carried by the rows
+  // (PLAIN: on W, the uniform factors applied after the per-lane sum)
+  const T w0 = PLAIN ? T(e.g1 * e.v2) : T(-hv2), wv[5] = {T(e.vn), T(e.vt1), T(e.vt2), T(e.Bt1), T(e.Bt2)};
+  const double omg = PLAIN ? 1.0 : e.omg;   // carried by the rows
   const T omgT = T(e.omg), gm1T = T(-e.omg);
   auto wdot = [&](const T* d) {
-    if constexpr (MIX) {
+    if constexpr (PLAIN) {
       T in = wv[0] * d[1];
 #pragma unroll
       for (int j = 1; j < 5; ++j) in += wv[j] * d[1 + j];
@@ -410,8 +411,8 @@ __host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, ROW 
       split_k(k, cW * wF + (cBy * dF[4] + cBz * dF[5]), cW * wq + (cBy * dq[4] + cBz * dq[5]), aF, aq, alu, all);
       sched_fence();
     }
-    const double fu = double(weno_split<WENO_Z, MIX>(vu, e3, e3Z, lit));
-    const double fl = double(weno_split<WENO_Z, MIX>(vl, e3, e3Z, lit));
+    const double fu = double(weno_split<WENO_Z, PLAIN>(vu, e3, e3Z, lit));
+    const double fl = double(weno_split<WENO_Z, PLAIN>(vl, e3, e3Z, lit));
     const double sp = fu + fl, sm = fu - fl;
     corr[0] += e.af * sp;
     corr[1] += e.af * e.vn * sp - e.af * e.cf * sm;
@@ -442,8 +443,8 @@ __host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, ROW 
               all);
       sched_fence();
     }
-    const double fu = double(weno_split<WENO_Z, MIX>(vu, e3, e3Z, lit));
-    const double fl = double(weno_split<WENO_Z, MIX>(vl, e3, e3Z, lit));
+    const double fu = double(weno_split<WENO_Z, PLAIN>(vu, e3, e3Z, lit));
+    const double fl = double(weno_split<WENO_Z, PLAIN>(vl, e3, e3Z, lit));
     const double sp = fu + fl, sm = fu - fl;
     corr[0] += e.as * sp;
     corr[1] += e.as * e.vn * sp - e.as * e.csl * sm;
@@ -466,7 +467,7 @@ __host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, ROW 
       if (k >= 1) vu[3 + k] = sF - a4 * sq;
       sched_fence();
     }
-    const double f4 = double(weno_split<WENO_Z, MIX>(vu, e3, e3Z, lit));
+    const double f4 = double(weno_split<WENO_Z, PLAIN>(vu, e3, e3Z, lit));
     corr[0] += f4;
     corr[1] += e.vn * f4;
     corr[2] += e.vt1 * f4;
@@ -491,8 +492,8 @@ __host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, ROW 
       split_k(k, sF, sq, aF, aq, alu, all);
       sched_fence();
     }
-    const double fu = double(weno_split<WENO_Z, MIX>(vu, e3, e3Z, lit));
-    const double fl = double(weno_split<WENO_Z, MIX>(vl, e3, e3Z, lit));
+    const double fu = double(weno_split<WENO_Z, PLAIN>(vu, e3, e3Z, lit));
+    const double fl = double(weno_split<WENO_Z, PLAIN>(vl, e3, e3Z, lit));
     const double sp = fu + fl, sm = fu - fl;
     corr[2] += -e.bz * e.s * sp;
     corr[3] += e.by * e.s * sp;

@@ -312,6 +312,12 @@ wm_status with_storage(const wm_patch* p, Fn&& fn) {
 
 bool f32_work(const wm_patch* p) { return p->f32 || p->cfg.precision == WM_MIXED; }
 
+// Whether the Jiang-Shu weights of an FP64 or FP32-state patch take the unscaled form
+// (phiN).  Where the differences vanish the scaled one has Q = 10 (eps/432)^4 in FP64,
+// 3e-290 at the line, and in FP32 squares (eps/432)^2, normal numbers down to eps 5e-17; below,
+// its 1/Q overflows from eps 5e-75 on (0/0 in equal zones), where the unscaled form goes on to 4e-77.
+bool plain_weights(const wm_patch* p) { return p->ph.eps < (p->f32 ? 1e-16 : 1e-70); }
+
 // Tile of one sweep axis of n faces in ncol columns that leaves the fewest
 // lanes idle: for each number of tiles along the axis, the shortest tile and as
 // many columns as 256 lanes and the LDS (max_zones) take.  Across the y and z
@@ -430,18 +436,22 @@ wm_status sweeps(wm_patch* p, const S* hydro, const S* bcell, SpeedKey* smax = n
   const dim3 grid(gx, (pl.nblk + gx - 1) / gx);
   const long r = prof_begin(p, K_SWEEP, mask == 7 ? 3 : 1);
   // kernel choice: work type (FP32 for the FP32 state and the mixed form),
-  // weights, and whether the waves write their signal-speed maxima
-  auto go = [&](auto tw, auto wz, auto dtmax) {
-    hipLaunchKernelGGL((sweep_kernel<decltype(wz)::value, decltype(tw), S, decltype(dtmax)::value>), grid,
-                       dim3(SW_THREADS), 0, p->stream, a);
+  // weights and their form, and whether the waves write their signal-speed maxima
+  auto go = [&](auto tw, auto wz, auto plain, auto dtmax) {
+    hipLaunchKernelGGL((sweep_kernel<decltype(wz)::value, decltype(tw), S, decltype(dtmax)::value,
+                                     decltype(plain)::value>),
+                       grid, dim3(SW_THREADS), 0, p->stream, a);
   };
-  auto pick_dt = [&](auto tw, auto wz) {
-    if (smax) go(tw, wz, std::true_type{});
-    else go(tw, wz, std::false_type{});
+  auto pick_dt = [&](auto tw, auto wz, auto plain) {
+    if (smax) go(tw, wz, plain, std::true_type{});
+    else go(tw, wz, plain, std::false_type{});
   };
   auto pick_wz = [&](auto tw) {
-    if (p->ph.weno_z) pick_dt(tw, std::true_type{});
-    else pick_dt(tw, std::false_type{});
+    constexpr bool MIXED = sizeof(tw) < sizeof(S);
+    using mixed = std::integral_constant<bool, MIXED>;
+    if (p->ph.weno_z) pick_dt(tw, std::true_type{}, mixed{});
+    else if (MIXED || plain_weights(p)) pick_dt(tw, std::false_type{}, std::true_type{});
+    else pick_dt(tw, std::false_type{}, mixed{});
   };
   if constexpr (sizeof(S) == 4) {   // FP32 state: the mixed arithmetic
     pick_wz(float{});
