@@ -151,22 +151,30 @@ __host__ __device__ __forceinline__ void face_eig_vjp(const double fp[8], const 
 // ---------------------------------------------------------------------------
 // phi = omega_0 X/3 + (omega_2 - 1/2) Y/6 and its gradient
 // ---------------------------------------------------------------------------
-template <bool WZ>
+// Jiang-Shu weights, WENO-Z weights, and the Jiang-Shu weights of the smallest eps.
+enum AdjWeights { ADJ_JS, ADJ_Z, ADJ_JS_TINY };
+// The scale of the left rows, and so of phi's arguments and value.  ADJ_JS forms products of
+// four s_k (one reciprocal for value and gradient), whose range the scale centres: it takes
+// eps from 5e-51 and arguments up to 5e50.  ADJ_JS_TINY forms products of three, unscaled, with
+// a reciprocal more, and takes eps down to 1e-102.  Below 1e-50 the host picks it.
+template <int W> constexpr double AdjScale = W == ADJ_JS ? 0x1p-43 : 1.0;
+
+template <int W>
 __host__ __device__ __forceinline__ void phiN_val_grad(double a, double b, double c, double d, double eps,
                                                        double epsZ, bool lit, double& val, double gr[4]) {
   const double t0 = a - b, t1 = a - 3.0 * b;
   const double t2 = b - c, t3 = b + c;
   const double t4 = c - d, t5 = 3.0 * c - d;
   const double X = t0 - t2, Y = t2 - t4;   // a - 2b + c, b - 2c + d
-  if constexpr (!WZ) {
-    // As phiN, with s_k = (eps + IS_k)/3, S_k = s_k^2, c = 3 p01 - m and Q = 3 p01 + m:
+  if constexpr (W == ADJ_JS) {
+    // As phiN, with s_k = (eps + IS_k)/3 (eps at the scale of the arguments), S_k = s_k^2, c = 3 p01 - m and Q = 3 p01 + m:
     // phi = (4 p12 X + c Y)/(12 Q), and with A = Y/12 - phi, B = Y/12 + phi,
     // C = X/3 - Y/12 - phi
     //   dphi/ds_0 = (6 s_0/Q)(S_1 A - 2 S_2 B),  dphi/ds_1 = (2 s_1/Q)(S_2 C + 3 S_0 A),
     //   dphi/ds_2 = (2 s_2/Q)(S_1 C - 6 S_0 B).
     (void)epsZ;
     (void)lit;
-    const double e3 = eps * (1.0 / 3.0);
+    const double e3 = eps * (AdjScale<W> * AdjScale<W> / 3.0);
     const double T0 = (13.0 / 3.0) * t0, T2 = (13.0 / 3.0) * t2, T4 = (13.0 / 3.0) * t4;
     const double s0 = fma(T0, t0, fma(t1, t1, e3));
     const double s1 = fma(T2, t2, fma(t3, t3, e3));
@@ -190,8 +198,30 @@ __host__ __device__ __forceinline__ void phiN_val_grad(double a, double b, doubl
     gr[1] = fma(-2.0, cX, cY) - u0 - 3.0 * v0 + (u1 + v1);
     gr[2] = fma(-2.0, cY, cX) - u1 + v1 + (u2 + 3.0 * v2);
     gr[3] = cY - (u2 + v2);
+    return;
+  }
+  const double g = X * (1.0 / 3.0), h = Y * (1.0 / 6.0);
+  double w0, w2, l0, l1, l2;   // normalised weights 0, 2 and dphi/dIS_k
+  if constexpr (W == ADJ_JS_TINY) {
+    // with s_k = eps + IS_k, alpha_k = d_k/s_k^2: dphi/ds_0 = (2 omega_0/s_0)(W - g),
+    // dphi/ds_1 = (2 omega_1/s_1) W, dphi/ds_2 = (2 omega_2/s_2)(W - h)
+    (void)epsZ;
+    (void)lit;
+    const double s0 = eps + 13.0 * t0 * t0 + 3.0 * t1 * t1;
+    const double s1 = eps + 13.0 * t2 * t2 + 3.0 * t3 * t3;
+    const double s2 = eps + 13.0 * t4 * t4 + 3.0 * t5 * t5;
+    const double s12 = s1 * s2, r = rcp_w(s0 * s12);
+    const double i0 = s12 * r, i1 = s0 * s2 * r, i2 = s0 * s1 * r;   // 1/s_k
+    const double al0 = i0 * i0, al1 = 6.0 * i1 * i1, al2 = 3.0 * i2 * i2;
+    const double isum = rcp_w(al0 + al1 + al2);
+    w0 = al0 * isum;
+    const double w1 = al1 * isum;
+    w2 = al2 * isum;
+    const double W3 = g * w0 + h * w2;
+    l0 = 2.0 * w0 * i0 * (W3 - g);
+    l1 = 2.0 * w1 * i1 * W3;
+    l2 = 2.0 * w2 * i2 * (W3 - h);
   } else {
-    const double g = X * (1.0 / 3.0), h = Y * (1.0 / 6.0);
     // WENO-Z: alpha_k = d_k (1 + u_k), q_k = 1/(eps_Z + IS_k), r_k = tau5 q_k, tau5 = |IS_0 - IS_2|,
     // u_k = r_k^2, or u_k = tau5 q_k^2 = r_k q_k as printed (`lit`).  Both give
     // du_k/dIS_k = -2 u_k q_k; du_k/dtau5 is 2 r_k q_k, or q_k^2 as printed.
@@ -206,26 +236,27 @@ __host__ __device__ __forceinline__ void phiN_val_grad(double a, double b, doubl
     const double u0 = r0 * s0, u1 = r1 * s1, u2 = r2 * s2;
     const double al0 = 1.0 + u0, al1 = 6.0 * (1.0 + u1), al2 = 3.0 * (1.0 + u2);
     const double isum = rcp_w(al0 + al1 + al2);
-    const double w0 = al0 * isum, w2 = al2 * isum;   // normalised weights 0, 2
-    const double W = g * w0 + h * w2;
-    // dphi/du_k = (G_k - W)/sum(alpha) * d_k, G = (g, 0, h)
-    const double M0 = (g - W) * isum, M1 = -W * isum * 6.0, M2 = (h - W) * isum * 3.0;
+    w0 = al0 * isum;
+    w2 = al2 * isum;
+    const double W3 = g * w0 + h * w2;
+    // dphi/du_k = (G_k - W3)/sum(alpha) * d_k, G = (g, 0, h)
+    const double M0 = (g - W3) * isum, M1 = -W3 * isum * 6.0, M2 = (h - W3) * isum * 3.0;
     const double ct = lit ? 1.0 : 2.0;   // du_k/dtau5 = ct s_k q_k
     const double ltau = ct * (M0 * s0 * q0 + M1 * s1 * q1 + M2 * s2 * q2);   // dphi/dtau5
     const double sg = dIS > 0.0 ? 1.0 : (dIS < 0.0 ? -1.0 : 0.0);
-    const double l0 = -2.0 * M0 * u0 * q0 + sg * ltau;   // dphi/dIS_k
-    const double l1 = -2.0 * M1 * u1 * q1;
-    const double l2 = -2.0 * M2 * u2 * q2 - sg * ltau;
-    const double cX = w0 * (1.0 / 3.0), cY = (w2 - 0.5) * (1.0 / 6.0);
-    val = cX * X + cY * Y;
-    // dIS_0/da = 26 t0 + 6 t1, dIS_0/db = -26 t0 - 18 t1
-    // dIS_1/db = 26 t2 + 6 t3, dIS_1/dc = -26 t2 + 6 t3
-    // dIS_2/dc = 26 t4 + 18 t5, dIS_2/dd = -26 t4 - 6 t5
-    gr[0] = cX + l0 * (26.0 * t0 + 6.0 * t1);
-    gr[1] = -2.0 * cX + cY + l0 * (-26.0 * t0 - 18.0 * t1) + l1 * (26.0 * t2 + 6.0 * t3);
-    gr[2] = cX - 2.0 * cY + l1 * (-26.0 * t2 + 6.0 * t3) + l2 * (26.0 * t4 + 18.0 * t5);
-    gr[3] = cY + l2 * (-26.0 * t4 - 6.0 * t5);
+    l0 = -2.0 * M0 * u0 * q0 + sg * ltau;
+    l1 = -2.0 * M1 * u1 * q1;
+    l2 = -2.0 * M2 * u2 * q2 - sg * ltau;
   }
+  const double cX = w0 * (1.0 / 3.0), cY = (w2 - 0.5) * (1.0 / 6.0);
+  val = cX * X + cY * Y;
+  // dIS_0/da = 26 t0 + 6 t1, dIS_0/db = -26 t0 - 18 t1
+  // dIS_1/db = 26 t2 + 6 t3, dIS_1/dc = -26 t2 + 6 t3
+  // dIS_2/dc = 26 t4 + 18 t5, dIS_2/dd = -26 t4 - 6 t5
+  gr[0] = cX + l0 * (26.0 * t0 + 6.0 * t1);
+  gr[1] = -2.0 * cX + cY + l0 * (-26.0 * t0 - 18.0 * t1) + l1 * (26.0 * t2 + 6.0 * t3);
+  gr[2] = cX - 2.0 * cY + l1 * (-26.0 * t2 + 6.0 * t3) + l2 * (26.0 * t4 + 18.0 * t5);
+  gr[3] = cY + l2 * (-26.0 * t4 - 6.0 * t5);
 }
 
 // ---------------------------------------------------------------------------
@@ -287,19 +318,21 @@ struct PairShape {
 // (interfaces 0..4) to f, the cotangents g[0..3] of Delta F^+ and g[4..7] of
 // Delta F^- (of uF at interface k: g[k] + g[3 + k], of uq al times their
 // difference, where they exist) and the cotangent of alpha.
-template <bool WZ>
+template <int W>
 __host__ __device__ __forceinline__ void row_split_grad(const double uF[5], const double uq[5], double al, double lf,
                                                         double eps, double epsZ, bool lit, double& f, double g[8],
                                                         double& lal) {
+  constexpr double unscale = 1.0 / AdjScale<W>;   // of the projections, which the scaled rows formed
+  lf *= unscale;
   double g4[4], pa, pb;
-  phiN_val_grad<WZ>(uF[4] - al * uq[4], uF[3] - al * uq[3], uF[2] - al * uq[2], uF[1] - al * uq[1], eps, epsZ, lit,
+  phiN_val_grad<W>(uF[4] - al * uq[4], uF[3] - al * uq[3], uF[2] - al * uq[2], uF[1] - al * uq[1], eps, epsZ, lit,
                     pa, g4);
   g[7] = g4[0] * lf; g[6] = g4[1] * lf; g[5] = g4[2] * lf; g[4] = g4[3] * lf;
   sched_fence();
-  phiN_val_grad<WZ>(uF[0] + al * uq[0], uF[1] + al * uq[1], uF[2] + al * uq[2], uF[3] + al * uq[3], eps, epsZ, lit,
+  phiN_val_grad<W>(uF[0] + al * uq[0], uF[1] + al * uq[1], uF[2] + al * uq[2], uF[3] + al * uq[3], eps, epsZ, lit,
                     pb, g4);
   g[0] = -g4[0] * lf; g[1] = -g4[1] * lf; g[2] = -g4[2] * lf; g[3] = -g4[3] * lf;
-  f = pa - pb;
+  f = (pa - pb) * unscale;
 #pragma unroll
   for (int k = 0; k < 5; ++k)
     lal += uq[k] * (k == 0 ? g[0] : (k == 4 ? -g[7] : g[k] - g[3 + k]));
@@ -327,7 +360,7 @@ __host__ __device__ __forceinline__ void pair_sums(const PairRows& r, const Pair
 // Forward and reverse of one pair up to the cotangents of its rows.  row(k) points
 // at the differences of interface k, PITCH values apart; they are read again for
 // the row cotangents rather than held.
-template <class PA, bool TWO, bool WZ, int PITCH, class ROW>
+template <class PA, bool TWO, int W, int PITCH, class ROW>
 __host__ __device__ __forceinline__ void pair_rev(const PairRows& r, ROW row, double eps, double epsZ, bool lit,
                                                   PairCot& c, PairGrad& g) {
   {
@@ -341,8 +374,8 @@ __host__ __device__ __forceinline__ void pair_rev(const PairRows& r, ROW row, do
       PA::proj(r, d, uF[k], uq[k], lF[k], lq[k]);
       sched_fence();
     }
-    row_split_grad<WZ>(uF, uq, r.alu, r.lfu, eps, epsZ, lit, c.fu, g.u, c.lalu);
-    if (TWO) row_split_grad<WZ>(lF, lq, r.all, r.lfl, eps, epsZ, lit, c.fl, g.l, c.lall);
+    row_split_grad<W>(uF, uq, r.alu, r.lfu, eps, epsZ, lit, c.fu, g.u, c.lalu);
+    if (TWO) row_split_grad<W>(lF, lq, r.all, r.lfl, eps, epsZ, lit, c.fl, g.l, c.lall);
   }
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -381,7 +414,8 @@ __host__ __device__ __forceinline__ void pair_difcot(const PairRows& r, const Pa
 // fast pair (m = 1, 7) and slow pair (m = 3, 5).  With (x, y, c, o, G, z) = (alpha_f,
 // alpha_s, c_f, c_s, Gamma_f, +1) for the fast and (alpha_s, alpha_f, c_s, c_f, Gamma_s, -1)
 // for the slow pair (c_s the slow speed here), W = omg (-v2/2, vn, vt1, vt2, Bt1, Bt2, -1):
-//   S = q (x W + z sra y beta),  A = q (G, -x c, z o y s by, z o y s bz),  q = 1/(4 a^2),
+//   S = q (x W + z sra y beta),  A = q (G, -x c, z o y s by, z o y s bz),  q = 1/(4 a^2)
+// (times SC, the AdjScale of the rows, here and in the other pairs),
 // and the right columns add to corr, with sp = fu + fl, sm = fu - fl,
 //   x sp;  x vn sp - x c sm;  x vt1 sp + z o y s by sm;  x vt2 sp + z o y s bz sm;
 //   z cs y isr by sp;  z cs y isr bz sp;  x (v2/2 + c^2 - g2 a^2) sp - G sm.
@@ -396,10 +430,10 @@ template <bool FAST> struct Magneto {
     G = x * c * e.vn - zo * bv;
   }
 };
-template <bool FAST, class ALF>
+template <bool FAST, int W, class ALF>
 __host__ __device__ __forceinline__ void magneto_rows(const FaceEig& e, ALF alf, const double lam[7], PairRows& r) {
   const Magneto<FAST> m(e);
-  const double q = e.qa2, qw = q * e.omg * m.x, qb = q * (e.sr * e.cs) * m.zs, hv2 = 0.5 * e.v2;
+  const double q = e.qa2 * AdjScale<W>, qw = q * e.omg * m.x, qb = q * (e.sr * e.cs) * m.zs, hv2 = 0.5 * e.v2;
   r.S[0] = -qw * hv2; r.S[1] = qw * e.vn; r.S[2] = qw * e.vt1; r.S[3] = qw * e.vt2;
   r.S[4] = qw * e.Bt1 + qb * e.by; r.S[5] = qw * e.Bt2 + qb * e.bz; r.S[6] = -qw;
   r.A[0] = q * m.G; r.A[1] = -q * (m.x * m.c); r.A[2] = q * m.zo * e.by; r.A[3] = q * m.zo * e.bz;
@@ -413,11 +447,12 @@ __host__ __device__ __forceinline__ void magneto_rows(const FaceEig& e, ALF alf,
   r.alu = alf(FAST ? 0 : 2);
   r.all = alf(FAST ? 6 : 4);
 }
-template <bool FAST>
+template <bool FAST, int W>
 __host__ __device__ __forceinline__ void magneto_post(const FaceEig& e, const double lam[7], const PairCot& p,
                                                       EigCot& eb) {
   const Magneto<FAST> m(e);
-  const double q = e.qa2, sra = e.sr * e.cs, z = FAST ? 1.0 : -1.0, hv2 = 0.5 * e.v2;
+  constexpr double SC = AdjScale<W>;
+  const double q = e.qa2 * SC, sra = e.sr * e.cs, z = FAST ? 1.0 : -1.0, hv2 = 0.5 * e.v2;
   const double sp = p.fu + p.fl, sm = p.fu - p.fl;
   const double lb = e.by * lam[2] + e.bz * lam[3], lB = e.by * lam[4] + e.bz * lam[5];
   // right columns
@@ -439,7 +474,7 @@ __host__ __device__ __forceinline__ void magneto_post(const FaceEig& e, const do
   const double LW = e.omg * (e.vn * p.lS[1] + e.vt1 * p.lS[2] + e.vt2 * p.lS[3] + e.Bt1 * p.lS[4] + e.Bt2 * p.lS[5] -
                              hv2 * p.lS[0] - p.lS[6]);
   const double LB = e.by * p.lS[4] + e.bz * p.lS[5], LC = e.by * p.lA[2] + e.bz * p.lA[3];
-  eb.add_q(e, m.x * LW + sra * m.zs * LB + m.G * p.lA[0] - m.x * m.c * p.lA[1] + m.zo * LC);
+  eb.add_q(e, SC * (m.x * LW + sra * m.zs * LB + m.G * p.lA[0] - m.x * m.c * p.lA[1] + m.zo * LC));
   const double qw = q * e.omg * m.x;
   lx += q * LW - q * m.c * p.lA[1];
   lv2 -= 0.5 * qw * p.lS[0];
@@ -469,12 +504,13 @@ __host__ __device__ __forceinline__ void magneto_post(const FaceEig& e, const do
 }
 
 // Alfven pair (m = 2, 6): S = (Ga/4, 0, -bz s/4, by s/4, 0, 0, 0), A = (-sr bz/4, sr by/4) on components 4, 5
-template <class ALF>
+template <int W, class ALF>
 __host__ __device__ __forceinline__ void alfven_rows(const FaceEig& e, ALF alf, const double lam[7], PairRows& r) {
+  constexpr double Q = 0.25 * AdjScale<W>;
   const double s = e.s, Ga = s * (e.bz * e.vt1 - e.by * e.vt2);
-  r.S[0] = 0.25 * Ga; r.S[1] = 0.0; r.S[2] = -0.25 * e.bz * s; r.S[3] = 0.25 * e.by * s;
+  r.S[0] = Q * Ga; r.S[1] = 0.0; r.S[2] = -Q * e.bz * s; r.S[3] = Q * e.by * s;
   r.S[4] = 0.0; r.S[5] = 0.0; r.S[6] = 0.0;
-  r.A[0] = -0.25 * e.sr * e.bz; r.A[1] = 0.25 * e.sr * e.by; r.A[2] = 0.0; r.A[3] = 0.0;
+  r.A[0] = -Q * e.sr * e.bz; r.A[1] = Q * e.sr * e.by; r.A[2] = 0.0; r.A[3] = 0.0;
   // corr += (0, 0, -bz s sp, by s sp, -bz isr sm, by isr sm, -Ga sp)
   const double lsp = s * (e.by * lam[3] - e.bz * lam[2]) - Ga * lam[6];
   const double lsm = e.isr * (e.by * lam[5] - e.bz * lam[4]);
@@ -483,24 +519,27 @@ __host__ __device__ __forceinline__ void alfven_rows(const FaceEig& e, ALF alf, 
   r.alu = alf(1);
   r.all = alf(5);
 }
+template <int W>
 __host__ __device__ __forceinline__ void alfven_post(const FaceEig& e, const double lam[7], const PairCot& c,
                                                      EigCot& eb) {
+  constexpr double Q = 0.25 * AdjScale<W>;
   const double s = e.s;
   const double sp = c.fu + c.fl, sm = c.fu - c.fl;
-  eb.bz -= s * (sp * lam[2] + 0.25 * c.lS[2]) + e.isr * sm * lam[4] + 0.25 * e.sr * c.lA[0];
-  eb.by += s * (sp * lam[3] + 0.25 * c.lS[3]) + e.isr * sm * lam[5] + 0.25 * e.sr * c.lA[1];
+  eb.bz -= s * (sp * lam[2] + Q * c.lS[2]) + e.isr * sm * lam[4] + Q * e.sr * c.lA[0];
+  eb.by += s * (sp * lam[3] + Q * c.lS[3]) + e.isr * sm * lam[5] + Q * e.sr * c.lA[1];
   eb.add_isr(e, sm * (e.by * lam[5] - e.bz * lam[4]));
-  eb.add_sr(e, 0.25 * (e.by * c.lA[1] - e.bz * c.lA[0]));
-  const double lGa = s * (0.25 * c.lS[0] - sp * lam[6]);   // Ga = s (bz vt1 - by vt2)
+  eb.add_sr(e, Q * (e.by * c.lA[1] - e.bz * c.lA[0]));
+  const double lGa = s * (Q * c.lS[0] - sp * lam[6]);   // Ga = s (bz vt1 - by vt2)
   eb.bz += lGa * e.vt1; eb.vt1 += lGa * e.bz; eb.by -= lGa * e.vt2; eb.vt2 -= lGa * e.by;
 }
 
 // entropy (m = 4): the single row L/2 = (1/2 - tau v^2/4, tau vn/2, tau vt1/2, tau vt2/2, tau Bt1/2, tau Bt2/2, -tau/2),
 // tau = (gamma - 1)/a^2 = -4 omg q
-template <class ALF>
+template <int W, class ALF>
 __host__ __device__ __forceinline__ void entropy_rows(const FaceEig& e, ALF alf, const double lam[7], PairRows& r) {
-  const double ht = -2.0 * e.omg * e.qa2;
-  r.S[0] = 0.5 - 0.5 * ht * e.v2; r.S[1] = ht * e.vn; r.S[2] = ht * e.vt1; r.S[3] = ht * e.vt2;
+  constexpr double SC = AdjScale<W>;
+  const double ht = -2.0 * SC * e.omg * e.qa2;
+  r.S[0] = 0.5 * SC - 0.5 * ht * e.v2; r.S[1] = ht * e.vn; r.S[2] = ht * e.vt1; r.S[3] = ht * e.vt2;
   r.S[4] = ht * e.Bt1; r.S[5] = ht * e.Bt2; r.S[6] = -ht;
   r.A[0] = r.A[1] = r.A[2] = r.A[3] = 0.0;
   // corr += (f4, vn f4, vt1 f4, vt2 f4, 0, 0, v2/2 f4)
@@ -509,9 +548,11 @@ __host__ __device__ __forceinline__ void entropy_rows(const FaceEig& e, ALF alf,
   r.alu = alf(3);
   r.all = r.alu;
 }
+template <int W>
 __host__ __device__ __forceinline__ void entropy_post(const FaceEig& e, const double lam[7], const PairCot& c,
                                                       EigCot& eb) {
-  const double ht = -2.0 * e.omg * e.qa2;
+  constexpr double SC = AdjScale<W>;
+  const double ht = -2.0 * SC * e.omg * e.qa2;
   const double f4 = c.fu;
   eb.vn += f4 * lam[1] + ht * c.lS[1];
   eb.vt1 += f4 * lam[2] + ht * c.lS[2];
@@ -521,7 +562,7 @@ __host__ __device__ __forceinline__ void entropy_post(const FaceEig& e, const do
   eb.add_v2(e, 0.5 * (f4 * lam[6] - ht * c.lS[0]));
   const double lht = -0.5 * e.v2 * c.lS[0] + e.vn * c.lS[1] + e.vt1 * c.lS[2] + e.vt2 * c.lS[3] +
                      e.Bt1 * c.lS[4] + e.Bt2 * c.lS[5] - c.lS[6];
-  eb.add_q(e, -2.0 * e.omg * lht);
+  eb.add_q(e, -2.0 * SC * e.omg * lht);
 }
 
 using MagnetoShape = PairShape<0, 4, true, 127>;
@@ -547,7 +588,7 @@ __host__ __device__ __forceinline__ void renew(FaceEig& e, double lam[7]) {
 // face-state cotangents follow from face_eig_vjp(eb).  One pair at a time: two at
 // once share the reads of the differences but need twice the registers, and two
 // waves per SIMD are worth more than those reads.
-template <bool WZ, int PITCH, class ALF, class ROW, class EMIT>
+template <int W, int PITCH, class ALF, class ROW, class EMIT>
 __host__ __device__ __forceinline__ void face_corr_vjp(FaceEig& e, ALF alf, double lam[7], ROW row,
                                                        const Phys& ph, EigCot& eb, double lal[7], EMIT emit) {
   const double eps = ph.eps, epsZ = ph.eps_Z;
@@ -560,11 +601,11 @@ __host__ __device__ __forceinline__ void face_corr_vjp(FaceEig& e, ALF alf, doub
     {
       renew(e, lam);
       PairRows r;
-      entropy_rows(e, alf, lam, r);
+      entropy_rows<W>(e, alf, lam, r);
       PairCot c;
-      pair_rev<EntropyShape, false, WZ, PITCH>(r, row, eps, epsZ, lit, c, gn);
+      pair_rev<EntropyShape, false, W, PITCH>(r, row, eps, epsZ, lit, c, gn);
       renew(e, lam);
-      entropy_post(e, lam, c, eb);
+      entropy_post<W>(e, lam, c, eb);
       lal[3] = c.lalu;
       eb.pin_all();
       pin(lal[3]);
@@ -572,17 +613,17 @@ __host__ __device__ __forceinline__ void face_corr_vjp(FaceEig& e, ALF alf, doub
     }
     renew(e, lam);
     PairRows ra, rn;
-    alfven_rows(e, alf, lam, ra);
+    alfven_rows<W>(e, alf, lam, ra);
     PairCot c;
-    pair_rev<AlfvenShape, true, WZ, PITCH>(ra, row, eps, epsZ, lit, c, ga);
+    pair_rev<AlfvenShape, true, W, PITCH>(ra, row, eps, epsZ, lit, c, ga);
     renew(e, lam);
-    alfven_post(e, lam, c, eb);
+    alfven_post<W>(e, lam, c, eb);
     lal[1] = c.lalu; lal[5] = c.lall;
     eb.pin_all();
     pin(lal[1]); pin(lal[5]);
     sched_fence();
     renew(e, lam);
-    entropy_rows(e, alf, lam, rn);
+    entropy_rows<W>(e, alf, lam, rn);
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
       double lD[14] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -600,12 +641,12 @@ __host__ __device__ __forceinline__ void face_corr_vjp(FaceEig& e, ALF alf, doub
     constexpr bool FAST = decltype(fast)::value;
     renew(e, lam);
     PairRows r;
-    magneto_rows<FAST>(e, alf, lam, r);
+    magneto_rows<FAST, W>(e, alf, lam, r);
     PairCot c;
     PairGrad g;
-    pair_rev<MagnetoShape, true, WZ, PITCH>(r, row, eps, epsZ, lit, c, g);
+    pair_rev<MagnetoShape, true, W, PITCH>(r, row, eps, epsZ, lit, c, g);
     renew(e, lam);
-    magneto_post<FAST>(e, lam, c, eb);
+    magneto_post<FAST, W>(e, lam, c, eb);
     double& lu = lal[FAST ? 0 : 2];
     double& ll = lal[FAST ? 6 : 4];
     lu = c.lalu; ll = c.lall;

@@ -135,7 +135,7 @@ constexpr int ADJ_ZONES = 280, ADJ_FACES = 276;
 // pair's; at 48^3 73-78, 37-39 and 35-37, where one tile spans the axis and the two
 // or three launches of its classes become one.
 constexpr int ADJ_LDS = (SW_NQ + SW_NPF) * ADJ_ZONES + SW_NQ * ADJ_FACES;   // doubles
-template <int AXIS, bool WZ>
+template <int AXIS, int W>
 __device__ __forceinline__ void adj_sweep_tile(const AdjSweepArgs& a, unsigned blk, double* lds) {
   constexpr int NC = ADJ_ZONES, ND = ADJ_FACES;
   // LDS: zone q/F, then the differences (14 rows) | zone primitives and speeds (8) |
@@ -301,7 +301,7 @@ __device__ __forceinline__ void adj_sweep_tile(const AdjSweepArgs& a, unsigned b
     face_eig(fp[0], fp[1], fp[2], fp[3], fp[4], fp[5], fp[6], fp[7], a.ph, e);
     EigCot eb;
     double lal[7], lfp[8];
-    face_corr_vjp<WZ, ND>(e, alf, lam, row, a.ph, eb, lal, emit);
+    face_corr_vjp<W, ND>(e, alf, lam, row, a.ph, eb, lal, emit);
     {
       pin(f_rho); pin(f_bt1); pin(f_bt2);   // nothing of face_eig is held for its reverse
       const double fq[8] = {f_rho, mean(FP_VN), mean(FP_VT1), mean(FP_VT2), mean(FP_BN), f_bt1, f_bt2, mean(FP_P)};
@@ -419,15 +419,15 @@ __device__ __forceinline__ void adj_sweep_tile(const AdjSweepArgs& a, unsigned b
 // each XCD takes a run of neighbouring column groups, whose lines of memory its L2
 // then fetches once (a group of 4 columns uses 32 of a line's 128 bytes).
 // AXIS 3: the three axes in one launch, x first.
-template <int AXIS, bool WZ>
+template <int AXIS, int W>
 __global__ __launch_bounds__(ADJ_THREADS, 2) void adj_sweep_kernel(AdjSweepArgs a) {
   __shared__ double lds[ADJ_LDS];
   const unsigned blk = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
   if (blk >= a.nblk) return;
-  if constexpr (AXIS < 3) adj_sweep_tile<AXIS, WZ>(a, blk, lds);
-  else if (blk < a.ax[1].blk0) adj_sweep_tile<0, WZ>(a, blk, lds);
-  else if (blk < a.ax[2].blk0) adj_sweep_tile<1, WZ>(a, blk - a.ax[1].blk0, lds);
-  else adj_sweep_tile<2, WZ>(a, blk - a.ax[2].blk0, lds);
+  if constexpr (AXIS < 3) adj_sweep_tile<AXIS, W>(a, blk, lds);
+  else if (blk < a.ax[1].blk0) adj_sweep_tile<0, W>(a, blk, lds);
+  else if (blk < a.ax[2].blk0) adj_sweep_tile<1, W>(a, blk - a.ax[1].blk0, lds);
+  else adj_sweep_tile<2, W>(a, blk - a.ax[2].blk0, lds);
 }
 
 // The sweeps of a small box in one launch: acc_h += the y and z sweeps' parts, and

@@ -574,8 +574,12 @@ wm_status launch_adj_kernel(wm_patch* p, AdjSweepArgs& a, unsigned nblk) {
   a.nblk = nblk;
   a.per_xcd = (nblk + 7) / 8;
   const dim3 grid(8 * a.per_xcd);
-  if (p->ph.weno_z) hipLaunchKernelGGL((adj_sweep_kernel<AXIS, true>), grid, dim3(ADJ_THREADS), 0, p->stream, a);
-  else hipLaunchKernelGGL((adj_sweep_kernel<AXIS, false>), grid, dim3(ADJ_THREADS), 0, p->stream, a);
+  auto go = [&](auto w) {
+    hipLaunchKernelGGL((adj_sweep_kernel<AXIS, decltype(w)::value>), grid, dim3(ADJ_THREADS), 0, p->stream, a);
+  };
+  if (p->ph.weno_z) go(std::integral_constant<int, ADJ_Z>{});
+  else if (p->ph.eps < 1e-50) go(std::integral_constant<int, ADJ_JS_TINY>{});   // see AdjScale
+  else go(std::integral_constant<int, ADJ_JS>{});
   return hip_check(hipGetLastError(), "adjoint sweep kernel");
 }
 
