@@ -948,17 +948,11 @@ namespace {
 // maxima of the eq. (cfl) signal speed (4 per block).  Up to DT_IN_UPDATE of them go
 // to the reduction scratch and the stage's update turns them into dt itself; more
 // go to the accumulator region (free until that update writes it), and
-// speed_blocks_kernel + dt_final_kernel turn them into dt before the update.  Where
-// they do not fit there either (very thin grids), the step runs the stand-alone
-// time-step pass first.
+// speed_blocks_kernel + dt_final_kernel turn them into dt before the update.
 enum class StepDt { given, in_update, blocks };
 StepDt fused_dt(const wm_patch* p) {
-  const size_t n = 4 * (size_t)p->sweep_all.nblk;
   static_assert(DT_IN_UPDATE <= 23 * RED_BLOCKS, "the keys lie in the speed and diagnostics partials");
-  if (n <= DT_IN_UPDATE) return StepDt::in_update;
-  const size_t acc_bytes = 8 * p->g.N * (p->f32 ? sizeof(float) : sizeof(double));
-  // (at most 2^31 values: the kernels index them in 32 bits)
-  return n * sizeof(SpeedKey) <= acc_bytes && n <= (size_t(1) << 31) ? StepDt::blocks : StepDt::given;
+  return 4 * (size_t)p->sweep_all.nblk <= DT_IN_UPDATE ? StepDt::in_update : StepDt::blocks;
 }
 
 wm_status launch_fused_dt(wm_patch* p) {
@@ -990,6 +984,10 @@ wm_status run_stage(wm_patch* p, int stage, StepDt how) {
     wm_status st;
     SpeedKey* keys = how == StepDt::in_update ? p->speed_part() : nullptr;
     SpeedKey* smax = how == StepDt::blocks ? reinterpret_cast<SpeedKey*>(p->acc<char>()) : keys;
+    // (8 bytes a wave against 8 elements a zone: choose_tile's tiles leave fewer than N/3
+    // waves in any box past DT_IN_UPDATE; the most, 0.26 N, where two axes have one zone)
+    if (how == StepDt::blocks && 4 * (size_t)p->sweep_all.nblk * sizeof(SpeedKey) > 8 * N * sizeof(S))
+      return fail(WM_ERR_ARG, "internal: signal speeds beyond the accumulator");
     if ((st = sweeps<S>(p, hyd_in, bcell_in, smax)) != WM_OK) return st;
     if (how == StepDt::blocks && (st = launch_fused_dt(p)) != WM_OK) return st;
     if ((st = launch_update<S>(p, stage, nullptr, keys)) != WM_OK) return st;
@@ -1034,7 +1032,6 @@ wm_status wm_step(wm_patch* p, double* dt_used) {
   if (s != WM_OK) return s;
   p->stage_done = -1;
   const StepDt how = fused_dt(p);
-  if (how == StepDt::given && (s = wm_compute_dt(p, nullptr)) != WM_OK) return s;
   for (int st = 0; st < n_stages(p); ++st)
     if ((s = run_stage(p, st, st == 0 ? how : StepDt::given)) != WM_OK) return s;
   if (dt_used) {
