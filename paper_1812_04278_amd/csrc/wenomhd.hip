@@ -636,17 +636,21 @@ wm_status launch_adj_sweeps(wm_patch* p, const double* hydro, const double* bcel
   return s;
 }
 
-// Whether the three adjoint sweeps go in one launch.  They do where a tile spans each
-// axis: every sweep is then one launch of at most a few hundred blocks, one after the
-// other because all add into the same arrays.  In one launch y and z store into arrays
-// of their own (the face fluxes of the forward step, free here; those of an FP32 state
-// are too short) and adj_collect_kernel adds them up; zone B comes with the transport
-// cotangents.  Five launches fewer and no idle tail per sweep: a step's backward takes
-// 113 us against 249 in 16^3, 172 against 263 in 36x31x32, 353 against 386 in 48^3, 610
-// against 638 in 64^3.  With several tiles on an axis, whose classes need launches of
-// their own, the arrays apart would only be more traffic.
+// Whether the three adjoint sweeps go in one launch.  They do in small boxes where a tile
+// spans each axis: every sweep is then one launch, one after the other because all add
+// into the same arrays.  In one launch y and z store into arrays of their own (the face
+// fluxes of the forward step, free here; those of an FP32 state are too short) and
+// adj_collect_kernel adds them up; zone B comes with the transport cotangents.  Five
+// launches fewer and no idle tail per sweep, against 16 N doubles more written and read.  A step's
+// backward, us, separate and in one launch: 16^3 232, 107; 36x31x32 259, 165; 48^3 383, 351;
+// 64^3 671, 612; 250x32x32 712, 664; 76^3 1,231, 1,212; 80^3 (512,000 zones) 1,345, 1,318, though
+// 32x126x126 (508,000) 1,301, 1,323; past the line 83^3 (572,000) 1,486, 1,501; 250x60x40
+// (600,000) 1,548, 1,607; 106^3 3,156, 3,292; 126^3 4,976, 5,069.  With several tiles on an axis, whose
+// classes need launches of their own, the arrays apart would only be more traffic.
+constexpr size_t ADJ_ONE_LAUNCH = size_t(1) << 19;   // zones
 bool adjoint_one_launch(const wm_patch* p) {
-  return !p->f32 && p->adj_plan[0].n == 1 && p->adj_plan[1].n == 1 && p->adj_plan[2].n == 1;
+  return !p->f32 && p->g.N <= ADJ_ONE_LAUNCH && p->adj_plan[0].n == 1 && p->adj_plan[1].n == 1 &&
+         p->adj_plan[2].n == 1;
 }
 
 wm_status check_adjoint(wm_patch* p, void* adj) {
