@@ -580,9 +580,11 @@ __device__ __forceinline__ double speed_of(SpeedKey k) {
 
 // The time step of a step's first stage, by every block of its update for
 // itself: in a small box (at most DT_IN_UPDATE keys) reading them again is
-// cheaper than the two launches that reduce them first (16^3 step 62.5 -> 58 us,
-// 228 keys; even at 32^3, 1,536 keys).
-constexpr unsigned DT_IN_UPDATE = 1536;
+// cheaper than the two launches that reduce them first.  A step, us, with the launches and in
+// the update: 20^3 (408 keys) 60.7, 57.1; 32^3 (1,536) 83.7, 79.8; 36^3 (2,232) 98.2, 95.3; 256x16x16
+// (3,368) 108.9, 107.2; 43^3 (4,056) 126.8, 125.7, FP32 state 111.7, 110.4.  They break even past the line:
+// 45^3 (4,860) 130.7, 130.7; 256x24x16 (4,932) 121.2, 121.2; 48^3 (5,540) 134.7, 135.1.
+constexpr unsigned DT_IN_UPDATE = 4096;
 template <typename S>
 __device__ __forceinline__ double stage0_dt(const UpdateArgs<S>& a) {
   __shared__ SpeedKey red[3][4];
@@ -799,7 +801,7 @@ __global__ __launch_bounds__(256) void update_pair_kernel(UpdateArgs<S> a) {
   static_assert((RK == 3 && STAGE >= 0 && STAGE < 3) || (RK == 4 && STAGE >= 0 && STAGE < 4), "stage of the scheme");
   const Grid& g = a.g;
   double dt = 0.0;
-  if constexpr (STAGE == 0 && !ROWS) {   // (a box of 256-zone rows has more keys)
+  if constexpr (STAGE == 0 && !ROWS) {   // (with keys the threads are numbered, also where nx is a multiple of 256)
     if (a.keys) dt = stage0_dt(a);
   }
   const int nx = g.nx;

@@ -23,6 +23,8 @@ CASES = [
     ("rk4-wenoz", (67, 61, 65), dict(integrator=B.WM_RK4, weights=B.WM_WENO_Z)),
     ("walls", (62, 59, 60), dict(walls=(1, 0, 1))),
     ("thin", (8, 8, 400), dict()),
+    ("thin-rows", (256, 16, 16), dict()),                              # 3,368
+    ("thin-rows", (256, 24, 16), dict()),                              # 4,932
     ("thin-f32", (1, 2, 8192), dict(precision=B.WM_MIXED_F32STATE)),
 ]
 
