@@ -16,13 +16,6 @@
 namespace wm {
 
 // ---------------------------------------------------------------------------
-// phi_N: value and gradient with respect to its four arguments (Sect. 2.2).
-// With omega = alpha/sum, g = X/3, h = Y/6 (X = a-2b+c, Y = b-2c+d) and
-// W = g omega_0 + h omega_2, dphi/dalpha_k = (G_k - W)/sum, G = (g, 0, h).
-// WENO-Z: alpha_k = d_k (1 + r_k^2), r_k = tau_5/(eps_Z + IS_k), tau_5 = |IS_0 - IS_2|.
-// ---------------------------------------------------------------------------
-
-// ---------------------------------------------------------------------------
 // face eigen-system scalars: cotangents of the FaceEig members -> face state
 // ---------------------------------------------------------------------------
 // Materialises x in a register at this point of the program: the compiler may
@@ -149,7 +142,9 @@ __host__ __device__ __forceinline__ void face_eig_vjp(const double fp[8], const 
 }
 
 // ---------------------------------------------------------------------------
-// phi = omega_0 X/3 + (omega_2 - 1/2) Y/6 and its gradient
+// phi_N = omega_0 X/3 + (omega_2 - 1/2) Y/6 (X = a-2b+c, Y = b-2c+d; Sect. 2.2) and its
+// gradient with respect to its four arguments.  With omega = alpha/sum, g = X/3, h = Y/6
+// and W3 = g omega_0 + h omega_2, dphi/dalpha_k = (G_k - W3)/sum, G = (g, 0, h).
 // ---------------------------------------------------------------------------
 // Jiang-Shu weights, WENO-Z weights, and the Jiang-Shu weights of the smallest eps.
 enum AdjWeights { ADJ_JS, ADJ_Z, ADJ_JS_TINY };

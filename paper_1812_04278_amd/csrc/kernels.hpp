@@ -27,9 +27,6 @@ struct Grid {
     return ((size_t)k * ny + j) * nx + i;
   }
   // the same index in 32 bits (N < 2^31 always)
-  __device__ __forceinline__ unsigned at32(int i, int j, int k) const {
-    return ((unsigned)k * (unsigned)ny + (unsigned)j) * (unsigned)nx + (unsigned)i;
-  }
 };
 
 // q / n for q < 2^31 and n <= 2^13 from inv = 1.0 / n, exactly: (q + 1/2) / n is at
@@ -99,7 +96,7 @@ template <typename TW> struct SweepTile {
 constexpr int SW_THREADS = 256;
 constexpr int SW_HL = 2, SW_HR = 3;          // stencil zones i-2 .. i+3
 constexpr int SW_NQ = 14;                    // q (7) and F (7) per zone
-constexpr int SW_NP = 11;                    // rho, v_n, v_t1, v_t2, B_n, B_t1, B_t2, P, c_f, c_A, c_s
+// zone primitives and speeds: rho, v_n, v_t1, v_t2, B_n, B_t1, B_t2, P, c_f, c_A, c_s
 enum { P_RHO = 0, P_VN, P_VT1, P_VT2, P_BN, P_BT1, P_BT2, P_P, P_CF, P_CA, P_CS };
 // the forward sweep's zone primitives and speeds: rho, B_t1 and B_t2 are read
 // from the zone q in LDS instead
@@ -119,8 +116,8 @@ __device__ __forceinline__ double nanmax(double a, double b) {   // NaN-propagat
 // stand-alone time-step pass both take it from zone_prologue, so their maxima
 // agree bitwise.  Non-negative doubles order like their bit patterns read as
 // unsigned integers, so the maximum is an integer max.  A fast speed that is
-// not real (a negative argument of its square roots, which sqrt_nr returns as
-// a negative value) makes the speed negative, and a NaN state makes it NaN:
+// not real (a negative c_fast^2, or argument of the root in it, gives a negative
+// value or NaN) makes the speed negative or NaN, and a NaN state makes it NaN:
 // both keys lie above every non-negative speed's, and dt_final_kernel turns
 // such a maximum into NaN.
 typedef unsigned long long SpeedKey;

@@ -255,9 +255,9 @@ __host__ __device__ __forceinline__ T weno_split(const T v[8], T e3, double e3_Z
 // the Lax-Friedrichs split, which is folded into every left row.
 struct FaceEig {
   double vn, vt1, vt2, Bt1, Bt2;
-  double a2, cs, sr, isr, cf, cf2, csl, csl2;
+  double cs, sr, isr, cf, csl;
   double by, bz, s, af, as;
-  double v2, Gf, Ga, Gs, qa2, tau, g1, g2, omg;
+  double v2, qa2, g1, g2, omg;
 };
 
 // alpha_f^2 = (D + dab) / (2D) and alpha_s^2 = (D - dab) / (2D) of eq. (alpha),
@@ -281,22 +281,21 @@ __host__ __device__ __forceinline__ void face_eig(double rho, double vn, double 
   e.isr = rsq_nr(rho);
   e.sr = rho * e.isr;
   const double irho = e.isr * e.isr;
-  e.a2 = gamma * P * irho;
+  const double a2 = gamma * P * irho;
   // one reciprocal square root each for (c_s, 1/a^2) and (c_fast, 1/c_fast);
   // c_slow = a |b_n| / c_fast
-  const double ics = rsq_nr(e.a2);
-  e.cs = e.a2 * ics;
+  const double ics = rsq_nr(a2);
+  e.cs = a2 * ics;
   const double ia2 = ics * ics;
   const double Bperp2 = Bt1 * Bt1 + Bt2 * Bt2;
   const double b2 = (Bn * Bn + Bperp2) * irho;
-  const double dab = e.a2 - b2;
-  const double p4 = 4.0 * e.a2 * (Bperp2 * irho);
+  const double dab = a2 - b2;
+  const double p4 = 4.0 * a2 * (Bperp2 * irho);
   const double D = sqrt_nr(dab * dab + p4);
-  e.cf2 = 0.5 * (e.a2 + b2 + D);
-  const double icf = rsq_pos(e.cf2);
-  e.cf = e.cf2 * icf;
+  const double cf2 = 0.5 * (a2 + b2 + D);
+  const double icf = rsq_pos(cf2);
+  e.cf = cf2 * icf;
   e.csl = e.cs * (fabs(Bn) * e.isr) * icf;
-  e.csl2 = e.csl * e.csl;
   if (Bperp2 > ph.eps_B) {
     const double ib = rsq_nr(Bperp2);
     e.by = Bt1 * ib;
@@ -319,12 +318,7 @@ __host__ __device__ __forceinline__ void face_eig(double rho, double vn, double 
   e.g2 = ph.g2;
   e.omg = 1.0 - gamma;
   e.qa2 = 0.25 * ia2;
-  e.tau = (gamma - 1.0) * ia2;
   e.v2 = vn * vn + vt1 * vt1 + vt2 * vt2;
-  const double bv = e.by * vt1 + e.bz * vt2;
-  e.Gf = e.af * e.cf * vn - e.as * e.csl * e.s * bv;
-  e.Ga = e.s * (e.bz * vt1 - e.by * vt2);
-  e.Gs = e.as * e.csl * vn + e.af * e.cf * e.s * bv;
 }
 
 // Characteristic part of the interface flux at face i+1/2,
@@ -348,8 +342,7 @@ __host__ __device__ __forceinline__ void face_corr(const FaceEig& e, AL al, ROW 
   const double sra = e.sr * e.cs;
   const double qa2 = e.qa2 * SC;
   // Gamma_f, Gamma_s, Gamma_a and the squares of the speeds are formed in the pair
-  // that uses them, not held from face_eig: the fast pair's peak decides the
-  // registers
+  // that uses them: the fast pair's peak decides the registers
   const double hv2 = 0.5 * e.v2;
   T vu[8], vl[8];
   // The fast and slow left rows share W = (g1 v2, omg vn, omg vt1, omg vt2,
