@@ -16,8 +16,9 @@
 //                        launch holds the sweeps of the three axes
 //   adj_glue kernels     the RK3 stage combinations
 //   init_adj kernels     transpose of the initial-state map (curl_h A, m, E)
-// Accumulation orders are fixed (LDS sub-rounds separated by barriers, no
-// atomics), so results are bitwise reproducible.
+// Accumulation orders are fixed, so results are bitwise reproducible: none of the
+// additions in memory are atomic, and those in LDS (by the LDS unit) meet at one address
+// in rounds, separated by barriers or issued in turn by one wave.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -321,8 +321,11 @@ bool plain_weights(const wm_patch* p) { return p->ph.eps < (p->f32 ? 1e-16 : 1e-
 // Tile of one sweep axis of n faces in ncol columns that leaves the fewest
 // lanes idle: for each number of tiles along the axis, the shortest tile and as
 // many columns as 256 lanes and the LDS (max_zones) take.  Across the y and z
-// axes (xacross) rows shorter than 64 bytes are weighed down: 64 x 4 tiles ran
-// 4% slower than 32 x 8 in FP64, though both use every lane.
+// axes (xacross) rows shorter than 64 and than 32 bytes are weighed down.  A step
+// without the weights and with them: 76^3 (3 columns, 9) 480, 405 us; 128^3 (1, 8) 2,441, 1,680,
+// FP32 state (2, 16) 1,697, 1,165; 104^3 (7, 9: 2.5% more blocks) 968, 958.  In an FP32 state
+// 11 to 15 columns cost less than the weight says: 54^3 149.6, 150.6, 66^3 226.1, 227.0.
+// The second round of a prologue of more than 256 zones is not counted.
 SweepAxis choose_tile(int n, int ncol, int max_zones, bool xacross, size_t es) {
   SweepAxis best{};
   double best_cost = 0.0;
@@ -357,6 +360,11 @@ void set_divisors(SweepAxis& x, int ncol) {
 // the y and z axes short rows are weighed down a little: an XCD fetches a line once
 // for its neighbouring blocks, so 2 and 4 columns ran alike (5.25 and 5.27 ms per
 // 128^3 step adjoint; blocks dealt to the XCDs in turn, 5.79 and, 2 columns, 6.76).
+// Tiles of 64 faces, whose waves each add to a column of their own without barriers, are
+// preferred: 127^3 4.85 ms against 5.13 (127 x 2), 128^3 4.83 against 5.04, 64x64x255 2.37 against
+// 2.83.  Tiles of 32, 16 and 8 go without barriers too, but the same weight for them trades
+// spanning tiles for more launches: 93^3 2.50 -> 2.33 and 128x96x64 2.06 -> 1.99 ms, though
+// 50x40x91 568 -> 597, 40x25x160 570 -> 601 and 96x90x90 2,377 -> 2,402 us.
 TilePlan adjoint_plan(int n, int ncol, bool xacross) {
   TilePlan best{};
   double best_cost = 0.0;
@@ -373,7 +381,7 @@ TilePlan adjoint_plan(int n, int ncol, bool xacross) {
       cost += (rounds < 4.0 ? std::ceil(rounds) : rounds + 0.5) + 0.2;
     }
     cost *= !xacross || tb >= 8 ? 1.0 : (tb >= 4 ? 1.02 : 1.06);
-    if (ta == 64) cost *= 0.94;   // each wave adds to its own column: fewer barriers
+    if (ta == 64) cost *= 0.94;
     if (best.n == 0 || cost < best_cost) {
       best = pl;
       best.ax.ta = ta;
